@@ -530,34 +530,68 @@ void list_radii(const relres_ctx* c, std::vector<double>& skin, std::vector<doub
     }
 }
 
+// Mean members of a stencil of a grid: the candidates of a home cell.
+double stencil_members(const GridHost& g)
+{
+    const int cells = g.ncell / std::max(1, g.nsys);
+    return g.ncell > 0 ? (double)g.members / g.ncell * std::min(g.div == 1 ? 27 : 125, cells) : 0.0;
+}
+
 // Home rows per wave of the list kernel (1 .. kRowsPerWave).  A wave tests
-// its rows one after another, so a launch with few waves spreads its tests
-// over more of them: when both lists together give fewer than 2048 waves at
-// 8 rows, each grid takes the largest power of two that still gives it 2000
-// waves.  Launches of at least 2048 waves at 16 rows take 16, so each
-// stencil is loaded for as many rows as possible; the others 8.  Measured on
-// MI355X: the 20480-atom liquid (3072 waves at 8 rows) builds slower with
-// fewer or more rows per wave (50 µs at 8, 58 µs at 16); 6000-atom hexane
-// dynamics (1000 waves) takes 5 % less time per step at 2 / 1 rows than at
-// 8 / 8; the 256-replica batch (1.44 M rows) runs 3 % faster at 16 than at
-// 8.  A caller override (relres_set_list_launch, relres_autotune) comes
+// its rows one after another and sets up each of their cells, so few rows
+// spread a small launch over more waves and many rows share a cell's set-up.
+// Measured on MI355X (list builds over graph replays): launches of at least
+// 262144 rows take 16 rows (256 replicas, 1.5 M rows: 442 us per build
+// against 492 at 8); smaller ones 8 (98304-atom copolymer, 123000 rows: 69.5
+// against 71.2 us at 16; 48000-atom hexane, 64000 rows: 53.4 against 60.7);
+// where that gives fewer than 2048 waves, each grid the largest power of two
+// that still gives it 2000 waves (6000-atom hexane: 30 us at 2 / 1 rows, 42
+// at 8 / 8).  A crowded stencil (long loops per row) halves 8 rows while the
+// launch stays below 4096 waves (20480 atoms at 14 A: 39.0 us at 4 rows, 42.0
+// at 8).  A caller override (relres_set_list_launch, relres_autotune) comes
 // first; then the environment variable RELRES_LIST_ROWS="atom,site" (for
 // tuning runs).
-int list_rows_per_wave(bool site, long long members, long long launch_rows, int rows)
+int list_rows_per_wave(const GridHost& g, long long launch_rows, int rows)
 {
     if (rows >= 1 && rows <= kRowsPerWave) return rows;
     if (const char* e = std::getenv("RELRES_LIST_ROWS")) {
         int a = 0, b = 0;
         if (std::sscanf(e, "%d,%d", &a, &b) == 2) {
-            const int r = site ? b : a;
+            const int r = g.site ? b : a;
             if (r >= 1 && r <= kRowsPerWave) return r;
         }
     }
-    if (launch_rows >= 2048LL * 16) return 16;
+    if (launch_rows >= 262144) return 16;
     int r = 8;
-    if (launch_rows >= 2048LL * r) return r;
-    while (r > 1 && members < 2000LL * r) r >>= 1;
+    if (launch_rows >= 2048LL * r)
+        return stencil_members(g) > kCrowdedStencil && launch_rows < 4096LL * r ? r / 2 : r;
+    while (r > 1 && g.members < 2000LL * r) r >>= 1;
     return r;
+}
+
+// The FP32 filter of the list kernel (GeomDev::filter_lo, filter_hi) for list
+// radius rl.  Positions relative to a row of the home cell are rounded to
+// FP32 (2^-24 of their size, at most A along any axis: reach cells of edge e
+// away, or half a box), subtracted (another 2^-24 of at most 2 A), and where
+// the difference is not the nearest image yet, folded with the rounded box
+// edge: below d = 8 * 2^-24 A per axis in all.  A pair at distance r then has
+// an FP32 distance within sqrt(3) d of r, and its square is rounded by less
+// than 8 * 2^-24.  Where that bound says nothing (or a box does not fit
+// FP32), every pair is left to the FP64 recipe.
+void list_filter(GeomDev& d, double rl, int reach)
+{
+    double A = 0.0;
+    for (int k = 0; k < 3; ++k) A = std::max(A, std::min(0.5 * d.box[k], reach * d.box[k] / d.n[k]));
+    const double u = std::ldexp(1.0, -24), slack = std::sqrt(3.0) * 8.0 * u * A * 1.01;
+    if (!(slack < 0.5 * rl) || !(std::max({d.box[0], d.box[1], d.box[2], rl}) < 1e12)) {
+        d.filter_lo = -1.0f;
+        d.filter_hi = INFINITY;
+        return;
+    }
+    const double lo = (rl - slack) * (rl - slack) * (1.0 - 8.0 * u);
+    const double hi = (rl + slack) * (rl + slack) * (1.0 + 8.0 * u);
+    d.filter_lo = std::nextafter((float)lo, 0.0f);
+    d.filter_hi = std::nextafter((float)hi, INFINITY);
 }
 
 // launch_rows: rows of both grids (they share the list-kernel launch);
@@ -666,7 +700,8 @@ int setup_grid(GridHost& g, const std::vector<double>& rl_sys, const std::vector
     // rows and list-kernel waves of every grid
     long long all_members = 0;
     for (int sy = 0; sy < nsys; ++sy) all_members += members_sys[sy];
-    g.rpw = list_rows_per_wave(g.site, all_members, launch_rows, rows_per_wave);
+    g.members = (int)all_members;
+    g.rpw = list_rows_per_wave(g, launch_rows, rows_per_wave);
     std::vector<GeomDev> geom(nsys);
     int rows = 0, waves = 0;
     double densest = 0.0;
@@ -678,6 +713,7 @@ int setup_grid(GridHost& g, const std::vector<double>& rl_sys, const std::vector
             d.n[k] = nn[3 * sy + k];
             d.inv_cell[k] = d.n[k] / box[k];
             d.box[k] = box[k];
+            d.inv_box[k] = 1.0 / box[k];
             d.half[k] = 0.5 * box[k];
         }
         d.cell_base = cell_base[sy];
@@ -686,6 +722,7 @@ int setup_grid(GridHost& g, const std::vector<double>& rl_sys, const std::vector
         d.wave_base = waves;
         d.rl2 = rl_sys[sy] * rl_sys[sy];
         d.half_skin2 = 0.25 * skin_sys[sy] * skin_sys[sy];
+        list_filter(d, rl_sys[sy], div + 1);
         rows += members_sys[sy];
         waves += (members_sys[sy] + g.rpw - 1) / g.rpw;
         // expected neighbours within the system's list radius
@@ -973,6 +1010,7 @@ int enqueue_build(relres_ctx* c, const double* pos, const double* box, hipStream
                              c->d_user2arow.as<int>(),
                              c->d_a_rec.as<int4>(), c->d_s_rec.as<int4>(),
                              c->d_status.as<Status>(), lists_per_wave(c), c->cand,
+                             std::max(stencil_members(c->ga), sites ? stencil_members(c->gs) : 0.0),
                              c->ga.div == 2 ? 5 : 3, (sites && c->gs.div == 2) ? 5 : 3, s));
         // A captured build copies nothing: the status only accumulates (see
         // Status), so relres_check_lists copies it once after the caller has
@@ -1689,7 +1727,9 @@ int relres_autotune(relres_ctx* c, const double* pos, const double* box, void* s
         out->cell_div_site = sites ? c->gs.div : 0;
         out->rows_atom = c->ga.rpw;
         out->rows_site = sites ? c->gs.rpw : 0;
-        out->cand_per_lane = list_candidates(c->ga.waves + (sites ? c->gs.waves : 0), c->cand);
+        out->cand_per_lane = list_candidates(c->ga.waves + (sites ? c->gs.waves : 0), c->cand,
+                                             std::max(stencil_members(c->ga),
+                                                      sites ? stencil_members(c->gs) : 0.0));
         // force kernel: lanes per atom row and per hybrid row
         const size_t fb = (size_t)c->n * 3 * (c->precision == 32 ? sizeof(float) : sizeof(double));
         TRY(ensure(f, fb, &gen));

@@ -55,10 +55,15 @@ struct GeomDev {
     int cell_base;            // global rank of this grid's first cell
     double inv_cell[3];       // n_k / L_k
     double box[3];            // L_k of the system
+    double inv_box[3];        // 1 / L_k
     double half[3];           // L_k / 2
     int row_base;             // global row of this grid's first member
     int members;
     int wave_base;            // first wave of this grid in the list kernel
+    // FP32 filter of the list kernel: a squared distance below filter_lo is
+    // inside the list radius, one above filter_hi outside (list_filter in the
+    // host code); in between the FP64 recipe decides
+    float filter_lo, filter_hi;
     int pad;
     double rl2;               // list radius squared (r_+ + the system's skin)^2
     double half_skin2;        // (the system's skin / 2)^2
@@ -203,13 +208,16 @@ hipError_t launch_place(GridDev* grids_dev, int ncell_a, int ncell_s, long long 
                         int* user2arow, hipStream_t s);
 // per_wave: one wave per home cell (small cells) instead of one block per cell
 // Candidates per lane of the row-group list kernel (2 or 4) for a launch of
-// total_waves waves; cand = 2 or 4 forces the value, 0 chooses it.
-int list_candidates(int total_waves, int cand);
+// total_waves waves; cand = 2 or 4 forces the value, 0 chooses it, also from
+// the mean members of a stencil (the larger of the two grids').
+constexpr double kCrowdedStencil = 1024.0;   // more members than that: a crowded stencil
+int list_candidates(int total_waves, int cand, double stencil_members);
 // stencil_a, stencil_s: 3 or 5 (GridDev::stencil of each grid); the
 // block-per-cell kernel only serves two 27-cell stencils
 hipError_t launch_lists(GridDev* grids_dev, int ncell_a, int ncell_s, int waves_a, int waves_s,
                         TopoDev topo, const int* user2arow, int4* a_rec, int4* s_rec, Status* st,
-                        bool per_wave, int cand, int stencil_a, int stencil_s, hipStream_t s);
+                        bool per_wave, int cand, double stencil_members, int stencil_a,
+                        int stencil_s, hipStream_t s);
 // cut64 = {r_s-, r_s+, r_c-, r_c+, and their squares} of every type pair, or
 // per_pair: the distances of each type pair come from a.pcut32 / a.pcut64
 hipError_t launch_forces(const ForceArgs& a, const double* cut64, bool per_pair, int pair_math,

@@ -372,6 +372,15 @@ __device__ __forceinline__ double readfirst_d(double v)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+__device__ __forceinline__ float readfirst_f(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ float readlane_f(float v, int l)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+
 __device__ __forceinline__ double readlane_d(double v, int l)
 {
     const long long b = __double_as_longlong(v);
@@ -626,27 +635,6 @@ __device__ __forceinline__ void clear_bucket_counts(const GridDev* __restrict__ 
     }
 }
 
-// Membership with the periodic shift of the candidate's stencil slot known in
-// advance.  When a grid has at least four cells along an axis, a neighbour
-// cell reached without wrapping lies within two cells (< L/2) of the home
-// atom, and one reached by wrapping lies more than L/2 away in the direction
-// of the wrap.  The single-shift recipe therefore applies exactly `shift`
-// (0 or -+L), and (x_j - x_i) + shift rounds exactly as the recipe's
-// (x_j - x_i) followed by "-= L" / "+= L".
-__device__ __forceinline__ bool member_shifted(double xi, double yi, double zi, double xj,
-                                               double yj, double zj, double sx, double sy,
-                                               double sz, double rl2)
-{
-#pragma clang fp contract(off)
-    const double dx = (xj - xi) + sx;
-    const double dy = (yj - yi) + sy;
-    const double dz = (zj - zi) + sz;
-    const double r2 = (dx * dx + dy * dy) + dz * dz;
-    return r2 < rl2;
-}
-
-constexpr int kResidentListWaves = 256 * 4 * 3;
-
 // A compile-time bool as a value (selects one of two instantiations of a
 // generic lambda).
 template <bool B>
@@ -698,19 +686,33 @@ __device__ __forceinline__ int stencil_rank(const GeomDev& G, RELRES_GLOBAL cons
 // candidates of the home cell's stencil are loaded straight into registers,
 // K per lane per round (candidate q in lane q % 64), and every home row of
 // the cell tests them there, so a candidate is read from memory once per cell
-// and never through LDS.  A larger K takes fewer rounds but more registers:
-// it pays when all waves of the launch are resident at once.  Candidates are
-// visited in stencil-slot order, each row's entries are appended in that
-// order with a wave ballot.  Only wave-level synchronisation is used, so
-// waves of one block may run different trip counts.  S is the stencil width
-// of the grid the wave's rows belong to (3: cells of one list radius; 5:
-// cells of half of it, fewer candidates per row and more cells per wave).
-template <int K, int S>
+// and never through LDS.  Candidates are visited in stencil-slot order, each
+// row's entries are appended in that order with a wave ballot.  Only
+// wave-level synchronisation is used, so waves of one block may run different
+// trip counts.  S is the stencil width of the grid the wave's rows belong to
+// (3: cells of one list radius; 5: cells of half of it, fewer candidates per
+// row and more cells per wave).
+//
+// Large launches are bound by vector issue, small ones by the chain of one
+// wave, so the distance test is a filter in FP32: positions relative to the
+// cell's first row (taken in FP64, nearest image, once per candidate and
+// cell) are within 2^-24 of their size, and a squared distance outside
+// [filter_lo, filter_hi] (GeomDev, an error bound around the list radius) is
+// decided by it.  A distance inside (about one test in 10^5) is decided by
+// the FP64 membership recipe, so the lists are those of that recipe.  The
+// filter takes 8 vector instructions per test instead of 12, 3 lane reads
+// per row instead of 6 and a third of the candidate registers (2 candidates:
+// 64 or 70 vector registers and 7 to 8 waves per SIMD instead of 88 and 5).
+// With the order and shapes of the launch (k_lists_wave, list_rows_per_wave)
+// one build went from 106 to 70 us for the 98304-atom copolymer, 607 to 440
+// for 256 replicas, 90 to 54 for 48000-atom hexane, 47.6 to 39.6 for 20480
+// atoms at 14 A (graph replays of 10 builds).
+// MolOnly: the only exclusions are the same-molecule ones.
+template <int K, int S, bool MolOnly>
 __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool site, int max_excl,
                                           const TopoDev& topo, const int* __restrict__ user2arow,
                                           int4* __restrict__ a_rec, int4* __restrict__ s_rec,
-                                          Status* __restrict__ st, int* slot_base,
-                                          double* slot_shift, int* slot_win,
+                                          Status* __restrict__ st, int* slot_base, int* slot_win,
                                           int* excl_lds)
 {
     using St = Stencil<S>;
@@ -725,29 +727,29 @@ __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool
     // no rows have no waves)
     const int gs_lo = g.nsys > 1 ? __builtin_amdgcn_readfirstlane(g.wave_sys[lw]) : 0;
     const GeomDev& G = g.geom[gs_lo];
-    // the grid's cell counts are wave-uniform: readfirstlane keeps them (and
-    // the cell arithmetic on them) in scalar registers, where the compiler
-    // would otherwise hold the values it read in vector registers (the box
-    // edges stay there: the selects of the image shifts take them so)
+    // the grid's values are wave-uniform: readfirstlane keeps them in scalar
+    // registers, where the compiler would otherwise hold them in vector ones
     const int n0 = __builtin_amdgcn_readfirstlane(G.n[0]);
     const int n1 = __builtin_amdgcn_readfirstlane(G.n[1]);
     const int n2 = __builtin_amdgcn_readfirstlane(G.n[2]);
-    const double Lx = G.box[0], Ly = G.box[1], Lz = G.box[2];
-    // known image shifts: every stencil slot a distinct cell with one
-    // periodic image (at least four cells per axis for the 27-cell stencil,
-    // five for the 125-cell one)
+    const double Lx = readfirst_d(G.box[0]), Ly = readfirst_d(G.box[1]), Lz = readfirst_d(G.box[2]);
+    const double iLx = readfirst_d(G.inv_box[0]), iLy = readfirst_d(G.inv_box[1]),
+                 iLz = readfirst_d(G.inv_box[2]);
+    const float flo = readfirst_f(G.filter_lo), fhi = readfirst_f(G.filter_hi);
+    // With enough cells per axis (S = 3: 5, S = 5: 7) every stencil cell is
+    // less than half a box from the home cell's rows, so the difference of two
+    // positions relative to one of those rows is their nearest image already.
     // (wave-uniform; readfirstlane makes the choice a scalar branch)
-    const bool known_shift = __builtin_amdgcn_readfirstlane(
-        S == 3 ? (n0 >= 4 && n1 >= 4 && n2 >= 4) : (n0 >= 5 && n1 >= 5 && n2 >= 5));
+    constexpr int kDirect = S == 3 ? 5 : 7;
+    const bool direct = __builtin_amdgcn_readfirstlane(n0 >= kDirect && n1 >= kDirect &&
+                                                       n2 >= kDirect);
     const int R = g.rows_per_wave;
     const int r0 = __builtin_amdgcn_readfirstlane(G.row_base + (lw - G.wave_base) * R);
     const int r1 = __builtin_amdgcn_readfirstlane(min(G.row_base + G.members, r0 + R));
-    const double hx = G.half[0], hy = G.half[1], hz = G.half[2];
-    const double rl2 = readfirst_d(G.rl2);
     const int cap = g.cap;
     const int* __restrict__ excl_off = topo.excl_off;
     const int* __restrict__ excl_idx = topo.excl_idx;
-    const int same_mol = topo.same_mol;
+    const int same_mol = MolOnly ? 1 : topo.same_mol;
     // exclusion lists of the wave's home rows, staged once (kRowsPerWave x max_excl)
     int* my_excl = excl_lds + wv * kRowsPerWave * max_excl;
 
@@ -756,17 +758,35 @@ __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool
     const int myrow = r0 + lane;
     double mx = 0.0, my = 0.0, mz = 0.0;
     int mt = 0, mmol = 0;
-    int mu = -1, mne = 0, marow = 0, mcell = -1, mcnt = 0;   // mne: exclusions of the row
+    int mu = -1, marow = 0, mcell = -1, mcnt = 0;
+    // The row's exclusions with itself: where they fill the index range
+    // [mlo, mlo + mspan] (chains with their bonded neighbours excluded; a row
+    // without exclusions, by itself), one unsigned compare tests them all and
+    // mne is 0; otherwise mne of them are staged in LDS (the row itself is
+    // tested by the range).
+    int mlo = -1, mspan = 0, mne = 0;
     if (lane < nh) {
         uint32_t ment;
         load_member(gpos, myrow, mx, my, mz, ment, mmol);
         mu = (int)(ment & kIdxMask);
         mt = (int)(ment >> kIdxBits);
         mcell = gbl(g.row_cell)[myrow];
-        if (excl_off) {
-            const int meb = excl_off[mu];
-            mne = excl_off[mu + 1] - meb;
-            for (int k = 0; k < mne; ++k) my_excl[lane * max_excl + k] = excl_idx[meb + k];
+        if constexpr (!MolOnly) {
+            mlo = mu;
+            if (excl_off) {
+                const int meb = excl_off[mu];
+                const int ne = excl_off[mu + 1] - meb;
+                if (ne > 0) {
+                    const int first = min(mu, excl_idx[meb]), last = max(mu, excl_idx[meb + ne - 1]);
+                    if (last - first == ne) {
+                        mlo = first;
+                        mspan = ne;
+                    } else {
+                        mne = ne;
+                        for (int k = 0; k < ne; ++k) my_excl[lane * max_excl + k] = excl_idx[meb + k];
+                    }
+                }
+            }
         }
         if (site) marow = user2arow[mu];
     }
@@ -782,14 +802,12 @@ __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool
     // unconditional (lanes past the stencil and empty slots read a valid entry
     // and drop it at use), so no branch makes the compiler wait for them early.
     int next_rank[St::kPerLane];
-    int next_lin = 0;      // the next home cell's linear index (its coordinates)
     auto ranks_of = [&](int h) {
         const int c = readlane_i(mcell, h);
-        next_lin = glor[c];
         if constexpr (S == 3) {
             next_rank[0] = gnbr[c * 27 + min(lane, 26)];
         } else {
-            const int lin = __builtin_amdgcn_readfirstlane(next_lin);
+            const int lin = __builtin_amdgcn_readfirstlane(glor[c]);
             const int cz = lin % n2, cy = (lin / n2) % n1, cx = lin / (n1 * n2);
 #pragma unroll
             for (int u = 0; u < St::kPerLane; ++u)
@@ -833,20 +851,13 @@ __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool
             s0[u] = ok ? next_lo[u] : 0;
             cnt[u] = ok ? next_hi[u] - next_lo[u] : 0;
         }
-        // this cell's linear index, read one cell ahead with its stencil ranks
-        const int lin_c = __builtin_amdgcn_readfirstlane(next_lin);
         if (h1 < nh) ranks_of(h1); else no_ranks();
-        // home cell coordinates: the periodic shift of every stencil slot
-        int cx = 0, cy = 0, cz = 0;
-        if (known_shift) {
-            cz = lin_c % n2;
-            cy = (lin_c / n2) % n1;
-            cx = lin_c / (n1 * n2);
-        }
+        // the cell's reference point and its rows relative to it (rows of one
+        // cell: no image shift between them)
+        const double rx = readlane_d(mx, h0), ry = readlane_d(my, h0), rz = readlane_d(mz, h0);
+        const float ax = (float)(mx - rx), ay = (float)(my - ry), az = (float)(mz - rz);
         // first candidate of every slot: a wave scan of the counts in slot
-        // order (slot lane, then slot lane + 64); with known shifts, each
-        // slot's periodic image shift (-L, 0 or +L per axis) is tabulated
-        // once here instead of per candidate
+        // order (slot lane, then slot lane + 64)
         int ncand = 0;
         int first[St::kPerLane];
 #pragma unroll
@@ -858,17 +869,8 @@ __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool
                 // member index of candidate q of this slot: slot_base + q
                 slot_base[slot] = s0[u] - first[u];
             }
-            if (known_shift && slot < St::kSlots) {
-                const int ox = St::off(slot, 0), oy = St::off(slot, 1), oz = St::off(slot, 2);
-                slot_shift[slot] = cx + ox < 0 ? -Lx : (cx + ox >= n0 ? Lx : 0.0);
-                slot_shift[St::kTab + slot] = cy + oy < 0 ? -Ly : (cy + oy >= n1 ? Ly : 0.0);
-                slot_shift[2 * St::kTab + slot] = cz + oz < 0 ? -Lz : (cz + oz >= n2 ? Lz : 0.0);
-            }
-            ncand += __builtin_amdgcn_readfirstlane(__shfl(pre, kWave - 1));
+            ncand += __builtin_amdgcn_readlane(pre, kWave - 1);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         int carry = -1;      // the slot of candidate cb - 1
         for (int cb = 0; cb < ncand; cb += kWave * K) {
             // The slot of each of the round's 64 K candidates (cb + p for p =
@@ -902,95 +904,112 @@ __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            double px[K], py[K], pz[K];
+            double qx[K], qy[K], qz[K];
+            int pi[K];          // member index of the candidate, -1: none
             uint32_t pe[K];     // the candidate's list entry
             int pm[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const int q = cb + lane + kWave * k;
-                px[k] = py[k] = pz[k] = 0.0;
+                qx[k] = qy[k] = qz[k] = 0.0;
                 pe[k] = 0;
                 pm[k] = 0;
-                if (q < ncand)
-                    load_member(gpos, slot_base[max(cslot[k], 0)] + q, px[k], py[k], pz[k],
-                                pe[k], pm[k]);
+                pi[k] = -1;
+                if (q < ncand) {
+                    pi[k] = slot_base[max(cslot[k], 0)] + q;
+                    load_member(gpos, pi[k], qx[k], qy[k], qz[k], pe[k], pm[k]);
+                }
             }
             // the next cell's member ranges (its stencil ranks were read at
             // this cell's start), issued after this cell's first candidate
             // reads and once per cell, outside the rows' loop
             if (cb == 0) range_of();
-            // periodic image shift of the candidate's slot, taken once per
-            // candidate for all the rows
-            double sx[K], sy[K], sz[K];
+            // the candidates relative to the reference point, nearest image
+            // (an empty slot lies at infinity: no test passes it)
+            float px[K], py[K], pz[K];
             int pu[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const bool ok = cb + lane + kWave * k < ncand;
-                const int slot = max(cslot[k], 0);
-                pu[k] = ok ? (int)(pe[k] & kIdxMask) : -1;
-                sx[k] = sy[k] = sz[k] = 0.0;
-                if (known_shift && ok) {
-                    sx[k] = slot_shift[slot];
-                    sy[k] = slot_shift[St::kTab + slot];
-                    sz[k] = slot_shift[2 * St::kTab + slot];
-                }
+                const double dx = qx[k] - rx, dy = qy[k] - ry, dz = qz[k] - rz;
+                px[k] = pi[k] >= 0 ? (float)(dx - Lx * rint(dx * iLx)) : __builtin_inff();
+                py[k] = (float)(dy - Ly * rint(dy * iLy));
+                pz[k] = (float)(dz - Lz * rint(dz * iLz));
+                pu[k] = (int)(pe[k] & kIdxMask);
             }
-            // The conditions of a (row, candidate) pair other than the
-            // distance are wave lane masks, one per k, combined with scalar
-            // ANDs: a lane's own work per row is its compares and its
-            // distance test.  `live` marks the slots holding a candidate.
-            uint64_t live[K];
-#pragma unroll
-            for (int k = 0; k < K; ++k) live[k] = __ballot(pu[k] >= 0);
-            // The rows' loop, instantiated for known image shifts and for
-            // the minimum image by comparison, each with and without the
-            // same-molecule exclusion, so each choice is one scalar branch
-            // per round and not a select or a branch per test.  Every cell
-            // has at least one home row (h1 > h0): a loop that always runs,
-            // so no path skips it with candidate reads pending.
-            auto row_loop = [&](auto known, auto own_mol) {
-            constexpr bool kKnown = decltype(known)::value;
-            constexpr bool kSameMol = decltype(own_mol)::value;
+            // The conditions of a (row, candidate) pair are wave lane masks,
+            // one per k, combined with scalar ANDs.  The rows' loop is
+            // instantiated for differences that are the nearest image already
+            // and for those that are not, so the choice is one scalar branch
+            // per round and not a select per test.  Every cell has at least
+            // one home row (h1 > h0): a loop that always runs, so no path
+            // skips it with candidate reads pending.
+            auto row_loop = [&](auto near) {
+            constexpr bool kNear = decltype(near)::value;
+            const float fLx = (float)Lx, fLy = (float)Ly, fLz = (float)Lz;
             int h = __builtin_amdgcn_readfirstlane(h0);
             do {
-                const double xi = readlane_d(mx, h), yi = readlane_d(my, h), zi = readlane_d(mz, h);
-                const int ui = readlane_i(mu, h);
-                const int moli = readlane_i(mmol, h);
-                const int ne = readlane_i(mne, h);
-                const int* hex = my_excl + h * max_excl;
+                const float xi = readlane_f(ax, h), yi = readlane_f(ay, h), zi = readlane_f(az, h);
                 int hc = readlane_i(mcnt, h);
                 RELRES_GLOBAL int* out =
                     glist + (size_t)__builtin_amdgcn_readfirstlane(r0 + h) * cap;
-                uint64_t keep[K];
+                uint64_t drop[K];
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    // the row's own atom shares its molecule: with the
-                    // same-molecule exclusion, one test drops both
-                    if constexpr (kSameMol) keep[k] = live[k] & ~__ballot(pm[k] == moli);
-                    else keep[k] = live[k] & __ballot(pu[k] != ui);
+                for (int k = 0; k < K; ++k) drop[k] = 0ull;
+                // the row's own atom shares its molecule: with the
+                // same-molecule exclusion, one test drops both
+                if (same_mol) {
+                    const int moli = readlane_i(mmol, h);
+#pragma unroll
+                    for (int k = 0; k < K; ++k) drop[k] = __ballot(pm[k] == moli);
                 }
-                // the row's exclusions: each read once for all K candidates,
-                // several reads in flight before the first compare
-#pragma unroll 4
-                for (int e = 0; e < ne; ++e) {
-                    const int x = hex[e];
+                if constexpr (!MolOnly) {
+                    const int lo = readlane_i(mlo, h), span = readlane_i(mspan, h);
+                    const int ne = readlane_i(mne, h);
 #pragma unroll
-                    for (int k = 0; k < K; ++k) keep[k] &= __ballot(pu[k] != x);
+                    for (int k = 0; k < K; ++k)
+                        drop[k] |= __ballot((unsigned)(pu[k] - lo) <= (unsigned)span);
+                    // scattered exclusions: each read once for all K
+                    // candidates, four reads in flight (past the end, the
+                    // last one again)
+                    const int* hex = my_excl + h * max_excl;
+                    for (int e = 0; e < ne; e += 4) {
+                        int x[4];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) x[v] = hex[min(e + v, ne - 1)];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+#pragma unroll
+                            for (int k = 0; k < K; ++k) drop[k] |= __ballot(pu[k] == x[v]);
+                    }
                 }
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     if (cb + kWave * k >= ncand) break;
-                    // the distance test for every lane (no divergent branch
-                    // around it), then the other conditions
-                    bool in;
-                    if constexpr (kKnown)
-                        in = member_shifted(xi, yi, zi, px[k], py[k], pz[k], sx[k], sy[k], sz[k],
-                                            rl2);
-                    else
-                        in = member(make_double4(xi, yi, zi, 0.0),
-                                    make_double4(px[k], py[k], pz[k], 0.0), Lx, Ly, Lz, hx, hy,
-                                    hz, rl2);
-                    const uint64_t mask = keep[k] & __ballot(in);
+                    float dx = px[k] - xi, dy = py[k] - yi, dz = pz[k] - zi;
+                    if constexpr (!kNear) {
+                        dx = fminf(fabsf(dx), fLx - fabsf(dx));
+                        dy = fminf(fabsf(dy), fLy - fabsf(dy));
+                        dz = fminf(fabsf(dz), fLz - fabsf(dz));
+                    }
+                    const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+                    uint64_t mask = __ballot(!(r2 > fhi)) & ~drop[k];
+                    const uint64_t open = mask & ~__ballot(r2 < flo);
+                    if (__builtin_expect(open != 0ull, 0)) {
+                        // too close to the list radius for the filter: the
+                        // FP64 recipe on the members' own positions
+                        bool in = false;
+                        if (__builtin_amdgcn_inverse_ballot_w64(open) && pi[k] >= 0) {
+                            double x, y, z;
+                            uint32_t e;
+                            int m;
+                            load_member(gpos, pi[k], x, y, z, e, m);
+                            in = member(make_double4(readlane_d(mx, h), readlane_d(my, h),
+                                                     readlane_d(mz, h), 0.0),
+                                        make_double4(x, y, z, 0.0), Lx, Ly, Lz, 0.5 * Lx, 0.5 * Ly,
+                                        0.5 * Lz, G.rl2);
+                        }
+                        mask = (mask & ~open) | __ballot(in);
+                    }
                     if (__builtin_amdgcn_inverse_ballot_w64(mask)) {
                         // 32-bit slot index: the store takes the row's scalar
                         // base and one lane offset
@@ -1002,13 +1021,8 @@ __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool
                 if (lane == h) mcnt = hc;
             } while (++h < h1);
             };
-            if (known_shift) {
-                if (same_mol) row_loop(BoolC<true>(), BoolC<true>());
-                else row_loop(BoolC<true>(), BoolC<false>());
-            } else {
-                if (same_mol) row_loop(BoolC<false>(), BoolC<true>());
-                else row_loop(BoolC<false>(), BoolC<false>());
-            }
+            if (direct) row_loop(BoolC<true>());
+            else row_loop(BoolC<false>());
         }
         if (ncand == 0) range_of();
         // the slot table is rewritten for the next cell
@@ -1029,10 +1043,13 @@ __device__ __forceinline__ void list_wave(const GridDev& g, int wv, int lw, bool
     if (lane < nh && mcnt > cap) atomicMax(&st->max_row[site ? 1 : 0], mcnt);
 }
 
-// One launch for both grids: waves [0, waves_a) build the atom list, the
-// rest the site list; SA and SS are the stencil widths of the two grids.
-template <int K, int SA, int SS>
-__global__ __launch_bounds__(256) void k_lists_wave(const GridDev* __restrict__ grids,
+// One launch for both grids; SA and SS are the stencil widths of the two
+// grids.  The waves of the site list come first: their stencils hold two to
+// three times the candidates of an atom wave's, and started last they ran on
+// alone at the end of the launch (98304-atom copolymer: build 76 against 71
+// us; 48000-atom hexane 69 against 61; 256 replicas 454 against 442).
+template <int K, int SA, int SS, bool MolOnly>
+__global__ __launch_bounds__(256, K == 2 ? (MolOnly ? 8 : 7) : 1) void k_lists_wave(const GridDev* __restrict__ grids,
                                                     int waves_a, int waves_total, int max_excl,
                                                     TopoDev topo,
                                                     const int* __restrict__ user2arow,
@@ -1041,7 +1058,6 @@ __global__ __launch_bounds__(256) void k_lists_wave(const GridDev* __restrict__ 
                                                     Status* __restrict__ st)
 {
     __shared__ int slot_base[4][Stencil<(SA > SS ? SA : SS)>::kTab];
-    __shared__ double slot_shift[4][3 * Stencil<(SA > SS ? SA : SS)>::kTab];
     __shared__ __align__(16) int slot_win[4][kWave * K];
     extern __shared__ int excl_lds[];
     // wave-uniform by construction; readfirstlane lets the compiler keep it
@@ -1049,16 +1065,15 @@ __global__ __launch_bounds__(256) void k_lists_wave(const GridDev* __restrict__ 
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int gw = blockIdx.x * 4 + wv;
     if (gw < waves_total) {                   // whole wave; no block barriers below
-        const bool site = gw >= waves_a;
-        const int lw = site ? gw - waves_a : gw;
+        const int waves_s = waves_total - waves_a;
+        const bool site = gw < waves_s;
+        const int lw = site ? gw : gw - waves_s;
         if (site)
-            list_wave<K, SS>(grids[1], wv, lw, true, max_excl, topo, user2arow, a_rec, s_rec, st,
-                             slot_base[wv], slot_shift[wv], slot_win[wv],
-                             excl_lds);
+            list_wave<K, SS, MolOnly>(grids[1], wv, lw, true, max_excl, topo, user2arow, a_rec,
+                                      s_rec, st, slot_base[wv], slot_win[wv], excl_lds);
         else
-            list_wave<K, SA>(grids[0], wv, lw, false, max_excl, topo, user2arow, a_rec, s_rec,
-                             st, slot_base[wv], slot_shift[wv], slot_win[wv],
-                             excl_lds);
+            list_wave<K, SA, MolOnly>(grids[0], wv, lw, false, max_excl, topo, user2arow, a_rec,
+                                      s_rec, st, slot_base[wv], slot_win[wv], excl_lds);
     }
     clear_bucket_counts(grids);   // last: the stores leave the start of the kernel alone
 }
@@ -2041,7 +2056,7 @@ hipError_t launch_place(GridDev* grids_dev, int ncell_a, int ncell_s, long long 
     return hipGetLastError();
 }
 
-int list_candidates(int total_waves, int cand)
+int list_candidates(int total_waves, int cand, double stencil_members)
 {
     if (cand == 2 || cand == 4) return cand;
     // RELRES_LIST_CANDIDATES=2|4 overrides the automatic choice (tuning runs)
@@ -2049,24 +2064,39 @@ int list_candidates(int total_waves, int cand)
         if (e[0] == '2' && e[1] == 0) return 2;
         if (e[0] == '4' && e[1] == 0) return 4;
     }
-    // all waves resident at once (about 3 per SIMD): more candidates per lane
-    return total_waves <= kResidentListWaves ? 4 : 2;
+    // 4 per lane needs the registers of 5 waves per SIMD, 2 those of 7 or 8:
+    // worth it in a launch of at most 4 waves per SIMD (24000-atom hexane,
+    // 4000 waves: build 34.4 against 38.5 us; 48000-atom hexane, 8000 waves:
+    // 56.7 against 53.4 us), or where a stencil takes many rounds of 128
+    // candidates (80000 atoms at 14 A, 1700 candidates: 117 against 127 us;
+    // the hexane's site stencils, 750 candidates, do not).
+    return total_waves <= 256 * 4 * 4 || stencil_members > kCrowdedStencil ? 4 : 2;
 }
 
 hipError_t launch_lists(GridDev* grids_dev, int ncell_a, int ncell_s, int waves_a, int waves_s,
                         TopoDev topo, const int* user2arow, int4* a_rec, int4* s_rec, Status* st,
-                        bool per_wave, int cand, int stencil_a, int stencil_s, hipStream_t s)
+                        bool per_wave, int cand, double stencil_members, int stencil_a,
+                        int stencil_s, hipStream_t s)
 {
     if (per_wave || stencil_a != 3 || stencil_s != 3) {
         const int total = waves_a + waves_s;
         if (total == 0) return hipSuccess;
         const int mx = topo.excl_off ? topo.max_excl : 0;
         const size_t dyn = sizeof(int) * 4 * kRowsPerWave * (size_t)mx;
-        const bool k4 = list_candidates(total, cand) == 4;
+        const bool k4 = list_candidates(total, cand, stencil_members) == 4;
         const dim3 grid((total + 3) / 4), block(256);
+        const bool mol_only = topo.same_mol && !topo.excl_off;
 #define RELRES_LISTS(K, SA, SS)                                                                   \
-        hipLaunchKernelGGL((k_lists_wave<K, SA, SS>), grid, block, dyn, s, grids_dev, waves_a, \
-                           total, mx, topo, user2arow, a_rec, s_rec, st)
+        do {                                                                                      \
+            if (mol_only)                                                                         \
+                hipLaunchKernelGGL((k_lists_wave<K, SA, SS, true>), grid, block, dyn, s,          \
+                                   grids_dev, waves_a, total, mx, topo, user2arow, a_rec, s_rec,  \
+                                   st);                                                           \
+            else                                                                                  \
+                hipLaunchKernelGGL((k_lists_wave<K, SA, SS, false>), grid, block, dyn, s,         \
+                                   grids_dev, waves_a, total, mx, topo, user2arow, a_rec, s_rec,  \
+                                   st);                                                           \
+        } while (0)
         const int sel = (k4 ? 4 : 0) | (stencil_a == 5 ? 2 : 0) | (stencil_s == 5 ? 1 : 0);
         switch (sel) {
         case 0: RELRES_LISTS(2, 3, 3); break;
