@@ -358,9 +358,10 @@ struct relres_ctx {
     // bonded terms and scaled 1-4 pairs (relres_set_bonded)
     bool has_bonded = false;
     double scale14 = 0.0;
-    DBuf d_items, d_bond_par, d_angle_par, d_dih_par, d_bond_part, d_bond_sum;
-    int bond_slots = 1;               // bonded items per atom (padded)
-    int bond_lg = 0;                  // lanes per atom of the bonded kernel = 2^bond_lg
+    DBuf d_bond_blocks, d_bond_passes, d_bond_terms, d_term_par, d_atom_slot, d_bond_part,
+        d_bond_sum;
+    int bond_nblocks = 0;             // blocks of the bonded kernel
+    int bond_max_atoms = 0, bond_max_slots = 0;
     // dynamics (relres_md_setup / relres_md_run)
     bool md_ready = false;
     double md_ftm2v = 0.0;
@@ -2118,64 +2119,144 @@ int relres_set_bonded(relres_ctx* c, int nbonds, const int* bonds, const double*
             pairs14[2 * t] == pairs14[2 * t + 1])
             return fail(RELRES_ERR_TOPOLOGY, "bad 1-4 pair %d", t);
 
-    // per atom: the terms it belongs to (bonds, angles, dihedrals, in order),
-    // then its 1-4 partners (ascending)
-    std::vector<std::vector<BondItem>> per(n);
-    auto add = [&](int atom, int kind, int slot, int t, const int* q) {
-        BondItem it{};
-        it.kind = kind;
-        it.slot = slot;
-        it.i = q[0];
-        it.j = q[1];
-        it.k = kind >= 1 ? q[2] : 0;
-        it.l = kind == 2 ? q[3] : 0;
-        it.par = t;
-        per[atom].push_back(it);
-    };
-    for (int t = 0; t < nbonds; ++t)
-        for (int u = 0; u < 2; ++u) add(bonds[2 * t + u], 0, u, t, bonds + 2 * t);
-    for (int t = 0; t < nangles; ++t)
-        for (int u = 0; u < 3; ++u) add(angles[3 * t + u], 1, u, t, angles + 3 * t);
-    for (int t = 0; t < ndihedrals; ++t)
-        for (int u = 0; u < 4; ++u) add(dihedrals[4 * t + u], 2, u, t, dihedrals + 4 * t);
-    std::vector<std::vector<int>> part(n);
-    for (int t = 0; t < npairs14; ++t) {
-        part[pairs14[2 * t]].push_back(pairs14[2 * t + 1]);
-        part[pairs14[2 * t + 1]].push_back(pairs14[2 * t]);
+    // the four kinds of terms: their number, atoms per term and atoms
+    static const int kAtoms[4] = {2, 3, 4, 2};
+    const int count[4] = {nbonds, nangles, ndihedrals, npairs14};
+    const int* arrays[4] = {bonds, angles, dihedrals, pairs14};
+    std::vector<int> items(n, 0);     // terms of every atom
+    std::vector<int> reach(n);        // largest atom of a term with this atom
+    for (int a = 0; a < n; ++a) reach[a] = a;
+    for (int kind = 0; kind < 4; ++kind)
+        for (int t = 0; t < count[kind]; ++t) {
+            const int* q = arrays[kind] + (size_t)kAtoms[kind] * t;
+            const int hi = *std::max_element(q, q + kAtoms[kind]);
+            for (int u = 0; u < kAtoms[kind]; ++u) {
+                items[q[u]]++;
+                reach[q[u]] = std::max(reach[q[u]], hi);
+            }
+        }
+    for (int a = 0; a < n; ++a)
+        if (items[a] > 4096)
+            return fail(RELRES_ERR_TOPOLOGY, "an atom has %d bonded items (max 4096)", items[a]);
+    // Blocks of consecutive atoms, ended where no term crosses if such a
+    // place is near.  At least 16 atoms (about a wave of each term kind), at
+    // most 96 (five waves of hexane terms, two rounds of the block's four
+    // waves), and 256 blocks where the system allows it.
+    std::vector<BondBlock> blocks;
+    std::vector<int> block_of(n);
+    const int target = std::max(16, std::min(96, n / 256));
+    for (int a0 = 0; a0 < n;) {
+        const int least = std::min(n - a0, target), most = std::min(n - a0, std::min(kBondAtoms, 2 * target));
+        int take = least, far = -1;
+        for (int k = 0; k < most; ++k) {
+            far = std::max(far, reach[a0 + k]);
+            if (k + 1 >= least && far <= a0 + k) {
+                take = k + 1;
+                break;
+            }
+        }
+        for (int k = 0; k < take; ++k) block_of[a0 + k] = (int)blocks.size();
+        blocks.push_back({a0, take, {0, 0, 0}, 0, 0, 0});
+        a0 += take;
     }
-    const int nt = c->ntypes;
-    for (int a = 0; a < n; ++a) {
-        std::sort(part[a].begin(), part[a].end());
-        for (int j : part[a]) {
-            BondItem it{};
-            it.kind = 3;
-            it.i = a;
-            it.j = j;
-            it.par = c->h_types[a] * nt + c->h_types[j];
-            per[a].push_back(it);
+    // the terms of every block, kind by kind (a term belongs to the block of
+    // each of its atoms)
+    const int nblk = (int)blocks.size();
+    std::vector<int> first(nblk + 1, 0);
+    std::vector<std::pair<int, int>> in_block;    // (kind, term)
+    for (int fill = 0; fill < 2; ++fill) {
+        for (int kind = 0; kind < 4; ++kind)
+            for (int t = 0; t < count[kind]; ++t) {
+                const int* q = arrays[kind] + (size_t)kAtoms[kind] * t;
+                for (int u = 0; u < kAtoms[kind]; ++u) {
+                    const int blk = block_of[q[u]];
+                    bool seen = false;
+                    for (int v = 0; v < u; ++v) seen = seen || block_of[q[v]] == blk;
+                    if (seen) continue;
+                    if (fill) in_block[first[blk]++] = {kind, t};
+                    else first[blk + 1]++;
+                }
+            }
+        if (!fill) {
+            for (int k = 0; k < nblk; ++k) first[k + 1] += first[k];
+            in_block.resize(first[nblk]);
         }
     }
-    // items per atom: a power of two holding every atom's list; lanes per
-    // atom: as many, at most 32 (more items are taken in turns)
-    size_t most = 1;
-    for (int a = 0; a < n; ++a) most = std::max(most, per[a].size());
-    if (most > 4096) return fail(RELRES_ERR_TOPOLOGY, "an atom has %zu bonded items (max 4096)", most);
-    int slots = 1;
-    while ((size_t)slots < most) slots <<= 1;
-    int lg = 0;
-    while ((1 << lg) < slots && lg < 5) ++lg;
-    BondItem none{};
-    none.kind = -1;
-    std::vector<BondItem> items((size_t)n * slots, none);
-    for (int a = 0; a < n; ++a)
-        std::copy(per[a].begin(), per[a].end(), items.begin() + (size_t)a * slots);
-    std::vector<double2> hbp(nbonds);
-    for (int t = 0; t < nbonds; ++t) hbp[t] = make_double2(bond_k[t], bond_r0[t]);
-    std::vector<double2> hap(nangles);
-    for (int t = 0; t < nangles; ++t) hap[t] = make_double2(angle_k[t], angle_t0[t]);
-    std::vector<double4> hdp(ndihedrals);
-    for (int t = 0; t < ndihedrals; ++t)
-        hdp[t] = make_double4(dih_k[t], (double)dih_n[t], std::cos(dih_d[t]), std::sin(dih_d[t]));
+    for (int k = nblk; k > 0; --k) first[k] = first[k - 1];   // the fill advanced them
+    first[0] = 0;
+    std::vector<BondPass> passes;
+    std::vector<BondTerm> terms;
+    std::vector<double4> term_par;
+    std::vector<unsigned short> atom_slot;
+    int max_atoms = 0, max_slots = 0;
+    const int nt = c->ntypes;
+    std::vector<int> slots;
+    for (int blk = 0; blk < nblk; ++blk) {
+        BondBlock& bb = blocks[blk];
+        max_atoms = std::max(max_atoms, bb.natoms);
+        bb.more0 = (int)passes.size();
+        const auto owned = [&](int atom) { return block_of[atom] == blk; };
+        for (int e0 = first[blk]; e0 < first[blk + 1];) {
+            // as many terms as have slots
+            int e1 = e0, used = 0;
+            slots.assign(bb.natoms + 1, 0);
+            for (; e1 < first[blk + 1]; ++e1) {
+                const int kind = in_block[e1].first;
+                const int* q = arrays[kind] + (size_t)kAtoms[kind] * in_block[e1].second;
+                int need = 0;
+                for (int u = 0; u < kAtoms[kind]; ++u) need += owned(q[u]);
+                if (used + need > kBondSlots) break;
+                used += need;
+                for (int u = 0; u < kAtoms[kind]; ++u)
+                    if (owned(q[u])) slots[q[u] - bb.atom0 + 1]++;
+            }
+            max_slots = std::max(max_slots, used);
+            for (int k = 0; k < bb.natoms; ++k) slots[k + 1] += slots[k];
+            BondPass ps{(int)terms.size(), 0, (int)atom_slot.size()};
+            atom_slot.insert(atom_slot.end(), slots.begin(), slots.end());
+            // runs of 64 terms of one kind, the longest kinds first, and every
+            // second round of four runs reversed, so the waves' loads even out
+            std::vector<std::pair<int, int>> runs;            // (kind, first entry)
+            for (int kind : {2, 1, 3, 0})
+                for (int e = e0, k = 0; e < e1; ++e)
+                    if (in_block[e].first == kind && k++ % 64 == 0) runs.push_back({kind, e});
+            const int waves = 4;
+            for (size_t r = waves; r < runs.size(); r += 2 * waves)
+                std::reverse(runs.begin() + r, runs.begin() + std::min(r + waves, runs.size()));
+            for (const auto& run : runs) {
+                int e = run.second;
+                for (int k = 0; k < 64; ++k, ++e) {
+                    BondTerm it{};
+                    it.kind = -1;
+                    double4 par = make_double4(0.0, 0.0, 0.0, 0.0);
+                    if (e < e1 && in_block[e].first == run.first) {
+                        const int kind = run.first, t = in_block[e].second;
+                        const int* q = arrays[kind] + (size_t)kAtoms[kind] * t;
+                        it.kind = (short)kind;
+                        for (int u = 0; u < 4; ++u) {
+                            const int atom = q[u < kAtoms[kind] ? u : 0];
+                            it.atom[u] = owned(atom) ? atom - bb.atom0 : ~atom;
+                            it.slot[u] = kNoSlot;
+                            if (u < kAtoms[kind] && owned(atom))
+                                it.slot[u] = (unsigned short)slots[atom - bb.atom0]++;
+                        }
+                        if (kind == 0) par = make_double4(bond_k[t], bond_r0[t], 0.0, 0.0);
+                        else if (kind == 1) par = make_double4(angle_k[t], angle_t0[t], 0.0, 0.0);
+                        else if (kind == 2) par = make_double4(dih_k[t], (double)dih_n[t],
+                                                               std::cos(dih_d[t]), std::sin(dih_d[t]));
+                        else it.pair = (short)(c->h_types[q[0]] * nt + c->h_types[q[1]]);
+                    }
+                    terms.push_back(it);
+                    term_par.push_back(par);
+                }
+            }
+            ps.nterms = (int)terms.size() - ps.term0;
+            if (e0 == first[blk]) bb.pass = ps;
+            else passes.push_back(ps);
+            e0 = e1;
+        }
+        bb.nmore = (int)passes.size() - bb.more0;
+    }
     // the buffers may be in use by work still queued on any stream
     HIP_TRY(hipDeviceSynchronize());
     long long* gen = &c->alloc_generation;
@@ -2184,17 +2265,18 @@ int relres_set_bonded(relres_ctx* c, int nbonds, const int* bonds, const double*
         if (bytes) HIP_TRY(hipMemcpy(b.p, src, bytes, hipMemcpyHostToDevice));
         return RELRES_OK;
     };
-    TRY(up(c->d_items, items.data(), sizeof(BondItem) * items.size()));
-    TRY(up(c->d_bond_par, hbp.data(), sizeof(double2) * hbp.size()));
-    TRY(up(c->d_angle_par, hap.data(), sizeof(double2) * hap.size()));
-    TRY(up(c->d_dih_par, hdp.data(), sizeof(double4) * hdp.size()));
-    const int nblk = bonded_blocks(n, lg);
+    TRY(up(c->d_bond_blocks, blocks.data(), sizeof(BondBlock) * blocks.size()));
+    TRY(up(c->d_bond_passes, passes.data(), sizeof(BondPass) * passes.size()));
+    TRY(up(c->d_bond_terms, terms.data(), sizeof(BondTerm) * terms.size()));
+    TRY(up(c->d_term_par, term_par.data(), sizeof(double4) * term_par.size()));
+    TRY(up(c->d_atom_slot, atom_slot.data(), sizeof(unsigned short) * atom_slot.size()));
     TRY(ensure(c->d_bond_part, sizeof(double) * 10 * (size_t)std::max(1, nblk), gen));
     TRY(ensure(c->d_bond_sum, sizeof(double) * 16, gen));
     // kinetic partials of the kick (one per bonded block) and of k_md_kinetic
     TRY(ensure(c->d_md_part, sizeof(double) * (size_t)std::max({1, nblk, md_blocks(n)}), gen));
-    c->bond_lg = lg;
-    c->bond_slots = slots;
+    c->bond_nblocks = nblk;
+    c->bond_max_atoms = max_atoms;
+    c->bond_max_slots = max_slots;
     c->scale14 = scale14;
     c->has_bonded = true;
     return RELRES_OK;
@@ -2209,20 +2291,22 @@ int enqueue_bonded(relres_ctx* c, const double* pos, void* forces, bool sums, co
     b.pos = pos;
     for (int k = 0; k < 3; ++k) b.box[k] = c->box[k];
     b.n = c->n;
-    b.items = c->d_items.as<BondItem>();
-    b.slots = c->bond_slots;
-    b.bond_par = c->d_bond_par.as<double2>();
-    b.angle_par = c->d_angle_par.as<double2>();
-    b.dih_par = c->d_dih_par.as<double4>();
+    b.nblocks = c->bond_nblocks;
+    b.max_atoms = c->bond_max_atoms;
+    b.max_slots = c->bond_max_slots;
+    b.blocks = c->d_bond_blocks.as<BondBlock>();
+    b.passes = c->d_bond_passes.as<BondPass>();
+    b.terms = c->d_bond_terms.as<BondTerm>();
+    b.term_par = c->d_term_par.as<double4>();
+    b.atom_slot = c->d_atom_slot.as<unsigned short>();
     b.scale14 = c->scale14;
     b.coef64 = c->d_coef64.as<PairCoef<double>>();
     b.pcut64 = c->d_pcut64.as<Cutoffs<double>>();
     b.forces = forces;
     b.partial = sums ? c->d_bond_part.as<double>() : nullptr;
-    b.log_lanes = c->bond_lg;
     HIP_TRY(launch_bonded(b, m, c->precision, s));
     if (sums)
-        HIP_TRY(launch_sum_partials(c->d_bond_part.as<double>(), bonded_blocks(c->n, c->bond_lg),
+        HIP_TRY(launch_sum_partials(c->d_bond_part.as<double>(), c->bond_nblocks,
                                     nullptr, 0, 10, c->d_bond_sum.as<double>(), s));
     return RELRES_OK;
 }
@@ -2267,7 +2351,7 @@ int relres_md_setup(relres_ctx* c, const double* masses, double dt, double kT, d
     TRY(ensure(c->d_md_F, (c->precision == 64 ? 8 : 4) * 3 * (size_t)n, gen));
     TRY(ensure(c->d_md_E, sizeof(double) * 3, gen));
     TRY(ensure(c->d_md_W, sizeof(double) * 6, gen));
-    TRY(ensure(c->d_md_part, sizeof(double) * (size_t)std::max(md_blocks(n), bonded_blocks(n, c->bond_lg)), gen));
+    TRY(ensure(c->d_md_part, sizeof(double) * (size_t)std::max(md_blocks(n), c->bond_nblocks), gen));
     TRY(ensure(c->d_md_stale, 64, gen));
     TRY(ensure(c->d_bond_sum, sizeof(double) * 16, gen));
     if (!c->h_stale && hipHostMalloc((void**)&c->h_stale, 64, hipHostMallocDefault) != hipSuccess)
@@ -2364,7 +2448,7 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
     MdState* stb = c->d_md_state.as<MdState>();             // two buffers
     m.st = stb + c->md_cur;
     const int nblk = md_blocks(c->n);                       // partials of k_md_kinetic
-    const int nblk_kick = bonded_blocks(c->n, c->bond_lg);  // partials of the kick
+    const int nblk_kick = c->bond_nblocks;  // partials of the kick
     const double* e_nb = c->d_md_E.as<double>();
     const double* w_nb = c->d_md_W.as<double>();
     const double* eb = c->d_bond_sum.as<double>();
@@ -2508,7 +2592,7 @@ void relres_destroy(relres_ctx* c)
     (void)hipDeviceSynchronize();
     for (DBuf* b : {&c->d_coef_grad, &c->d_bpartial, &c->d_sys, &c->d_boxes, &c->d_row_ew, &c->d_wave_ew,
                     &c->d_wave_sys}) release(*b);
-    for (DBuf* b : {&c->d_items, &c->d_bond_par, &c->d_angle_par, &c->d_dih_par,
+    for (DBuf* b : {&c->d_bond_blocks, &c->d_bond_passes, &c->d_bond_terms, &c->d_term_par, &c->d_atom_slot,
                     &c->d_bond_part, &c->d_bond_sum,
                     &c->d_mass, &c->d_md_state, &c->d_md_xref,
                     &c->d_md_F, &c->d_md_E, &c->d_md_W, &c->d_md_part, &c->d_md_stale})

@@ -253,42 +253,59 @@ hipError_t launch_zero_outputs(double* energy, double* virial, int nsys, hipStre
 hipError_t launch_reduce_sys_ew(const GridDev* grids_dev, int ngrids, const ForceArgs& a,
                                 double* energy, double* virial, hipStream_t s);
 
-// Bonded terms and scaled 1-4 pairs (relres_md.hip).  Per atom, the terms
-// it belongs to: term_ent packs kind (bits 30-31: 0 bond, 1 angle,
-// 2 dihedral), the atom's slot in the term (bits 28-29) and the term index.
-// One item of an atom's bonded work: a (term, slot) entry or a 1-4 partner.
-// Atoms of the term in the term's order (a bond uses i, j; an angle i, j =
-// vertex, k; a dihedral i, j, k, l); a 1-4 item has i = the atom, j = the
-// partner and par = the pair's type-pair index.  kind -1 marks padding.
-struct BondItem {
-    int kind;                         // 0 bond, 1 angle, 2 dihedral, 3 1-4 pair, -1 none
-    int slot;                         // the atom's place in the term
-    int i, j, k, l;
-    int par;                          // row of bond_par / angle_par / dih_par, or type pair
+// Bonded terms and scaled 1-4 pairs (relres_md.hip).  One term as a block of
+// the bonded kernel evaluates it: its atoms in the term's order (a bond uses
+// two, an angle three with the vertex second, a dihedral four, a 1-4 pair
+// two; unused ones repeat the first), each the atom's place in the block or ~
+// its index when another block owns it, and the LDS slot that takes the force
+// on each owned atom.
+constexpr int kNoSlot = 0xffff;
+struct BondTerm {
+    short kind;                       // 0 bond, 1 angle, 2 dihedral, 3 1-4 pair, -1 padding
+    short pair;                       // type pair of a 1-4 pair
+    int atom[4];
+    unsigned short slot[4];
     int pad;
 };
+// A block's atoms and passes.  A pass is as many of the block's terms as have
+// LDS slots: terms term0 .. term0 + nterms - 1 (a multiple of 64, each run of
+// 64 of one kind), and the first slot of every atom of the block, then the
+// end, at atom_slot[slot0 ..].  Passes past the first (atoms of thousands of
+// terms) are passes more0 .. more0 + nmore - 1.
+struct BondPass {
+    int term0, nterms;
+    int slot0;
+};
+struct BondBlock {
+    int atom0, natoms;
+    BondPass pass;
+    int more0, nmore;
+    int pad;
+};
+constexpr int kBondAtoms = 256;       // most atoms of a block (one thread each)
+constexpr int kBondSlots = 2048;      // most force slots of a pass (48 KB of LDS)
 struct BondedArgs {
     const double* pos;
     double box[3];
     int n;
-    const BondItem* items;            // n x slots, atom-major; padded with kind -1
-    int slots;                        // items per atom (a power of two)
-    const double2* bond_par;          // K, r0
-    const double2* angle_par;         // K, theta0
-    const double4* dih_par;           // K, n, cos d, sin d
+    int nblocks;
+    int max_atoms, max_slots;         // the largest of any block / pass (LDS layout)
+    const BondBlock* blocks;
+    const BondPass* passes;
+    const BondTerm* terms;
+    const double4* term_par;          // per term: K, r0 | K, theta0 | K, n, cos d, sin d
+    const unsigned short* atom_slot;
     double scale14;
     const PairCoef<double>* coef64;
     const Cutoffs<double>* pcut64;
     void* forces;                     // N x 3 of the force type; added to
     double* partial;                  // per block: 4 energies, 6 virial; or null
-    int log_lanes;                    // lanes per atom = 2^log_lanes (<= slots, <= 32)
 };
 struct MdArgs;
 // Bonded and 1-4 forces added to b.forces; with m, also the half kick of a
 // dynamics step and the kinetic partials (m->partial).
 hipError_t launch_bonded(const BondedArgs& b, const MdArgs* m, int force_prec, hipStream_t s);
 int md_blocks(int n);                 // blocks of the one-thread-per-atom kernels
-int bonded_blocks(int n, int log_lanes);   // blocks of the bonded kernel
 // out[k] = sum of p1[blk * K + k] over its blocks, then of p2, in block order
 hipError_t launch_sum_partials(const double* p1, int n1, const double* p2, int n2, int K,
                                double* out, hipStream_t s);

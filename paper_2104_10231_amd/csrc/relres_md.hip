@@ -2,11 +2,12 @@
 // pair potential (Sec. 3.2 of the paper): bonded terms, scaled 1-4 pairs and
 // a Nose-Hoover velocity-Verlet integrator.
 //
-// Bonded terms: a group of lanes per atom evaluates the atom's (term, slot)
-// entries and scaled 1-4 pairs side by side in FP64 and sums their forces
-// with lane moves in a fixed order; in a dynamics step the same kernel gives
-// the half kick.  A term's energy and virial are counted by its first slot.
-// No atomics, so results are deterministic.  Formulas
+// Bonded terms: a block owns a range of consecutive atoms and evaluates every
+// term that touches them once in FP64, waves of one term kind; each atom then
+// adds its terms' forces from LDS in a fixed order, and in a dynamics step the
+// same kernel gives the half kick.  A term's energy and virial are counted by
+// the block that owns its first atom (a 1-4 pair's by halves).  No atomics, so
+// results are deterministic.  Formulas
 // (forces are -dE/dx):
 //   bond      E = K (r - r0)^2, d = x_i - x_j: F_i = -2K (r - r0) d / r
 //   angle     E = K (theta - theta0)^2, a = x_i - x_j, b = x_k - x_j:
@@ -42,20 +43,6 @@ __device__ __forceinline__ void mi_diff(const double xa[3], const double xb[3],
         const double h = 0.5 * box[k];
         const double lo = v - box[k], hi = v + box[k];
         d[k] = v > h ? lo : (v < -h ? hi : v);
-    }
-}
-
-// The positions of an item's atoms i, j, k, l (unused ones, and the padding
-// items' atoms, read as atom 0 and ignored), all read before any is used.
-__device__ __forceinline__ void item_positions(const double* __restrict__ pos, int n,
-                                               const BondItem& it, double x[4][3])
-{
-    const int at[4] = {it.i, it.j, it.k, it.l};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int a = (unsigned)at[q] < (unsigned)n ? at[q] : 0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) x[q][c] = pos[3 * (size_t)a + c];
     }
 }
 
@@ -105,107 +92,109 @@ __device__ __forceinline__ double block_sum(const double* v, double (*red)[kMdBl
     return r;
 }
 
-// The force of one (term, slot) entry on its atom, added to fa; the term's
-// energy and virial go to acc (energies 0..2, virial 4..9) from its first
-// slot only.
-__device__ __forceinline__ void entry_force(const BondedArgs& b, const BondItem& it,
-                                            const double x[4][3], double fa[3], double acc[10])
-{
-    const int kind = it.kind, slot = it.slot, t = it.par;
-    double f[4][3];
-    if (kind == 0) {
-        const double2 par = b.bond_par[t];
-        double d[3];
-        mi_diff(x[0], x[1], b.box, d);
-        const double r = sqrt(dot3(d, d));
-        const double dr = r - par.y;
-        const double sc = -2.0 * par.x * dr / r;
-        for (int c = 0; c < 3; ++c) {
-            f[0][c] = sc * d[c];
-            f[1][c] = -f[0][c];
-        }
-        if (slot == 0) {
-            acc[0] += par.x * dr * dr;
-            add_virial(acc + 4, d, f[0]);
-        }
-    } else if (kind == 1) {
-        const double2 par = b.angle_par[t];
-        double u[3], v[3];
-        mi_diff(x[0], x[1], b.box, u);
-        mi_diff(x[2], x[1], b.box, v);
-        // reciprocals once: a divide is a long instruction sequence in FP64
-        const double ilu = 1.0 / sqrt(dot3(u, u)), ilv = 1.0 / sqrt(dot3(v, v));
-        double c = dot3(u, v) * ilu * ilv;
-        c = c > 1.0 ? 1.0 : (c < -1.0 ? -1.0 : c);
-        const double th = acos(c);
-        const double dth = th - par.y;
-        const double g = 2.0 * par.x * dth / sqrt((1.0 - c) * (1.0 + c));   // sin theta
-        for (int q = 0; q < 3; ++q) {
-            f[0][q] = g * (v[q] * ilv - c * u[q] * ilu) * ilu;
-            f[2][q] = g * (u[q] * ilu - c * v[q] * ilv) * ilv;
-            f[1][q] = -f[0][q] - f[2][q];
-        }
-        if (slot == 0) {
-            acc[1] += par.x * dth * dth;
-            add_virial(acc + 4, u, f[0]);
-            add_virial(acc + 4, v, f[2]);
-        }
-    } else {
-        const double4 par = b.dih_par[t];      // K, n, cos d, sin d
-        double b1[3], b2[3], b3[3], m[3], nn[3];
-        mi_diff(x[1], x[0], b.box, b1);
-        mi_diff(x[2], x[1], b.box, b2);
-        mi_diff(x[3], x[2], b.box, b3);
-        cross3(b1, b2, m);
-        cross3(b2, b3, nn);
-        const double lb2 = sqrt(dot3(b2, b2));
-        // phi = atan2(y, x) without the library calls: cos phi = x / r,
-        // sin phi = y / r (r = |m||n|), cos and sin of n phi by repeated
-        // angle addition, then of n phi - d with cos d, sin d from the host
-        const double x = dot3(m, nn), y = lb2 * dot3(b1, nn);
-        const double ir = 1.0 / sqrt(x * x + y * y);
-        const double cp = x * ir, sp = y * ir;
-        double cn = 1.0, sn = 0.0;
-        for (int k = 0; k < (int)par.y; ++k) {
-            const double c2 = cn * cp - sn * sp;
-            sn = sn * cp + cn * sp;
-            cn = c2;
-        }
-        const double cos_arg = cn * par.z + sn * par.w;
-        const double sin_arg = sn * par.z - cn * par.w;
-        const double dE = -par.x * par.y * sin_arg;
-        const double imm = lb2 / dot3(m, m), in2 = lb2 / dot3(nn, nn);
-        const double ib2 = 1.0 / (lb2 * lb2);
-        const double p = dot3(b1, b2) * ib2, q = dot3(b3, b2) * ib2;
-        for (int c = 0; c < 3; ++c) {
-            const double gi = -m[c] * imm, gl = nn[c] * in2;
-            f[0][c] = -dE * gi;
-            f[3][c] = -dE * gl;
-            f[1][c] = -dE * (-(1.0 + p) * gi + q * gl);
-            f[2][c] = -dE * (p * gi - (1.0 + q) * gl);
-        }
-        if (slot == 0) {
-            acc[2] += par.x * (1.0 + cos_arg);
-            const double li[3] = {-b1[0], -b1[1], -b1[2]};
-            const double ll[3] = {b2[0] + b3[0], b2[1] + b3[1], b2[2] + b3[2]};
-            add_virial(acc + 4, li, f[0]);
-            add_virial(acc + 4, b2, f[2]);
-            add_virial(acc + 4, ll, f[3]);
-        }
-    }
-    for (int c = 0; c < 3; ++c) fa[c] += f[slot][c];
-}
-
-// The scaled 1-4 pair (a, j) through Eq. 20 (FG and CG parts, the pair's own
-// distances), seen from atom a: its force on a added to fa, half its energy
-// to acc[3] and half its virial to acc[4..9] (the pair is met from both atoms).
-__device__ __forceinline__ void pair14_force(const BondedArgs& b, const BondItem& it,
-                                             const double x[4][3], double fa[3], double acc[10])
+// The forces of one term on its atoms at x, f[slot]; with `own` the term's
+// energy and virial are added to acc (energies 0..3, virial 4..9).
+__device__ __forceinline__ void bond_force(const BondedArgs& b, const double par[4],
+                                           const double x[4][3], bool own, double f[4][3],
+                                           double acc[10])
 {
     double d[3];
-    mi_diff(x[0], x[1], b.box, d);             // x_a - x_j
+    mi_diff(x[0], x[1], b.box, d);
+    const double r = sqrt(dot3(d, d));
+    const double dr = r - par[1];
+    const double sc = -2.0 * par[0] * dr / r;
+    for (int c = 0; c < 3; ++c) {
+        f[0][c] = sc * d[c];
+        f[1][c] = -f[0][c];
+    }
+    if (own) {
+        acc[0] += par[0] * dr * dr;
+        add_virial(acc + 4, d, f[0]);
+    }
+}
+
+__device__ __forceinline__ void angle_force(const BondedArgs& b, const double par[4],
+                                            const double x[4][3], bool own, double f[4][3],
+                                            double acc[10])
+{
+    double u[3], v[3];
+    mi_diff(x[0], x[1], b.box, u);
+    mi_diff(x[2], x[1], b.box, v);
+    // reciprocals once: a divide is a long instruction sequence in FP64
+    const double ilu = 1.0 / sqrt(dot3(u, u)), ilv = 1.0 / sqrt(dot3(v, v));
+    double c = dot3(u, v) * ilu * ilv;
+    c = c > 1.0 ? 1.0 : (c < -1.0 ? -1.0 : c);
+    const double th = acos(c);
+    const double dth = th - par[1];
+    const double g = 2.0 * par[0] * dth / sqrt((1.0 - c) * (1.0 + c));   // sin theta
+    for (int q = 0; q < 3; ++q) {
+        f[0][q] = g * (v[q] * ilv - c * u[q] * ilu) * ilu;
+        f[2][q] = g * (u[q] * ilu - c * v[q] * ilv) * ilv;
+        f[1][q] = -f[0][q] - f[2][q];
+    }
+    if (own) {
+        acc[1] += par[0] * dth * dth;
+        add_virial(acc + 4, u, f[0]);
+        add_virial(acc + 4, v, f[2]);
+    }
+}
+
+// par: K, n, cos d, sin d
+__device__ __forceinline__ void dihedral_force(const BondedArgs& b, const double par[4],
+                                               const double x[4][3], bool own, double f[4][3],
+                                               double acc[10])
+{
+    double b1[3], b2[3], b3[3], m[3], nn[3];
+    mi_diff(x[1], x[0], b.box, b1);
+    mi_diff(x[2], x[1], b.box, b2);
+    mi_diff(x[3], x[2], b.box, b3);
+    cross3(b1, b2, m);
+    cross3(b2, b3, nn);
+    const double lb2 = sqrt(dot3(b2, b2));
+    // phi = atan2(y, x) without the library calls: cos phi = x / r,
+    // sin phi = y / r (r = |m||n|), cos and sin of n phi by repeated
+    // angle addition, then of n phi - d with cos d, sin d from the host
+    const double cx = dot3(m, nn), y = lb2 * dot3(b1, nn);
+    const double ir = 1.0 / sqrt(cx * cx + y * y);
+    const double cp = cx * ir, sp = y * ir;
+    double cn = 1.0, sn = 0.0;
+    for (int k = 0; k < (int)par[1]; ++k) {
+        const double c2 = cn * cp - sn * sp;
+        sn = sn * cp + cn * sp;
+        cn = c2;
+    }
+    const double cos_arg = cn * par[2] + sn * par[3];
+    const double sin_arg = sn * par[2] - cn * par[3];
+    const double dE = -par[0] * par[1] * sin_arg;
+    const double imm = lb2 / dot3(m, m), in2 = lb2 / dot3(nn, nn);
+    const double ib2 = 1.0 / (lb2 * lb2);
+    const double p = dot3(b1, b2) * ib2, q = dot3(b3, b2) * ib2;
+    for (int c = 0; c < 3; ++c) {
+        const double gi = -m[c] * imm, gl = nn[c] * in2;
+        f[0][c] = -dE * gi;
+        f[3][c] = -dE * gl;
+        f[1][c] = -dE * (-(1.0 + p) * gi + q * gl);
+        f[2][c] = -dE * (p * gi - (1.0 + q) * gl);
+    }
+    if (own) {
+        acc[2] += par[0] * (1.0 + cos_arg);
+        const double li[3] = {-b1[0], -b1[1], -b1[2]};
+        const double ll[3] = {b2[0] + b3[0], b2[1] + b3[1], b2[2] + b3[2]};
+        add_virial(acc + 4, li, f[0]);
+        add_virial(acc + 4, b2, f[2]);
+        add_virial(acc + 4, ll, f[3]);
+    }
+}
+
+// The scaled 1-4 pair through Eq. 20 (FG and CG parts, the pair's own
+// distances), type-pair index pi; half of its energy and virial for each of
+// its atoms that the block owns (share = 0.5 or 1).
+__device__ __forceinline__ void pair14_force(const BondedArgs& b, int pi, const double x[4][3],
+                                             double share, double f[4][3], double acc[10])
+{
+    double d[3];
+    mi_diff(x[0], x[1], b.box, d);
     const double r2 = dot3(d, d);
-    const int pi = it.par;
     const Cutoffs<double>& cut = b.pcut64[pi];
     double fp = 0.0, en = 0.0;
     if (r2 < cut.rso2) {
@@ -220,84 +209,136 @@ __device__ __forceinline__ void pair14_force(const BondedArgs& b, const BondItem
         fp += f2;
         en += e2;
     }
-    const double s = b.scale14 * fp;           // F_a = s (x_a - x_j)
-    const double f[3] = {s * d[0], s * d[1], s * d[2]};
-    for (int c = 0; c < 3; ++c) fa[c] += f[c];
-    acc[3] += 0.5 * b.scale14 * en;
-    const double hd[3] = {0.5 * d[0], 0.5 * d[1], 0.5 * d[2]};
-    add_virial(acc + 4, hd, f);
+    const double s = b.scale14 * fp;           // F_0 = s (x_0 - x_1)
+    for (int c = 0; c < 3; ++c) {
+        f[0][c] = s * d[c];
+        f[1][c] = -f[0][c];
+    }
+    acc[3] += share * b.scale14 * en;
+    const double hd[3] = {share * d[0], share * d[1], share * d[2]};
+    add_virial(acc + 4, hd, f[0]);
 }
 
-// Bonded and 1-4 forces, one aligned group of 2^log_lanes lanes per atom:
-// the lanes take the atom's items (its term entries in order, then its 1-4
-// partners; one padded record each, so a lane needs no offset table) in
-// turn, and the group adds their forces with lane moves in a fixed order, so
-// an atom's items are evaluated side by side and no force passes through
-// memory.  The group's first lane adds the sum to `forces`
-// and, in a dynamics step (kick != 0), gives the half kick v += dt/2 F/m and
-// the kinetic term of the block partial.  With b.partial every block writes
-// its 10 sums (energies: bonds, angles, dihedrals, 1-4; virial).  No
-// atomics, so results are deterministic.
-template <typename TF>
+// Bonded and 1-4 forces, one block per range of consecutive atoms
+// (BondBlock).  The block's positions are staged in LDS; thread t evaluates
+// the block's terms t, t + 256, ..., which the host has grouped so that a wave
+// holds terms of one kind, and leaves each owned atom's force in that atom's
+// slots in LDS; then one thread per atom adds its slots in order.  Every term
+// is evaluated once per block that owns an atom of it, so once for molecules
+// that do not straddle blocks, by waves that take one branch: bound by the
+// dependent reads (term, then position) and one term's arithmetic, 1.2 MFLOP
+// of FP64 per 1000 hexane molecules.  (One lane per atom and term, the version
+// before, evaluated each term two to four times in waves of all four kinds:
+// 48000-atom hexane 29.8 us in the kernel trace, now 7.4; 6000 atoms 8.0, now
+// 4.7, the launch and three dependent memory round trips.)
+// The atom's thread adds the sum to `forces` and, in a dynamics step
+// (kick != 0), gives the half kick v += dt/2 F/m and the kinetic term of the
+// block partial.  With Sums every block writes its 10 sums to b.partial
+// (energies: bonds, angles, dihedrals, 1-4; virial).  No atomics, so results are
+// deterministic.
+template <typename TF, bool Sums>
 __global__ __launch_bounds__(kMdBlock) void k_bonded(BondedArgs b, MdArgs m, int kick)
 {
-    __shared__ double red[10][kMdBlock / 64];
-    const int lg = b.log_lanes;
-    const int G = 1 << lg;
-    const int gid = blockIdx.x * kMdBlock + (int)threadIdx.x;
-    const int a = gid >> lg;
-    const int sub = gid & (G - 1);
+    extern __shared__ double lds[];
+    __shared__ double red[Sums ? 10 : 1][kMdBlock / 64];
+    double* lpos = lds;                                  // [3][max_atoms]
+    double* lf = lds + 3 * b.max_atoms;                  // [3][max_slots]
+    const BondBlock bb = b.blocks[blockIdx.x];
+    const int tid = (int)threadIdx.x;
+    const int a = bb.atom0 + tid;
+    const bool live = tid < bb.natoms;                   // this thread's atom
     double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     double fa[3] = {0.0, 0.0, 0.0};
-    const bool live = a < b.n;
-    const bool lead = live && sub == 0;
-    // the leader's own data first: it does not depend on the items
+    // the first term and the atom's own data: none of these reads waits on another
+    BondPass ps = bb.pass;
+    BondTerm it;
+    it.kind = -1;
+    double4 par = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (tid < ps.nterms) {
+        it = b.terms[ps.term0 + tid];
+        par = b.term_par[ps.term0 + tid];
+    }
     TF* F = (TF*)b.forces;
     TF f0[3] = {TF(0), TF(0), TF(0)};
     double v0[3] = {0.0, 0.0, 0.0}, ma = 1.0;
-    if (lead) {
-        for (int c = 0; c < 3; ++c) f0[c] = F[3 * a + c];
+    if (live) {
+        for (int c = 0; c < 3; ++c) lpos[c * b.max_atoms + tid] = b.pos[3 * (size_t)a + c];
+        for (int c = 0; c < 3; ++c) f0[c] = F[3 * (size_t)a + c];
         if (kick) {
-            for (int c = 0; c < 3; ++c) v0[c] = m.vel[3 * a + c];
+            for (int c = 0; c < 3; ++c) v0[c] = m.vel[3 * (size_t)a + c];
             ma = m.mass[a];
         }
     }
-    if (live) {
-        const BondItem* items = b.items + (size_t)a * b.slots;
-        for (int k = sub; k < b.slots; k += G) {
-            const BondItem it = items[k];
+    __syncthreads();
+    for (int p = 0; ps.nterms > 0; ++p) {
+        for (int t = tid; t < ps.nterms; t += kMdBlock) {
+            if (p > 0 || t > tid) {
+                it = b.terms[ps.term0 + t];
+                par = b.term_par[ps.term0 + t];
+            }
+            if (it.kind < 0) continue;
+            // positions: an owned atom's from LDS, another block's from memory
             double x[4][3];
-            item_positions(b.pos, b.n, it, x);
-            if (it.kind == 3) pair14_force(b, it, x, fa, acc);
-            else if (it.kind >= 0) entry_force(b, it, x, fa, acc);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) x[q][c] = lpos[c * b.max_atoms + max(it.atom[q], 0)];
+            if ((it.atom[0] | it.atom[1] | it.atom[2] | it.atom[3]) < 0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (it.atom[q] < 0)
+                        for (int c = 0; c < 3; ++c) x[q][c] = b.pos[3 * (size_t)~it.atom[q] + c];
+            }
+            const double pr[4] = {par.x, par.y, par.z, par.w};
+            const bool own = Sums && it.atom[0] >= 0;
+            double f[4][3] = {};
+            if (it.kind == 0) bond_force(b, pr, x, own, f, acc);
+            else if (it.kind == 1) angle_force(b, pr, x, own, f, acc);
+            else if (it.kind == 2) dihedral_force(b, pr, x, own, f, acc);
+            else pair14_force(b, it.pair, x, Sums ? (it.atom[0] >= 0 ? 0.5 : 0.0) +
+                                                   (it.atom[1] >= 0 ? 0.5 : 0.0) : 0.0, f, acc);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (it.slot[q] == kNoSlot) continue;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) lf[c * b.max_slots + it.slot[q]] = f[q][c];
+            }
         }
+        __syncthreads();
+        if (live) {
+            const int s0 = b.atom_slot[ps.slot0 + tid], s1 = b.atom_slot[ps.slot0 + tid + 1];
+            for (int k = s0; k < s1; ++k)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) fa[c] += lf[c * b.max_slots + k];
+        }
+        if (p >= bb.nmore) break;
+        ps = b.passes[bb.more0 + p];
+        __syncthreads();               // the slots are used again
     }
-    // every lane takes part in the group sums (idle lanes add zeros)
-    for (int c = 0; c < 3; ++c) fa[c] = group_sum(fa[c], G);
     double ke = 0.0;
-    if (lead) {
+    if (live) {
         TF ft[3];
         for (int c = 0; c < 3; ++c) {
             ft[c] = f0[c] + (TF)fa[c];
-            F[3 * a + c] = ft[c];
+            F[3 * (size_t)a + c] = ft[c];
         }
         if (kick) {
             const double dt = m.st->dt;
             const double am = m.ftm2v / ma;
             for (int c = 0; c < 3; ++c) {
                 const double v = v0[c] + 0.5 * dt * am * (double)ft[c];
-                m.vel[3 * a + c] = v;
+                m.vel[3 * (size_t)a + c] = v;
                 ke += ma * v * v;
             }
         }
     }
-    if (b.partial) {
+    if constexpr (Sums) {
         const double r = block_sum<10>(acc, red);
-        if (threadIdx.x < 10) b.partial[(size_t)blockIdx.x * 10 + threadIdx.x] = r;
+        if (tid < 10) b.partial[(size_t)blockIdx.x * 10 + tid] = r;
     }
     if (kick) {
         const double r = block_sum<1>(&ke, red);
-        if (threadIdx.x == 0) m.partial[blockIdx.x] = r;
+        if (tid == 0) m.partial[blockIdx.x] = r;
     }
 }
 
@@ -511,22 +552,22 @@ __global__ void k_md_unit_scale(MdState* st) { st->s2 = 1.0; }
 hipError_t launch_bonded(const BondedArgs& b, const MdArgs* m, int force_prec, hipStream_t s)
 {
     if (b.n == 0) return hipSuccess;
-    const dim3 grid(bonded_blocks(b.n, b.log_lanes));
+    const dim3 grid(b.nblocks);
     const MdArgs none{};
     const int kick = m ? 1 : 0;
-    if (force_prec == 64)
-        hipLaunchKernelGGL(k_bonded<double>, grid, dim3(kMdBlock), 0, s, b, m ? *m : none, kick);
-    else
-        hipLaunchKernelGGL(k_bonded<float>, grid, dim3(kMdBlock), 0, s, b, m ? *m : none, kick);
+    const size_t lds = sizeof(double) * 3 * (size_t)(b.max_atoms + b.max_slots);
+#define RELRES_BONDED(TF, SUMS)                                                                  \
+    hipLaunchKernelGGL((k_bonded<TF, SUMS>), grid, dim3(kMdBlock), lds, s, b, m ? *m : none, kick)
+    if (force_prec == 64) {
+        if (b.partial) RELRES_BONDED(double, true); else RELRES_BONDED(double, false);
+    } else {
+        if (b.partial) RELRES_BONDED(float, true); else RELRES_BONDED(float, false);
+    }
+#undef RELRES_BONDED
     return hipGetLastError();
 }
 
 int md_blocks(int n) { return (n + kMdBlock - 1) / kMdBlock; }
-
-int bonded_blocks(int n, int log_lanes)
-{
-    return (int)(((long long)n << log_lanes) + kMdBlock - 1) / kMdBlock;
-}
 
 hipError_t launch_sum_partials(const double* p1, int n1, const double* p2, int n2, int K,
                                double* out, hipStream_t s)
