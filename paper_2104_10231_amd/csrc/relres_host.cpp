@@ -292,13 +292,14 @@ struct relres_ctx {
     std::vector<int> hybrid;
     std::vector<PairCoef<double>> coef64;     // per type pair
     std::vector<PairCoef<double>> coef_grad;  // [4][pair]: d/d eps_FG, sigma_FG, eps_CG, sigma_CG
+    std::vector<double> pair_eps;             // [pair][2]: eps_FG, eps_CG (0: no CG part)
     // per-type parameters the pair tables were mixed from (relres_create,
     // relres_set_type_params); false after relres_set_pair_params, which
     // bypasses the mixing (per-type gradients are then undefined)
     std::vector<double> type_par;     // [4][ntypes]: eps_FG, sigma_FG, eps_CG, sigma_CG
     bool tables_from_types = true;
     DBuf d_mix_jac, d_gpair;          // mixing Jacobian (see mix_jacobian); pair gradients
-    DBuf d_coef64, d_coef32, d_hybrid, d_coef_grad, d_bpartial, d_pcut64, d_pcut32;
+    DBuf d_coef64, d_coef32, d_hybrid, d_back_tab, d_bpartial, d_pcut64, d_pcut32;
     double cut64[8] = {0};            // the distances of every pair when !per_pair
 
     bool topo_set = false;
@@ -390,6 +391,7 @@ void build_tables(relres_ctx* c, const double* ef, const double* sf, const doubl
     const size_t np = (size_t)nt * nt;
     c->coef64.assign(np, PairCoef<double>{});
     c->coef_grad.assign(4 * np, PairCoef<double>{});
+    c->pair_eps.assign(2 * np, 0.0);
     const int ns = c->no_shift;
     for (int a = 0; a < nt; ++a)
         for (int b = 0; b < nt; ++b) {
@@ -399,7 +401,9 @@ void build_tables(relres_ctx* c, const double* ef, const double* sf, const doubl
             fg_part(c->coef64[q], ef[q], sf[q], 0, r[0], Ds);
             fg_part(c->coef_grad[0 * np + q], ef[q], sf[q], 1, r[0], Ds);
             fg_part(c->coef_grad[1 * np + q], ef[q], sf[q], 2, r[0], Ds);
+            c->pair_eps[2 * q] = ef[q];
             if (c->hybrid[a] && c->hybrid[b]) {
+                c->pair_eps[2 * q + 1] = ec[q];
                 cg_part(c->coef64[q], ec[q], sc[q], 0, r[1], r[2], Ds, Dc, ns);
                 cg_part(c->coef_grad[2 * np + q], ec[q], sc[q], 1, r[1], r[2], Ds, Dc, ns);
                 cg_part(c->coef_grad[3 * np + q], ec[q], sc[q], 2, r[1], r[2], Ds, Dc, ns);
@@ -469,8 +473,6 @@ int upload_tables(relres_ctx* c)
                       hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->d_coef32.p, coef32.data(), sizeof(PairCoef<float>) * coef32.size(),
                       hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->d_coef_grad.p, c->coef_grad.data(),
-                      sizeof(PairCoef<double>) * c->coef_grad.size(), hipMemcpyHostToDevice));
     const size_t np = c->dist.size() / 4;
     std::vector<Cutoffs<double>> p64(np);
     std::vector<Cutoffs<float>> p32(np);
@@ -478,6 +480,20 @@ int upload_tables(relres_ctx* c)
         p64[q] = cutoffs_of<double>(&c->dist[4 * q]);
         p32[q] = cutoffs_of<float>(&c->dist[4 * q]);
     }
+    // the adjoint's packed table (kBackTab)
+    std::vector<double> back(np * kBackTab);
+    for (size_t q = 0; q < np; ++q) {
+        double* t = &back[q * kBackTab];
+        for (int k = 0; k < 4; ++k) {
+            const double* rec = reinterpret_cast<const double*>(&c->coef_grad[k * np + q]);
+            if (k < 2) std::copy(rec, rec + kFgFields, t + (k == 0 ? kTabFgE : kTabFgS));
+            else std::copy(rec + kFgFields, rec + kFgFields + kCgFields, t + (k == 2 ? kTabCgE : kTabCgS));
+        }
+        t[kTabEps] = c->pair_eps[2 * q];
+        t[kTabEps + 1] = c->pair_eps[2 * q + 1];
+        std::memcpy(t + kTabCut, &p64[q], sizeof(Cutoffs<double>));
+    }
+    HIP_TRY(hipMemcpy(c->d_back_tab.p, back.data(), sizeof(double) * back.size(), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->d_pcut64.p, p64.data(), sizeof(Cutoffs<double>) * np, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->d_pcut32.p, p32.data(), sizeof(Cutoffs<float>) * np, hipMemcpyHostToDevice));
     return RELRES_OK;
@@ -1375,7 +1391,7 @@ int relres_create(const relres_params* p, relres_ctx** out)
     int rc;
     if ((rc = ensure(c->d_coef64, sizeof(PairCoef<double>) * c->coef64.size(), &c->alloc_generation))) return bail(rc);
     if ((rc = ensure(c->d_coef32, sizeof(PairCoef<float>) * c->coef64.size(), &c->alloc_generation))) return bail(rc);
-    if ((rc = ensure(c->d_coef_grad, sizeof(PairCoef<double>) * c->coef_grad.size(), &c->alloc_generation))) return bail(rc);
+    if ((rc = ensure(c->d_back_tab, sizeof(double) * kBackTab * nt * nt, &c->alloc_generation))) return bail(rc);
     if ((rc = ensure(c->d_pcut64, sizeof(Cutoffs<double>) * nt * nt, &c->alloc_generation))) return bail(rc);
     if ((rc = ensure(c->d_pcut32, sizeof(Cutoffs<float>) * nt * nt, &c->alloc_generation))) return bail(rc);
     if ((rc = ensure(c->d_hybrid, sizeof(int) * nt, &c->alloc_generation))) return bail(rc);
@@ -2065,11 +2081,11 @@ int enqueue_backward(relres_ctx* c, const double* pos, const double* grad_forces
     b.gforce = grad_forces;
     b.genergy = grad_energy;
     b.gpos = grad_pos;
-    b.cgrad = c->d_coef_grad.as<PairCoef<double>>();
-    const int waves = (a.blocks_a + a.blocks_b) * (kForceBlock / 64);
-    TRY(ensure(c->d_bpartial, sizeof(double) * (size_t)std::max(1, waves) * nbins, &c->alloc_generation));
+    b.table = c->d_back_tab.as<double>();
+    TRY(ensure(c->d_bpartial, sizeof(double) * (size_t)std::max(1, a.blocks_a + a.blocks_b) * nbins,
+               &c->alloc_generation));
     b.partial = c->d_bpartial.as<double>();
-    HIP_TRY(launch_backward(b, waves, grad_pair, s));
+    HIP_TRY(launch_backward(b, grad_pair, s));
     return RELRES_OK;
 }
 
@@ -2590,7 +2606,7 @@ void relres_destroy(relres_ctx* c)
 {
     if (!c) return;
     (void)hipDeviceSynchronize();
-    for (DBuf* b : {&c->d_coef_grad, &c->d_bpartial, &c->d_sys, &c->d_boxes, &c->d_row_ew, &c->d_wave_ew,
+    for (DBuf* b : {&c->d_back_tab, &c->d_bpartial, &c->d_sys, &c->d_boxes, &c->d_row_ew, &c->d_wave_ew,
                     &c->d_wave_sys}) release(*b);
     for (DBuf* b : {&c->d_bond_blocks, &c->d_bond_passes, &c->d_bond_terms, &c->d_term_par, &c->d_atom_slot,
                     &c->d_bond_part, &c->d_bond_sum,

@@ -223,19 +223,27 @@ hipError_t launch_lists(GridDev* grids_dev, int ncell_a, int ncell_s, int waves_
 hipError_t launch_forces(const ForceArgs& a, const double* cut64, bool per_pair, int pair_math,
                          int precision, bool ew, hipStream_t s);
 hipError_t launch_list_stats(GridDev* grids_dev, int ngrids, Status* st, hipStream_t s);
-// Backward (adjoint) pass: ForceArgs (positions, lists, FP64 table) plus
+// The adjoint's table, kBackTab doubles per type pair: the FG fields of the
+// eps and the sigma derivative records, the CG fields of both, eps_FG, eps_CG,
+// and the pair's distances (Cutoffs).
+constexpr int kFgFields = 10, kCgFields = 14;       // PairCoef's fields, FG first
+constexpr int kTabFgE = 0, kTabFgS = kFgFields, kTabCgE = 2 * kFgFields,
+              kTabCgS = kTabCgE + kCgFields, kTabEps = kTabCgS + kCgFields,
+              kTabCut = kTabEps + 2, kBackTab = kTabCut + 8;
+static_assert(sizeof(PairCoef<double>) == sizeof(double) * (kFgFields + kCgFields), "PairCoef");
+static_assert(kBackTab % 2 == 0, "the table is copied two doubles at a time");
+// Backward (adjoint) pass: ForceArgs (positions, lists) plus
 struct BackArgs {
     ForceArgs f;
     const double* gforce;                 // dJ/dF, N x 3, or NULL
     const double* genergy;                // dJ/dE per system (device, nsys) or NULL
     double* gpos;                         // out: dJ/dx, N x 3
-    const PairCoef<double>* cgrad;        // [4][ntypes^2] derivative records
-    double* partial;                      // per wave: [ntypes^2][4] parameter sums
+    const double* table;                  // [ntypes^2][kBackTab]
+    double* partial;                      // [ntypes^2][4][blocks] parameter sums of the blocks
 };
 constexpr int kBackwardTypes = 8;
-// waves = wavefronts of the launch; grad_pair receives [4][ntypes][ntypes];
-// distances per type pair from b.f.pcut64
-hipError_t launch_backward(const BackArgs& b, int waves, double* grad_pair, hipStream_t s);
+// grad_pair receives [4][ntypes][ntypes]; distances per type pair from b.f.pcut64
+hipError_t launch_backward(const BackArgs& b, double* grad_pair, hipStream_t s);
 // per-type gradients [4][nt] from pair gradients [4][nt][nt] and the mixing
 // Jacobian [2][nt][nt][6] (relres_backward_types)
 hipError_t launch_type_grad(const double* gpair, const double* jac, int nt, double* gtype,

@@ -2181,126 +2181,150 @@ hipError_t launch_list_stats(GridDev* grids_dev, int ngrids, Status* st, hipStre
 // of parameter P (the terms are linear in the record's coefficients).  Each
 // unordered pair appears in both rows, hence the half energy weight.
 
-// FG part with the Hessian factor, FP64.
-__device__ __forceinline__ void fg_terms2(const PairCoef<double>& c, const Cutoffs<double>& cut,
-                                          double r2, double& fpair, double& en, double& hc)
+// The terms are linear in eps, so the record of the eps derivative (unit eps)
+// gives the pair's own terms too: fpair = eps f_eps, hc = eps h_eps.  A pair
+// is evaluated with the eps and the sigma records only, which share r and its
+// powers.
+//
+// Terms of one pair from a record: fpair, energy and h = (d fpair/dr)/r.
+struct PairTerms {
+    double f, e, h;
+};
+
+// LJ region: q = {c12, c6, e12, e6}
+__device__ __forceinline__ PairTerms lj_terms(const double* q, double r2i, double r6i, double shift)
+{
+    return {r6i * (q[0] * r6i - q[1]) * r2i, r6i * (q[2] * r6i - q[3]) - shift,
+            r2i * r2i * r6i * (8.0 * q[1] - 14.0 * q[0] * r6i)};
+}
+
+// A quartic zone: g = {gamma_0 .. gamma_4}, d = r - r_-
+__device__ __forceinline__ PairTerms zone_terms(double g0, double g1, double g2, double g3,
+                                                double g4, double d, double ir, double shift)
+{
+    const double dp = g1 + d * (2.0 * g2 + d * (3.0 * g3 + d * (4.0 * g4)));
+    const double dpp = 2.0 * g2 + d * (6.0 * g3 + d * (12.0 * g4));
+    const double f = -dp * ir;
+    return {f, g0 + d * (g1 + d * (g2 + d * (g3 + d * g4))) - shift, (-dpp - f) * ir * ir};
+}
+
+// The eps and sigma terms of one pair, FG part (r2 < r_s+^2) or CG part
+// (r2 < r_c+^2); T is the pair's table.
+template <bool CG>
+__device__ __forceinline__ void back_terms(const double* T, double r2, PairTerms& te, PairTerms& ts)
 {
     using M = MathF64<2>;
-    if (r2 < cut.rsi2) {
+    const Cutoffs<double>& cut = *reinterpret_cast<const Cutoffs<double>*>(T + kTabCut);
+    const double* E = T + (CG ? kTabCgE : kTabFgE);
+    const double* S = T + (CG ? kTabCgS : kTabFgS);
+    // CG fields: 4 LJ, gamma_0+, gamma_3+, gamma_4+, 5 of f_c-, Gamma_c-', Gamma_c-
+    if (r2 < (CG ? cut.rci2 : cut.rsi2)) {
+        if (CG && r2 < cut.rso2) {
+            if (r2 < cut.rsi2) {
+                te = {0.0, E[4] - E[13], 0.0};
+                ts = {0.0, S[4] - S[13], 0.0};
+                return;
+            }
+            double r, ir;
+            M::root(r2, r, ir);
+            const double d = r - cut.rsi;
+            te = zone_terms(E[4], 0.0, 0.0, E[5], E[6], d, ir, E[13]);
+            ts = zone_terms(S[4], 0.0, 0.0, S[5], S[6], d, ir, S[13]);
+            return;
+        }
         const double r2i = M::recip(r2);
         const double r6i = r2i * r2i * r2i;
-        fpair = r6i * (c.fg_c12 * r6i - c.fg_c6) * r2i;
-        en = r6i * (c.fg_e12 * r6i - c.fg_e6) - c.fg_shift;
-        hc = r2i * r2i * r6i * (8.0 * c.fg_c6 - 14.0 * c.fg_c12 * r6i);
+        te = lj_terms(E, r2i, r6i, CG ? E[12] : E[9]);
+        ts = lj_terms(S, r2i, r6i, CG ? S[12] : S[9]);
     } else {
         double r, ir;
         M::root(r2, r, ir);
-        const double d = r - cut.rsi;
-        const double dp = c.fg_g[1] + d * (2.0 * c.fg_g[2] + d * (3.0 * c.fg_g[3] + d * (4.0 * c.fg_g[4])));
-        const double dpp = 2.0 * c.fg_g[2] + d * (6.0 * c.fg_g[3] + d * (12.0 * c.fg_g[4]));
-        fpair = -dp * ir;
-        en = c.fg_g[0] + d * (c.fg_g[1] + d * (c.fg_g[2] + d * (c.fg_g[3] + d * c.fg_g[4]))) - c.fg_shift;
-        hc = (-dpp - fpair) * ir * ir;
+        const double d = r - (CG ? cut.rci : cut.rsi);
+        constexpr int g = CG ? 7 : 4;
+        te = zone_terms(E[g], E[g + 1], E[g + 2], E[g + 3], E[g + 4], d, ir, CG ? E[12] : E[9]);
+        ts = zone_terms(S[g], S[g + 1], S[g + 2], S[g + 3], S[g + 4], d, ir, CG ? S[12] : S[9]);
     }
 }
 
-// CG part with the Hessian factor, FP64.
-__device__ __forceinline__ void cg_terms2(const PairCoef<double>& c, const Cutoffs<double>& cut,
-                                          double r2, double& fpair, double& en, double& hc)
-{
-    using M = MathF64<2>;
-    if (r2 < cut.rsi2) {
-        fpair = 0.0;
-        en = c.sp_g0 - c.sp_shift;
-        hc = 0.0;
-    } else if (r2 < cut.rso2) {
-        double r, ir;
-        M::root(r2, r, ir);
-        const double d = r - cut.rsi;
-        const double dp = d * d * (3.0 * c.sp_g3 + 4.0 * c.sp_g4 * d);
-        const double dpp = d * (6.0 * c.sp_g3 + 12.0 * c.sp_g4 * d);
-        fpair = -dp * ir;
-        en = c.sp_g0 + d * d * d * (c.sp_g3 + d * c.sp_g4) - c.sp_shift;
-        hc = (-dpp - fpair) * ir * ir;
-    } else if (r2 < cut.rci2) {
-        const double r2i = M::recip(r2);
-        const double r6i = r2i * r2i * r2i;
-        fpair = r6i * (c.cg_c12 * r6i - c.cg_c6) * r2i;
-        en = r6i * (c.cg_e12 * r6i - c.cg_e6) - c.cm_shift;
-        hc = r2i * r2i * r6i * (8.0 * c.cg_c6 - 14.0 * c.cg_c12 * r6i);
-    } else {
-        double r, ir;
-        M::root(r2, r, ir);
-        const double d = r - cut.rci;
-        const double dp = c.cm_g[1] + d * (2.0 * c.cm_g[2] + d * (3.0 * c.cm_g[3] + d * (4.0 * c.cm_g[4])));
-        const double dpp = 2.0 * c.cm_g[2] + d * (6.0 * c.cm_g[3] + d * (12.0 * c.cm_g[4]));
-        fpair = -dp * ir;
-        en = c.cm_g[0] + d * (c.cm_g[1] + d * (c.cm_g[2] + d * (c.cm_g[3] + d * c.cm_g[4]))) - c.cm_shift;
-        hc = (-dpp - fpair) * ir * ir;
-    }
-}
-
-// One list row of the backward pass (FG part when CG is false, CG part when
-// true); TM bounds the number of types.
+// Entries sub, sub + G, ... of one list row (FG part when CG is false, CG
+// part when true), two per lane at a time: their list loads, then their
+// position and gradient gathers, are issued together; `e` holds the first two
+// (read with the row record).  TM bounds the number of types.  acc[q]: the eps
+// and sigma sums of entries of type q.
 template <bool CG, int TM>
-__device__ __forceinline__ void back_row(const BackArgs& b, const BoxV& bx, int ti,
+__device__ __forceinline__ void back_row(const BackArgs& b, const BoxV& bx, const double* T,
                                          double xi, double yi, double zi, double gix, double giy,
                                          double giz, double ebar, const int* __restrict__ lst,
-                                         int cnt, int sub, int G, double gp[3], double acc[TM][4])
+                                         int cnt, int sub, int G, uint32_t e[2], double gp[3],
+                                         double acc[TM][2])
 {
     const ForceArgs& a = b.f;
-    const int nt = a.ntypes;
-    const int np = nt * nt;
-    const PairCoef<double>* coef = (const PairCoef<double>*)a.coef64;
-    constexpr int P0 = CG ? 2 : 0;
-    for (int k = sub; k < cnt; k += G) {
-        const uint32_t e = (uint32_t)lst[k];
-        const int uj = (int)(e & kIdxMask), tj = (int)(e >> kIdxBits);
-        double dx = xi - a.pos[3 * uj];
-        double dy = yi - a.pos[3 * uj + 1];
-        double dz = zi - a.pos[3 * uj + 2];
-        dx -= bx.L[0] * rint(dx * bx.iL[0]);
-        dy -= bx.L[1] * rint(dy * bx.iL[1]);
-        dz -= bx.L[2] * rint(dz * bx.iL[2]);
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        const int pi = ti * nt + tj;
-        const Cutoffs<double>& cut = a.pcut64[pi];
-        if (!(r2 < (CG ? cut.rco2 : cut.rso2))) continue;
-        double fp, en, hc, fe, ee, fs, es;
-        if constexpr (CG) {
-            cg_terms2(coef[pi], cut, r2, fp, en, hc);
-            cg_term<MathF64<2>>(b.cgrad[2 * np + pi], cut, r2, fe, ee);
-            cg_term<MathF64<2>>(b.cgrad[3 * np + pi], cut, r2, fs, es);
-        } else {
-            fg_terms2(coef[pi], cut, r2, fp, en, hc);
-            fg_term<MathF64<2>>(b.cgrad[0 * np + pi], cut, r2, fe, ee);
-            fg_term<MathF64<2>>(b.cgrad[1 * np + pi], cut, r2, fs, es);
-        }
-        double wx = gix, wy = giy, wz = giz;
-        if (b.gforce) {
-            wx -= b.gforce[3 * uj];
-            wy -= b.gforce[3 * uj + 1];
-            wz -= b.gforce[3 * uj + 2];
-        }
-        const double dw = dx * wx + dy * wy + dz * wz;
-        gp[0] += -ebar * fp * dx + fp * wx + hc * dw * dx;
-        gp[1] += -ebar * fp * dy + fp * wy + hc * dw * dy;
-        gp[2] += -ebar * fp * dz + fp * wz + hc * dw * dz;
-        const double gd = gix * dx + giy * dy + giz * dz;
-        const double ve = 0.5 * ebar * ee + gd * fe;
-        const double vs = 0.5 * ebar * es + gd * fs;
+    for (int base = sub; base < cnt; base += 2 * G) {
+        double px[2], py[2], pz[2], gx[2], gy[2], gz[2];
 #pragma unroll
-        for (int q = 0; q < TM; ++q)
-            if (q == tj) {
-                acc[q][P0] += ve;
-                acc[q][P0 + 1] += vs;
+        for (int u = 0; u < 2; ++u) {
+            const int k = base + u * G;
+            if (base != sub) e[u] = k < cnt ? (uint32_t)lst[k] : kNoEntry;
+            else if (k >= cnt) e[u] = kNoEntry;
+        }
+        gather_batch<2>(a, e, px, py, pz);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            gx[u] = gy[u] = gz[u] = 0.0;
+            if (b.gforce) {
+                const int uj = e[u] != kNoEntry ? (int)(e[u] & kIdxMask) : 0;
+                gx[u] = b.gforce[3 * uj];
+                gy[u] = b.gforce[3 * uj + 1];
+                gz[u] = b.gforce[3 * uj + 2];
             }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (e[u] == kNoEntry) continue;
+            const int tj = (int)(e[u] >> kIdxBits);
+            double dx = xi - px[u];
+            double dy = yi - py[u];
+            double dz = zi - pz[u];
+            dx -= bx.L[0] * rint(dx * bx.iL[0]);
+            dy -= bx.L[1] * rint(dy * bx.iL[1]);
+            dz -= bx.L[2] * rint(dz * bx.iL[2]);
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            const double* Tj = T + tj * kBackTab;
+            const Cutoffs<double>& cut = *reinterpret_cast<const Cutoffs<double>*>(Tj + kTabCut);
+            if (!(r2 < (CG ? cut.rco2 : cut.rso2))) continue;
+            PairTerms te, ts;
+            back_terms<CG>(Tj, r2, te, ts);
+            const double eps = Tj[kTabEps + (CG ? 1 : 0)];
+            const double fp = eps * te.f, hc = eps * te.h;
+            const double wx = gix - gx[u], wy = giy - gy[u], wz = giz - gz[u];
+            const double hd = hc * (dx * wx + dy * wy + dz * wz) - ebar * fp;
+            gp[0] += fp * wx + hd * dx;
+            gp[1] += fp * wy + hd * dy;
+            gp[2] += fp * wz + hd * dz;
+            const double gd = gix * dx + giy * dy + giz * dz, he = 0.5 * ebar;
+            const double ve = he * te.e + gd * te.f;
+            const double vs = he * ts.e + gd * ts.f;
+#pragma unroll
+            for (int q = 0; q < TM; ++q) {
+                acc[q][0] += q == tj ? ve : 0.0;
+                acc[q][1] += q == tj ? vs : 0.0;
+            }
+        }
     }
 }
 
+// One launch over the rows of the force kernel.  What bounds it is the chain
+// row record -> list entries -> gathers -> pair terms of its waves and the
+// FP64 issue of the terms.  The tables are staged in LDS (read per pair from
+// memory before), two entries per lane are in flight, a pair takes two record
+// evaluations instead of three, and a block leaves one partial per bin, with
+// the blocks of a bin side by side for k_reduce_bins (one per wave, a whole
+// record apart, before).  98304-atom copolymer, four types: 35 us in the kernel
+// trace, 72.7 us before.
 template <int TM>
-__global__ __launch_bounds__(kForceBlock) void k_backward(BackArgs b)
+__global__ __launch_bounds__(kForceBlock, TM == 4 ? 4 : 1) void k_backward(BackArgs b)
 {
+    extern __shared__ __align__(16) double back_lds[];
     const ForceArgs& a = b.f;
     const bool rb = (int)blockIdx.x >= a.blocks_a;
     const int lb = rb ? (int)blockIdx.x - a.blocks_a : (int)blockIdx.x;
@@ -2311,42 +2335,72 @@ __global__ __launch_bounds__(kForceBlock) void k_backward(BackArgs b)
     const int G = 1 << lg;
     const int row = logical * (kForceBlock >> lg) + ((int)threadIdx.x >> lg);
     const int sub = (int)threadIdx.x & (G - 1);
+    const int nt = a.ntypes, np = nt * nt;
+    double* tab = back_lds;                              // [np][kBackTab]
+    double* red = back_lds + np * kBackTab;              // [4 waves][nt][nt][4]
 
-    int4 rec = make_int4(-1, 0, 0, 1);
-    int cnt_a = 0;
-    if (!rb) {
-        if (row < a.n_arow) rec = a.a_rec[row];
-    } else if (row < a.n_srow) {
-        rec = a.s_rec[row];
-        cnt_a = a.a_rec[rec.w].z;
+    // the packed tables' first words before the row record, so the two reads
+    // overlap (written to LDS once the row's own reads are issued)
+    typedef double double2v __attribute__((ext_vector_type(2)));
+    RELRES_GLOBAL const double2v* ptab = (RELRES_GLOBAL const double2v*)b.table;
+    const int words = np * kBackTab / 2;
+    const double2v t_first = ptab[min((int)threadIdx.x, words - 1)];
+    // the first entries of the row's own list, whatever its length (slots past
+    // the end are dropped once it is known)
+    const bool live = rb ? row < a.n_srow : row < a.n_arow;
+    uint32_t e_own[2], e_fg[2] = {kNoEntry, kNoEntry};
+    {
+        const int* lst = rb ? a.s_list + (size_t)row * a.s_cap : a.a_list + (size_t)row * a.a_cap;
+        const int cap = rb ? a.s_cap : a.a_cap;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            e_own[u] = live && sub + u * G < cap ? (uint32_t)lst[sub + u * G] : kNoEntry;
     }
+    int4 rec = make_int4(-1, 0, 0, 1);
+    if (live) rec = rb ? a.s_rec[row] : a.a_rec[row];
     const bool own = rb ? rec.x >= 0 : (rec.x >= 0 && rec.w == 0);
-    const int sy = rec.x >= 0 ? rec.y >> kTypeBits : 0;
-    const double ebar = b.genergy ? b.genergy[sy] : 0.0;
-    const BoxV bx = row_box(a, sy);
-    double acc[TM][4];
-#pragma unroll
-    for (int q = 0; q < TM; ++q)
-#pragma unroll
-        for (int P = 0; P < 4; ++P) acc[q][P] = 0.0;
-    double gp[3] = {0.0, 0.0, 0.0};
-    const int ti = rec.y & ((1 << kTypeBits) - 1);
+    int cnt_a = rec.z;
+    double xi = 0.0, yi = 0.0, zi = 0.0, gix = 0.0, giy = 0.0, giz = 0.0;
     if (own) {
         const int ui = rec.x;
-        const double xi = a.pos[3 * ui], yi = a.pos[3 * ui + 1], zi = a.pos[3 * ui + 2];
-        double gix = 0.0, giy = 0.0, giz = 0.0;
+        if (rb) {
+            const int* lst = a.a_list + (size_t)rec.w * a.a_cap;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (sub + u * G < a.a_cap) e_fg[u] = (uint32_t)lst[sub + u * G];
+            cnt_a = a.a_rec[rec.w].z;
+        }
+        xi = a.pos[3 * ui];
+        yi = a.pos[3 * ui + 1];
+        zi = a.pos[3 * ui + 2];
         if (b.gforce) {
             gix = b.gforce[3 * ui];
             giy = b.gforce[3 * ui + 1];
             giz = b.gforce[3 * ui + 2];
         }
+    }
+    const int sy = rec.x >= 0 ? rec.y >> kTypeBits : 0;
+    const double ebar = b.genergy ? b.genergy[sy] : 0.0;
+    const BoxV bx = row_box(a, sy);
+    {
+        double2v* t2 = (double2v*)tab;
+        if ((int)threadIdx.x < words) t2[threadIdx.x] = t_first;
+        for (int k = (int)threadIdx.x + kForceBlock; k < words; k += kForceBlock) t2[k] = ptab[k];
+    }
+    for (int k = (int)threadIdx.x; k < 4 * 4 * np; k += kForceBlock) red[k] = 0.0;
+    __syncthreads();
+    double afg[TM][2] = {}, acg[TM][2] = {};
+    double gp[3] = {0.0, 0.0, 0.0};
+    const int ti = rec.y & ((1 << kTypeBits) - 1);
+    if (own) {
         const int ar = rb ? rec.w : row;
-        const int ca = rb ? cnt_a : rec.z;
-        back_row<false, TM>(b, bx, ti, xi, yi, zi, gix, giy, giz, ebar,
-                            a.a_list + (size_t)ar * a.a_cap, ca, sub, G, gp, acc);
+        const double* T = tab + ti * nt * kBackTab;
+        back_row<false, TM>(b, bx, T, xi, yi, zi, gix, giy, giz, ebar,
+                            a.a_list + (size_t)ar * a.a_cap, cnt_a, sub, G, rb ? e_fg : e_own, gp,
+                            afg);
         if (rb)
-            back_row<true, TM>(b, bx, ti, xi, yi, zi, gix, giy, giz, ebar,
-                               a.s_list + (size_t)row * a.s_cap, rec.z, sub, G, gp, acc);
+            back_row<true, TM>(b, bx, T, xi, yi, zi, gix, giy, giz, ebar,
+                               a.s_list + (size_t)row * a.s_cap, rec.z, sub, G, e_own, gp, acg);
     }
     for (int c = 0; c < 3; ++c) gp[c] = group_sum(gp[c], G);
     if (own && sub == 0) {
@@ -2354,37 +2408,56 @@ __global__ __launch_bounds__(kForceBlock) void k_backward(BackArgs b)
         b.gpos[3 * rec.x + 1] = gp[1];
         b.gpos[3 * rec.x + 2] = gp[2];
     }
-    // per-wave sums per (row type, entry type, parameter), fixed order
-    const int nt = a.ntypes;
-    const int nbins = 4 * nt * nt;
-    const int wave = (int)blockIdx.x * (kForceBlock / 64) + (int)(threadIdx.x >> 6);
-    double* out = b.partial + (size_t)wave * nbins;
-    for (int t = 0; t < nt; ++t)
+    // per-wave sums per (row type, entry type, parameter) of the types the
+    // wave's rows have, then the block's waves in order
+    const int wave = (int)(threadIdx.x >> 6);
+    for (int t = 0; t < nt; ++t) {
+        if (__ballot(own && ti == t) == 0ull) continue;
+        double v[2 * TM];
+        double* out = red + ((size_t)wave * nt + t) * 4 * nt;
 #pragma unroll
-        for (int q = 0; q < TM; ++q) {
-            if (q >= nt) break;
-            // the four parameters' sums at once (their chains interleaved)
-            double s[4];
+        for (int part = 0; part < 2; ++part) {
+            if (part == 1 && !rb) break;
 #pragma unroll
-            for (int P = 0; P < 4; ++P) s[P] = (own && ti == t) ? acc[q][P] : 0.0;
-            wave_sums(s);
-            if ((threadIdx.x & 63) == 63) {
+            for (int q = 0; q < TM; ++q)
 #pragma unroll
-                for (int P = 0; P < 4; ++P) out[(t * nt + q) * 4 + P] = s[P];
+                for (int P = 0; P < 2; ++P)
+                    v[2 * q + P] = own && ti == t ? (part ? acg[q][P] : afg[q][P]) : 0.0;
+            const int lane = (int)threadIdx.x & (kWave - 1);
+#pragma unroll
+            for (int k = 0; k < 2 * TM; k += 8) {
+                double w[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) w[j] = k + j < 2 * TM ? v[k + j] : 0.0;
+                const double s = wave_sum8(w);
+                const int comp = k + wave_sum8_lane(lane & 7);     // 2 q + P
+                if (lane < 8 && (comp >> 1) < nt) out[4 * (comp >> 1) + 2 * part + (comp & 1)] = s;
             }
         }
+    }
+    __syncthreads();
+    for (int k = (int)threadIdx.x; k < 4 * np; k += kForceBlock)
+        b.partial[(size_t)k * gridDim.x + blockIdx.x] =
+            ((red[k] + red[4 * np + k]) + red[8 * np + k]) + red[12 * np + k];
 }
 
-// dJ/dP[a][b] = sum over waves of the partial sums, in wave order; one block
-// per bin.
-__global__ __launch_bounds__(256) void k_reduce_bins(const double* __restrict__ partial, int waves,
+// dJ/dP[a][b] = sum over blocks of the partial sums, in a fixed order; one
+// block per bin, whose partials lie side by side.
+__global__ __launch_bounds__(256) void k_reduce_bins(const double* __restrict__ partial, int blocks,
                                                      int nt, double* __restrict__ grad_pair)
 {
     __shared__ double red[4];
     const int bin = (int)blockIdx.x;             // (t * nt + q) * 4 + P
-    const int nbins = 4 * nt * nt;
+    const double* p = partial + (size_t)bin * blocks;
     double s = 0.0;
-    for (int w = (int)threadIdx.x; w < waves; w += 256) s += partial[(size_t)w * nbins + bin];
+    // four loads of a thread in flight (past the end, the last one again, dropped)
+    for (int w = (int)threadIdx.x; w < blocks; w += 1024) {
+        double x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = p[min(w + 256 * u, blocks - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += w + 256 * u < blocks ? x[u] : 0.0;
+    }
     const double v = wave_sum(s);
     if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -2394,23 +2467,24 @@ __global__ __launch_bounds__(256) void k_reduce_bins(const double* __restrict__ 
     }
 }
 
-hipError_t launch_backward(const BackArgs& b, int waves, double* grad_pair, hipStream_t s)
+hipError_t launch_backward(const BackArgs& b, double* grad_pair, hipStream_t s)
 {
     const int nt = b.f.ntypes;
     const int blocks = b.f.blocks_a + b.f.blocks_b;
     if (blocks > 0) {
         const dim3 grid(blocks), block(kForceBlock);
+        const size_t lds = sizeof(double) * (size_t)nt * nt * (kBackTab + 16);
         if (nt <= 2)
-            hipLaunchKernelGGL(k_backward<2>, grid, block, 0, s, b);
+            hipLaunchKernelGGL(k_backward<2>, grid, block, lds, s, b);
         else if (nt <= 4)
-            hipLaunchKernelGGL(k_backward<4>, grid, block, 0, s, b);
+            hipLaunchKernelGGL(k_backward<4>, grid, block, lds, s, b);
         else
-            hipLaunchKernelGGL(k_backward<8>, grid, block, 0, s, b);
+            hipLaunchKernelGGL(k_backward<8>, grid, block, lds, s, b);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_reduce_bins, dim3(4 * nt * nt), dim3(256), 0, s, b.partial,
-                       blocks > 0 ? waves : 0, nt, grad_pair);
+    hipLaunchKernelGGL(k_reduce_bins, dim3(4 * nt * nt), dim3(256), 0, s, b.partial, blocks, nt,
+                       grad_pair);
     return hipGetLastError();
 }
 
@@ -2419,36 +2493,38 @@ hipError_t launch_backward(const BackArgs& b, int waves, double* grad_pair, hipS
 // dJ/d eps_ab times d eps_ab/d eps_t, and dJ/d sigma_t likewise through
 // eps_ab and sigma_ab.  jac[(f * nt^2 + q) * 6] holds, for pair q = a*nt + b,
 // the derivatives of (eps_ab, eps_ab, sigma_ab) with respect to (eps_a,
-// sigma_a, sigma_a), then those with respect to type b's values.  One thread
-// per output, sums in a fixed order.
-__global__ __launch_bounds__(256) void k_type_grad(const double* __restrict__ gpair,
-                                                   const double* __restrict__ jac, int nt,
-                                                   double* __restrict__ gtype)
+// sigma_a, sigma_a), then those with respect to type b's values.  Eight lanes
+// per output (kBackwardTypes), lane b with the pairs (t, b) and (b, t), summed
+// in a fixed order: one round of reads, where a thread per output waited for
+// each of its 2 nt pairs (4.4 us for four types, now 3.8).
+__global__ __launch_bounds__(4 * kBackwardTypes * kBackwardTypes) void k_type_grad(
+    const double* __restrict__ gpair, const double* __restrict__ jac, int nt,
+    double* __restrict__ gtype)
 {
-    const int o = (int)threadIdx.x;
-    if (o >= 4 * nt) return;
+    const int o = (int)threadIdx.x / kBackwardTypes, b = (int)threadIdx.x % kBackwardTypes;
+    const bool in = o < 4 * nt && b < nt;
     const int P = o / nt, t = o % nt;
-    const int f = P >> 1, y = P & 1;          // family, 0 = eps / 1 = sigma
-    const size_t np = (size_t)nt * nt;
-    const double* ge = gpair + (size_t)(2 * f) * np;       // dJ/d eps_ab of the family
-    const double* gs = gpair + (size_t)(2 * f + 1) * np;   // dJ/d sigma_ab
-    const double* J = jac + (size_t)f * np * 6;
     double s = 0.0;
-    for (int b = 0; b < nt; ++b) {            // pairs (t, b): type t is the first
-        const size_t q = (size_t)t * nt + b;
-        s += y == 0 ? ge[q] * J[6 * q] : ge[q] * J[6 * q + 1] + gs[q] * J[6 * q + 2];
+    if (in) {
+        const int f = P >> 1, y = P & 1;          // family, 0 = eps / 1 = sigma
+        const size_t np = (size_t)nt * nt;
+        const double* ge = gpair + (size_t)(2 * f) * np;       // dJ/d eps_ab of the family
+        const double* gs = gpair + (size_t)(2 * f + 1) * np;   // dJ/d sigma_ab
+        const double* J = jac + (size_t)f * np * 6;
+        const size_t q = (size_t)t * nt + b, r = (size_t)b * nt + t;
+        // type t is the first of the pair, then the second
+        s = y == 0 ? ge[q] * J[6 * q] : ge[q] * J[6 * q + 1] + gs[q] * J[6 * q + 2];
+        s += y == 0 ? ge[r] * J[6 * r + 3] : ge[r] * J[6 * r + 4] + gs[r] * J[6 * r + 5];
     }
-    for (int a = 0; a < nt; ++a) {            // pairs (a, t): type t is the second
-        const size_t q = (size_t)a * nt + t;
-        s += y == 0 ? ge[q] * J[6 * q + 3] : ge[q] * J[6 * q + 4] + gs[q] * J[6 * q + 5];
-    }
-    gtype[o] = s;
+    s = group_sum(s, kBackwardTypes);
+    if (in && b == 0) gtype[o] = s;
 }
 
 hipError_t launch_type_grad(const double* gpair, const double* jac, int nt, double* gtype,
                             hipStream_t s)
 {
-    hipLaunchKernelGGL(k_type_grad, dim3(1), dim3(256), 0, s, gpair, jac, nt, gtype);
+    hipLaunchKernelGGL(k_type_grad, dim3(1), dim3(4 * kBackwardTypes * kBackwardTypes), 0, s, gpair,
+                       jac, nt, gtype);
     return hipGetLastError();
 }
 

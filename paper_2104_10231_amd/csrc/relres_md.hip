@@ -226,8 +226,8 @@ __device__ __forceinline__ void pair14_force(const BondedArgs& b, int pi, const 
 // slots in LDS; then one thread per atom adds its slots in order.  Every term
 // is evaluated once per block that owns an atom of it, so once for molecules
 // that do not straddle blocks, by waves that take one branch: bound by the
-// dependent reads (term, then position) and one term's arithmetic, 1.2 MFLOP
-// of FP64 per 1000 hexane molecules.  (One lane per atom and term, the version
+// dependent reads (term, then position) and the arithmetic of one term.
+// (One lane per atom and term, the version
 // before, evaluated each term two to four times in waves of all four kinds:
 // 48000-atom hexane 29.8 us in the kernel trace, now 7.4; 6000 atoms 8.0, now
 // 4.7, the launch and three dependent memory round trips.)
