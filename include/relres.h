@@ -419,8 +419,9 @@ int relres_md_state(relres_ctx *ctx, double *xi, double *eta, int set);
  * buffer thermo (nsteps / thermo_every rows): non-bonded energy (Eq. 3), 1-4
  * energy, bond, angle and dihedral energies, kinetic energy, the extended
  * energy K + U + Q xi^2/2 + g kT eta (conserved by the integrator), and the
- * trace of the virial.  Enqueued on `stream`; waits at every list build and
- * at the end.                                                              */
+ * trace of the virial.  Enqueued on `stream`; at every list build it waits for
+ * the status of the build before, and at the end for the run.  When a row of a
+ * build overflowed, the run goes back to that build with grown rows.        */
 int relres_md_run(relres_ctx *ctx, double *pos, double *vel, int nsteps, int thermo_every,
                   double *thermo, void *stream);
 

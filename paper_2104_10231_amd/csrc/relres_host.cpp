@@ -368,8 +368,8 @@ struct relres_ctx {
     double md_ftm2v = 0.0;
     int md_rebuild = 10;
     int md_cur = 0;                   // which of the two state buffers is current
-    DBuf d_mass, d_md_state, d_md_xref, d_md_F, d_md_E, d_md_W, d_md_part, d_md_stale;
-    unsigned int* h_stale = nullptr;
+    DBuf d_mass, d_md_state, d_md_xref, d_md_vsave, d_md_F, d_md_E, d_md_W, d_md_part;
+    unsigned md_stale_seen = 0;       // Status::md_stale when a run last looked at it
 
     bool timing = false;
     std::vector<hipEvent_t> ev_free;
@@ -2362,16 +2362,14 @@ int relres_md_setup(relres_ctx* c, const double* masses, double dt, double kT, d
     long long* gen = &c->alloc_generation;
     TRY(ensure(c->d_mass, sizeof(double) * n, gen));
     HIP_TRY(hipMemcpy(c->d_mass.p, masses, sizeof(double) * n, hipMemcpyHostToDevice));
-    TRY(ensure(c->d_md_state, 2 * sizeof(MdState), gen));   // current and next
+    TRY(ensure(c->d_md_state, 3 * sizeof(MdState), gen));   // current, next, at the last build
     TRY(ensure(c->d_md_xref, sizeof(double) * 3 * n, gen));
+    TRY(ensure(c->d_md_vsave, sizeof(double) * 3 * n, gen));
     TRY(ensure(c->d_md_F, (c->precision == 64 ? 8 : 4) * 3 * (size_t)n, gen));
     TRY(ensure(c->d_md_E, sizeof(double) * 3, gen));
     TRY(ensure(c->d_md_W, sizeof(double) * 6, gen));
     TRY(ensure(c->d_md_part, sizeof(double) * (size_t)std::max(md_blocks(n), c->bond_nblocks), gen));
-    TRY(ensure(c->d_md_stale, 64, gen));
     TRY(ensure(c->d_bond_sum, sizeof(double) * 16, gen));
-    if (!c->h_stale && hipHostMalloc((void**)&c->h_stale, 64, hipHostMallocDefault) != hipSuccess)
-        return fail(RELRES_ERR_HIP, "pinned host allocation failed");
     MdState st{};
     st.xi = st.eta = 0.0;
     st.K = 0.0;
@@ -2415,30 +2413,6 @@ int relres_md_state(relres_ctx* c, double* xi, double* eta, int set)
     return RELRES_OK;
 }
 
-namespace {
-
-// Build the lists at pos (waiting for the build), after checking that no
-// atom moved more than half the skin since the previous build.
-int md_rebuild(relres_ctx* c, const double* pos, hipStream_t s, bool check)
-{
-    // the displacement flag of the steps since the previous build is copied
-    // ahead of the build and read once the build has been waited for: one
-    // host wait per rebuild, not two
-    if (check)
-        HIP_TRY(hipMemcpyAsync(c->h_stale, c->d_md_stale.p, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    const double box[3] = {c->box[0], c->box[1], c->box[2]};
-    TRY(build_checked(c, pos, box, s));
-    if (check && *c->h_stale)
-        return fail(RELRES_ERR_STALE_LISTS, "an atom moved more than half the skin between list "
-                    "builds: rebuild more often or use a larger skin");
-    c->warn_pending = false;          // dynamics checks the displacements itself
-    HIP_TRY(hipMemcpyAsync(c->d_md_xref.p, pos, sizeof(double) * 3 * c->n, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(launch_clear_words((unsigned long long*)c->d_md_stale.p, 8, s));
-    return RELRES_OK;
-}
-
-}  // namespace
-
 int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int thermo_every,
                   double* thermo, void* stream)
 {
@@ -2459,59 +2433,132 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
     m.mass = c->d_mass.as<double>();
     m.xref = c->d_md_xref.as<double>();
     m.half_skin2 = 0.25 * skin_of(c, 0) * skin_of(c, 0);
-    m.stale = (unsigned*)c->d_md_stale.p;
+    m.stale = reinterpret_cast<unsigned int*>(static_cast<char*>(c->d_status.p) +
+                                              offsetof(Status, md_stale));
     m.partial = c->d_md_part.as<double>();
-    MdState* stb = c->d_md_state.as<MdState>();             // two buffers
+    MdState* stb = c->d_md_state.as<MdState>();             // two buffers, then the saved state
     m.st = stb + c->md_cur;
+    double* vsave = c->d_md_vsave.as<double>();
     const int nblk = md_blocks(c->n);                       // partials of k_md_kinetic
-    const int nblk_kick = c->bond_nblocks;  // partials of the kick
+    const int nblk_kick = c->bond_nblocks;                  // partials of the kick
     const double* e_nb = c->d_md_E.as<double>();
     const double* w_nb = c->d_md_W.as<double>();
     const double* eb = c->d_bond_sum.as<double>();
-    // forces at the starting positions, the kinetic energy and the first
-    // thermostat half step
-    TRY(md_rebuild(c, pos, s, false));
-    TRY(relres_forces(c, pos, F, nullptr, nullptr, s));
-    TRY(enqueue_bonded(c, pos, F, false, nullptr, s));
-    HIP_TRY(launch_md_kinetic(m, s));
-    HIP_TRY(launch_md_scalar(m.st, m.partial, nblk, m.ftm2v, 0, nsteps > 0, nullptr, nullptr,
-                             nullptr, nullptr, s));
+    const double box[3] = {c->box[0], c->box[1], c->box[2]};
     auto row_of = [&](int step) -> double* {
         return thermo_every > 0 && step % thermo_every == 0
                    ? thermo + (size_t)8 * (step / thermo_every - 1) : nullptr;
     };
-    for (int step = 1; step <= nsteps; ++step) {
-        // from the second step on, the drift also does the scalar work after
-        // the previous step (second thermostat half step, its row, first
-        // half step of this one), reading one state buffer, writing the other
-        if (step == 1) {
-            HIP_TRY(launch_md_drift(m, m.st, m.st, 0, 0, nullptr, nullptr, nullptr, nullptr, prec, s));
-        } else {
-            const int next = 1 - c->md_cur;
-            HIP_TRY(launch_md_drift(m, stb + c->md_cur, stb + next, nblk_kick, 1, e_nb, w_nb, eb,
-                                    row_of(step - 1), prec, s));
-            c->md_cur = next;
-            m.st = stb + next;
-        }
-        if (step % c->md_rebuild == 0) TRY(md_rebuild(c, pos, s, true));
+
+    // The run goes from list build to list build without waiting for them: a
+    // build's status is examined when the next one is due (by then it is
+    // there) and once more at the end.  Before each build the positions,
+    // velocities and thermostat state are saved on the device, so when a row
+    // turns out to have overflowed (its forces were short) the run goes back to
+    // that build with grown rows.  A wait at every build left the GPU idle for
+    // about 25 us each time.
+    int mark = 0, mark_cur = c->md_cur;    // step and state buffer of the last build
+    bool first = true;                     // no displacements to check before its status
+    // saves the run's state at step `step` (its drift done) and builds there
+    auto build = [&](int step) -> int {
+        mark = step;
+        mark_cur = c->md_cur;
+        HIP_TRY(launch_md_mark(m, vsave, stb + 2, s));
+        if (c->lanes_stale) return build_checked(c, pos, box, s);
+        return enqueue_build(c, pos, box, s);
+    };
+    // examines the last build and the displacements up to its status;
+    // RELRES_ERR_LIST_RETRY: go back to it
+    auto confirm = [&]() -> int {
+        const int rc = examine_status(c);
+        c->warn_pending = false;           // dynamics checks the displacements itself
+        if (rc != RELRES_OK && rc != RELRES_ERR_LIST_RETRY) return rc;
+        const unsigned seen = c->h_status->md_stale;
+        if (!first && seen != c->md_stale_seen)
+            return fail(RELRES_ERR_STALE_LISTS, "an atom moved more than half the skin between list "
+                        "builds: rebuild more often or use a larger skin");
+        c->md_stale_seen = seen;
+        first = false;
+        return rc;
+    };
+    auto go_back = [&]() -> int {
+        const size_t bytes = sizeof(double) * 3 * (size_t)c->n;
+        HIP_TRY(hipMemcpyAsync(pos, m.xref, bytes, hipMemcpyDeviceToDevice, s));
+        HIP_TRY(hipMemcpyAsync(vel, vsave, bytes, hipMemcpyDeviceToDevice, s));
+        c->md_cur = mark_cur;
+        m.st = stb + mark_cur;
+        HIP_TRY(hipMemcpyAsync(m.st, stb + 2, sizeof(MdState), hipMemcpyDeviceToDevice, s));
+        first = true;
+        return RELRES_OK;
+    };
+    // forces of step `step`, the half kick and the kinetic partials
+    auto finish_step = [&](int step) -> int {
         const bool out = row_of(step) != nullptr;
         TRY(relres_forces(c, pos, F, out ? c->d_md_E.as<double>() : nullptr,
                           out ? c->d_md_W.as<double>() : nullptr, s));
-        // bonded and 1-4 forces, the half kick and the kinetic partials
-        TRY(enqueue_bonded(c, pos, F, out, &m, s));
-    }
-    // the second half step of the last step
-    if (nsteps > 0)
-        HIP_TRY(launch_md_scalar(m.st, m.partial, nblk_kick, m.ftm2v, 1, 0, e_nb, w_nb, eb,
-                                 row_of(nsteps), s));
-    HIP_TRY(launch_md_finish(m, s));
-    // the last steps since the previous build must not have outrun the skin either
-    HIP_TRY(hipMemcpyAsync(c->h_stale, c->d_md_stale.p, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (*c->h_stale)
-        return fail(RELRES_ERR_STALE_LISTS, "an atom moved more than half the skin between list "
-                    "builds: rebuild more often or use a larger skin");
-    return RELRES_OK;
+        return enqueue_bonded(c, pos, F, out, &m, s);
+    };
+    // steps step0 + 1 .. nsteps and the end of the run, the lists being those
+    // of step0's build
+    auto steps_from = [&](int step0) -> int {
+        if (step0 == 0) {
+            // forces at the starting positions, the kinetic energy and the
+            // first thermostat half step
+            TRY(relres_forces(c, pos, F, nullptr, nullptr, s));
+            TRY(enqueue_bonded(c, pos, F, false, nullptr, s));
+            HIP_TRY(launch_md_kinetic(m, s));
+            HIP_TRY(launch_md_scalar(m.st, m.partial, nblk, m.ftm2v, 0, nsteps > 0, nullptr, nullptr,
+                                     nullptr, nullptr, s));
+        } else {
+            TRY(finish_step(step0));
+        }
+        for (int step = step0 + 1; step <= nsteps; ++step) {
+            // from the second step on, the drift also does the scalar work after
+            // the previous step (second thermostat half step, its row, first
+            // half step of this one), reading one state buffer, writing the other
+            if (step == 1) {
+                HIP_TRY(launch_md_drift(m, m.st, m.st, 0, 0, nullptr, nullptr, nullptr, nullptr, prec, s));
+            } else {
+                const int next = 1 - c->md_cur;
+                HIP_TRY(launch_md_drift(m, stb + c->md_cur, stb + next, nblk_kick, 1, e_nb, w_nb, eb,
+                                        row_of(step - 1), prec, s));
+                c->md_cur = next;
+                m.st = stb + next;
+            }
+            if (step % c->md_rebuild == 0) {
+                TRY(confirm());
+                TRY(build(step));
+            }
+            TRY(finish_step(step));
+        }
+        // the second half step of the last step
+        if (nsteps > 0)
+            HIP_TRY(launch_md_scalar(m.st, m.partial, nblk_kick, m.ftm2v, 1, 0, e_nb, w_nb, eb,
+                                     row_of(nsteps), s));
+        HIP_TRY(launch_md_finish(m, s));
+        // the last steps since the previous build must not have outrun the skin either
+        HIP_TRY(hipMemcpyAsync(c->h_status, c->d_status.p, sizeof(Status), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        return confirm();
+    };
+    auto run = [&]() -> int {
+        TRY(drain_check(c));
+        TRY(build(0));
+        int rc = steps_from(0);
+        // rows grow past every length seen, so a build is gone back to once
+        for (int at = -1, tries = 0; rc == RELRES_ERR_LIST_RETRY;) {
+            tries = mark == at ? tries + 1 : 1;
+            if (tries > 4) return fail(RELRES_ERR_LIST_OVERFLOW, "list capacity did not converge");
+            at = mark;
+            TRY(go_back());
+            TRY(build(at));
+            rc = steps_from(at);
+        }
+        return rc;
+    };
+    const int rc = run();
+    if (rc != RELRES_OK) (void)hipStreamSynchronize(s);   // nothing of the run is left behind an error
+    return rc;
 }
 
 int relres_list_stats(relres_ctx* c, relres_stats* out)
@@ -2611,9 +2658,8 @@ void relres_destroy(relres_ctx* c)
     for (DBuf* b : {&c->d_bond_blocks, &c->d_bond_passes, &c->d_bond_terms, &c->d_term_par, &c->d_atom_slot,
                     &c->d_bond_part, &c->d_bond_sum,
                     &c->d_mass, &c->d_md_state, &c->d_md_xref,
-                    &c->d_md_F, &c->d_md_E, &c->d_md_W, &c->d_md_part, &c->d_md_stale})
+                    &c->d_md_F, &c->d_md_E, &c->d_md_W, &c->d_md_part, &c->d_md_vsave})
         release(*b);
-    if (c->h_stale) (void)hipHostFree(c->h_stale);
     for (DBuf* b : {&c->d_coef64, &c->d_coef32, &c->d_hybrid, &c->d_types, &c->d_mol, &c->d_excl_off,
                     &c->d_excl_idx, &c->d_grids, &c->d_wpos, &c->d_key_a, &c->d_key_s,
                     &c->d_user2arow, &c->d_a_rec, &c->d_s_rec, &c->d_status, &c->d_partials, &c->d_seg_tot,

@@ -132,7 +132,8 @@ struct Status {
     unsigned moved_query;           // the same count for relres_moved_atoms
     unsigned pad;
     unsigned ew_failed;             // cumulative count of energy/virial waits that gave up
-    unsigned pad2;
+    unsigned md_stale;              // cumulative count, over dynamics steps, of waves with an
+                                    // atom more than half the skin from the last build
 };
 
 struct ForceArgs {
@@ -334,9 +335,9 @@ struct MdArgs {
     double* vel;                      // N x 3, stored velocities
     const void* forces;               // N x 3 of the force type
     const double* mass;
-    const double* xref;               // positions at the last list build
+    double* xref;                     // positions at the last list build
     double half_skin2;                // (skin / 2)^2
-    unsigned int* stale;              // set when an atom moved more than skin / 2
+    unsigned int* stale;              // Status::md_stale
     double* partial;                  // per block kinetic partial
     MdState* st;
 };
@@ -347,6 +348,9 @@ struct MdArgs {
 hipError_t launch_md_drift(const MdArgs& m, const MdState* st_in, MdState* st_out, int nparts,
                            int scalar, const double* e_nb, const double* w_nb, const double* eb,
                            double* row, int force_prec, hipStream_t s);
+// positions, velocities and thermostat state at a list build: m.xref = pos,
+// vsave = vel, *ssave = *m.st
+hipError_t launch_md_mark(const MdArgs& m, double* vsave, MdState* ssave, hipStream_t s);
 hipError_t launch_md_kinetic(const MdArgs& m, hipStream_t s);
 // kinetic energy from the partials; second / first thermostat half steps;
 // with row, one row of thermodynamic output

@@ -504,8 +504,22 @@ __global__ __launch_bounds__(kMdBlock) void k_md_drift(MdArgs m, const MdState* 
         dmax2 += dx * dx;
     }
     // an atom that moved more than half the skin since the last build
-    // invalidates the lists; the host checks the flag at the next build
-    if (dmax2 > m.half_skin2) atomicOr(m.stale, 1u);
+    // invalidates the lists; the host checks the count with the next build's status
+    const uint64_t far = __ballot(dmax2 > m.half_skin2);
+    if (far != 0ull && ((int)threadIdx.x & 63) == __ffsll((long long)far) - 1) atomicAdd(m.stale, 1u);
+}
+
+// Everything a run needs to go on from a list build: the reference positions
+// of the displacement check, the velocities and the thermostat state.
+__global__ __launch_bounds__(kMdBlock) void k_md_mark(MdArgs m, double* __restrict__ vsave,
+                                                      MdState* __restrict__ ssave)
+{
+    const int i = blockIdx.x * kMdBlock + threadIdx.x;      // one component each
+    if (i < 3 * m.n) {
+        m.xref[i] = m.pos[i];
+        vsave[i] = m.vel[i];
+    }
+    if (i == 0) *ssave = *m.st;
 }
 
 // Kinetic partials of the stored velocities (no kick), at the start of a run.
@@ -587,6 +601,13 @@ hipError_t launch_md_drift(const MdArgs& m, const MdState* st_in, MdState* st_ou
     else
         hipLaunchKernelGGL(k_md_drift<float>, dim3(blocks), dim3(kMdBlock), 0, s, m, st_in,
                            st_out, nparts, scalar, e_nb, w_nb, eb, row);
+    return hipGetLastError();
+}
+
+hipError_t launch_md_mark(const MdArgs& m, double* vsave, MdState* ssave, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_md_mark, dim3((unsigned)((3LL * m.n + kMdBlock - 1) / kMdBlock)),
+                       dim3(kMdBlock), 0, s, m, vsave, ssave);
     return hipGetLastError();
 }
 
