@@ -311,7 +311,16 @@ struct relres_ctx {
     DBuf d_sys;                       // system of each atom (nsys > 1)
     std::vector<double> boxes;        // [nsys][3] of the last build
     std::vector<double> boxes_dev;    // [nsys][6] as uploaded
-    DBuf d_boxes, d_row_ew, d_wave_ew, d_wave_sys;
+    DBuf d_boxes, d_wave_ew;
+    // rows of the force launch's waves with several systems, for every lane
+    // count in use (ForceArgs::waves_tab, sys_wave): [kind][log2 lanes].  A
+    // table is written once for a set of systems, so that a captured launch
+    // keeps the one it was captured with.
+    struct WaveTab {
+        DBuf waves, first;
+        int n = 0;
+        bool valid = false;
+    } wave_tab[2][7];
     int same_mol = 0;
     bool has_excl = false;
     int max_excl = 0;
@@ -345,7 +354,7 @@ struct relres_ctx {
     void* scratch = nullptr;          // this device's static scratch (relres_forces_noalloc)
     hipError_t scratch_err = hipSuccess;
     int lanes_a = 0, lanes_b = 0;        // caller override, 0 = automatic
-    int auto_la = 4, auto_lb = 16;
+    int auto_lanes[2][2] = {{4, 16}, {4, 16}};   // [forces only, with energy/virial][kind]
     // list kernel shape: rows per wave (atom, site grids) and candidates per
     // lane; caller or autotuner override, 0 = automatic
     int rows_a = 0, rows_s = 0, cand = 0;
@@ -518,6 +527,12 @@ int next_pow2_clamped(double x, int lo, int hi)
     int p = 1;
     while (p < x && p < hi) p <<= 1;
     return std::max(lo, std::min(hi, p));
+}
+
+// The power of two nearest to x (by ratio) in [lo, hi].
+int nearest_pow2_clamped(double x, int lo, int hi)
+{
+    return std::max(lo, std::min(hi, x > 1.0 ? 1 << (int)std::lround(std::log2(x)) : 1));
 }
 
 int log2i(int v)
@@ -877,6 +892,49 @@ int upload_grids(relres_ctx* c, hipStream_t s)
     return RELRES_OK;
 }
 
+// Lanes per row of the force launches: kind 0 rows of ordinary atoms, 1 of
+// hybrid ones; ew: with energy or virial.
+int force_lanes(const relres_ctx* c, int kind, bool ew)
+{
+    const int set = kind == 0 ? c->lanes_a : c->lanes_b;
+    return set ? set : c->auto_lanes[ew ? 1 : 0][kind];
+}
+
+// The wave tables of the current lane counts (several systems): a wave takes
+// 64 / lanes consecutive rows of one system.  Called wherever the systems or
+// the lane counts change, so that force calls only pass them on.
+int wave_tables(relres_ctx* c)
+{
+    if (c->nsys == 1) return RELRES_OK;
+    for (int q = 0; q < 4; ++q) {
+        const int kind = q & 1;
+        const std::vector<int>& members = kind == 0 ? c->atoms_sys : c->sites_sys;
+        const int lanes = force_lanes(c, kind, q >= 2), per = 64 / lanes;
+        relres_ctx::WaveTab& t = c->wave_tab[kind][log2i(lanes)];
+        if (t.valid) continue;
+        std::vector<int4> waves;
+        std::vector<int> first;
+        int row = 0;
+        for (int sy = 0; sy < c->nsys; ++sy) {
+            first.push_back((int)waves.size());
+            for (int k = 0; k < members[sy]; k += per)
+                waves.push_back(make_int4(row + k, std::min(per, members[sy] - k), sy, 0));
+            row += members[sy];
+        }
+        first.push_back((int)waves.size());
+        TRY(ensure(t.waves, sizeof(int4) * waves.size(), &c->alloc_generation));
+        TRY(ensure(t.first, sizeof(int) * first.size(), &c->alloc_generation));
+        HIP_TRY(hipDeviceSynchronize());   // tables of earlier systems may still be in use
+        if (!waves.empty())
+            HIP_TRY(hipMemcpy(t.waves.p, waves.data(), sizeof(int4) * waves.size(), hipMemcpyHostToDevice));
+        HIP_TRY(hipMemcpy(t.first.p, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice));
+        t.n = (int)waves.size();
+        t.valid = true;
+        ++c->alloc_generation;             // launches captured with an earlier table are stale
+    }
+    return RELRES_OK;
+}
+
 // Exact entries and longest rows of both lists (one small kernel, then a
 // synchronisation); refreshes the statistics and the automatic lane counts.
 int refresh_list_stats(relres_ctx* c, hipStream_t s)
@@ -893,23 +951,35 @@ int refresh_list_stats(relres_ctx* c, hipStream_t s)
     st.atom_max_row = c->n ? c->h_status->longest[0] : 0;
     st.site_max_row = (c->n && sites) ? c->h_status->longest[1] : 0;
     // Automatic lanes per row: about E list entries per lane.  A launch that
-    // fits the machine a few times over is latency-bound and takes E = 4
-    // (short chains per lane); a much larger one is bound by issue, and its
-    // per-row work (record, reductions across the row's lanes) shrinks with
-    // fewer lanes per row: E = 8, then 16.  Measured on MI355X (force launch):
-    // the 20480-atom liquid (2304 waves at E = 4) is fastest at E = 4; the
-    // 98304-atom copolymer (24576 waves) at E = 8, 38.4 against 45.9 us; the
-    // 256-replica batch (210000 waves) at E = 16, 221 against 342 us.
+    // fits the machine a few times over is latency-bound: E = 4, lanes rounded
+    // up to a power of two (short chains per lane).  A larger one is bound by
+    // issue and by reads in flight, and its per-row work (record, reductions
+    // across the row's lanes) shrinks with fewer lanes: E = 8, the nearest
+    // power of two.  Force launch with energy and virial at E = 4 up / 8
+    // nearest: 20480-atom liquid (2304 waves at E = 4) 9.0 / 9.8 us;
+    // 20480 atoms at 14 A (10240) 18.2 / 15.9; 98304-atom copolymer (12288)
+    // 21.0 / 18.8; 48000-atom hexane (14000) 23.5 / 21.1; 80000 atoms at 14 A
+    // (40000) 57.2 / 47.0; 256 replicas (231000) 264 / 198.  Forces only, the
+    // last takes 146 us with 4 / 16 lanes (E = 4, no sums over the wave)
+    // against 168 with 2 / 8; the others are alike.
     const double avg_a = c->n ? (double)st.atom_entries / c->n : 0.0;
     const double avg_s = c->n_sites ? (double)st.site_entries / c->n_sites : 0.0;
     const long long waves4 =
         ((long long)c->n * next_pow2_clamped(avg_a / 4.0, 1, 32) +
          (long long)c->n_sites * next_pow2_clamped((avg_a + avg_s) / 4.0, 1, 64)) / 64;
-    const double per_lane = waves4 <= 8192 ? 4.0 : (waves4 <= 65536 ? 8.0 : 16.0);
-    c->auto_la = next_pow2_clamped(avg_a / per_lane, 1, 32);
-    c->auto_lb = next_pow2_clamped((avg_a + avg_s) / per_lane, 1, 64);
+    for (int ew = 0; ew < 2; ++ew) {
+        int* lanes = c->auto_lanes[ew];
+        if (waves4 <= 8192) {
+            lanes[0] = next_pow2_clamped(avg_a / 4.0, 1, 32);
+            lanes[1] = next_pow2_clamped((avg_a + avg_s) / 4.0, 1, 64);
+        } else {
+            const double e = !ew && waves4 > 65536 ? 4.0 : 8.0;
+            lanes[0] = nearest_pow2_clamped(avg_a / e, 1, 32);
+            lanes[1] = nearest_pow2_clamped((avg_a + avg_s) / e, 1, 64);
+        }
+    }
     c->stats_fresh = true;
-    return RELRES_OK;
+    return wave_tables(c);
 }
 
 // List builder: groups of rows per wave.  One block per cell remains
@@ -1537,6 +1607,8 @@ int relres_set_systems(relres_ctx* c, int nsys, const int* atom_offsets)
         HIP_TRY(hipMemcpy(c->d_sys.p, sys.data(), sizeof(int) * c->n, hipMemcpyHostToDevice));
     }
     c->nsys = nsys;
+    for (auto& kind : c->wave_tab)
+        for (auto& t : kind) t.valid = false;
     c->skins.clear();                 // every system at the default skin
     c->sys_off = off;
     c->atoms_sys = atoms;
@@ -1635,7 +1707,7 @@ int relres_set_launch(relres_ctx* c, int lanes_atom, int lanes_site)
             return fail(RELRES_ERR_ARG, "lanes per row must be 0 (automatic) or a power of two <= 64");
     c->lanes_a = lanes_atom;
     c->lanes_b = lanes_site;
-    return RELRES_OK;
+    return c->topo_set ? wave_tables(c) : RELRES_OK;
 }
 
 int relres_set_list_launch(relres_ctx* c, int rows_atom, int rows_site, int cand_per_lane)
@@ -1770,8 +1842,8 @@ int relres_autotune(relres_ctx* c, const double* pos, const double* box, void* s
         }
         TRY(relres_set_launch(c, lpick.first, lpick.second));
         out->force_us = best;
-        out->lanes_atom = lpick.first ? lpick.first : c->auto_la;
-        out->lanes_site = lpick.second ? lpick.second : c->auto_lb;
+        out->lanes_atom = lpick.first ? lpick.first : c->auto_lanes[1][0];
+        out->lanes_site = lpick.second ? lpick.second : c->auto_lanes[1][1];
         return RELRES_OK;
     };
     const int saved[7] = {c->rows_a, c->rows_s, c->cand, c->lanes_a, c->lanes_b, c->div_a,
@@ -1801,17 +1873,17 @@ namespace {
 
 // Arguments of one force launch over the lists of the last build, with the
 // lane split of the context; energy/virial buffers are the caller's.
-ForceArgs force_args(const relres_ctx* c, const double* pos, void* forces, double* energy,
-                     double* virial)
+int force_args(relres_ctx* c, const double* pos, void* forces, double* energy, double* virial,
+               ForceArgs& a)
 {
     const bool sites = c->n_sites > 0;
-    const int la = c->lanes_a ? c->lanes_a : c->auto_la;
-    const int lb = c->lanes_b ? c->lanes_b : c->auto_lb;
+    const bool ew = energy || virial;
+    const int la = force_lanes(c, 0, ew), lb = force_lanes(c, 1, ew);
     auto blocks = [](long long rows, int lanes) {
         long long b = (rows * lanes + kForceBlock - 1) / kForceBlock;
         return (int)((b + 7) / 8 * 8);
     };
-    ForceArgs a{};
+    a = ForceArgs{};
     a.pos = pos;
     for (int k = 0; k < 3; ++k) {
         a.box[k] = c->box[k];
@@ -1851,7 +1923,18 @@ ForceArgs force_args(const relres_ctx* c, const double* pos, void* forces, doubl
     const double avg_a = c->n ? (double)c->stats.atom_entries / c->n : 0.0;
     const double avg_s = c->n_sites ? (double)c->stats.site_entries / c->n_sites : 0.0;
     a.wide_batch = c->n > 0 && avg_a >= 8.0 * la && (!sites || avg_a + avg_s >= 8.0 * lb);
-    return a;
+    if (c->nsys > 1) {
+        TRY(wave_tables(c));               // there already, but for a changed override
+        for (int kind = 0; kind < 2; ++kind) {
+            const relres_ctx::WaveTab& t = c->wave_tab[kind][log2i(kind == 0 ? la : lb)];
+            a.waves_tab[kind] = t.waves.as<int4>();
+            a.sys_wave[kind] = t.first.as<int>();
+            a.n_waves[kind] = t.n;
+        }
+        a.blocks_a = blocks(a.n_waves[0], 64);
+        a.blocks_b = sites ? blocks(a.n_waves[1], 64) : 0;
+    }
+    return RELRES_OK;
 }
 
 }  // namespace
@@ -1867,8 +1950,8 @@ int relres_forces(relres_ctx* c, const double* pos, void* forces, double* energy
         return RELRES_OK;
     }
     if (!pos || !forces) return fail(RELRES_ERR_ARG, "pos or forces is NULL");
-    const bool sites = c->n_sites > 0;
-    ForceArgs a = force_args(c, pos, forces, energy, virial);
+    ForceArgs a;
+    TRY(force_args(c, pos, forces, energy, virial, a));
     {
         // energy/virial records: a fresh buffer may hold another context's
         // records, whose tags could match this context's; clear it (tag 0)
@@ -1892,12 +1975,8 @@ int relres_forces(relres_ctx* c, const double* pos, void* forces, double* energy
     const bool ew = energy || virial;
     if (ew && c->nsys > 1) {
         const size_t waves = (size_t)(a.blocks_a + a.blocks_b) * (kForceBlock / 64);
-        TRY(ensure(c->d_row_ew, sizeof(double) * 8 * (size_t)(c->n + c->n_sites), &c->alloc_generation));
         TRY(ensure(c->d_wave_ew, sizeof(double) * 8 * waves, &c->alloc_generation));
-        TRY(ensure(c->d_wave_sys, sizeof(int) * waves, &c->alloc_generation));
-        a.row_ew = c->d_row_ew.as<double>();
         a.wave_ew = c->d_wave_ew.as<double>();
-        a.wave_sys = c->d_wave_sys.as<int>();
     }
     HIP_TRY(launch_forces(a, c->cut64, c->per_pair, c->pair_math, c->precision, ew, s));
     if (timed) {
@@ -1905,7 +1984,7 @@ int relres_forces(relres_ctx* c, const double* pos, void* forces, double* energy
         c->ev_force.push_back({e0, e1});
     }
     if (ew && c->nsys > 1)
-        HIP_TRY(launch_reduce_sys_ew(c->d_grids.as<GridDev>(), sites ? 2 : 1, a, energy, virial, s));
+        HIP_TRY(launch_reduce_sys_ew(a, energy, virial, s));
     return RELRES_OK;
 }
 
@@ -1927,7 +2006,8 @@ int relres_forces_noalloc(relres_ctx* c, const double* pos, void* forces, double
     if (!c->scratch)
         return fail(RELRES_ERR_HIP, "relres_forces_noalloc: no address for the static scratch "
                     "on device %d: %s", c->device, hipGetErrorString(c->scratch_err));
-    ForceArgs a = force_args(c, pos, forces, energy, virial);
+    ForceArgs a;
+    TRY(force_args(c, pos, forces, energy, virial, a));
     const size_t need = kScratchEpochBytes +
                         (size_t)kEwRecBytes * (size_t)(a.blocks_a + a.blocks_b + kEwGroups);
     if (ew && need > kScratchBytes)
@@ -2046,8 +2126,7 @@ int enqueue_backward(relres_ctx* c, const double* pos, const double* grad_forces
     BackArgs b{};
     ForceArgs& a = b.f;
     const bool sites = c->n_sites > 0;
-    const int la = c->lanes_a ? c->lanes_a : c->auto_la;
-    const int lb = c->lanes_b ? c->lanes_b : c->auto_lb;
+    const int la = force_lanes(c, 0, true), lb = force_lanes(c, 1, true);
     auto blocks = [](long long rows, int lanes) {
         long long k = (rows * lanes + kForceBlock - 1) / kForceBlock;
         return (int)((k + 7) / 8 * 8);
@@ -2653,8 +2732,13 @@ void relres_destroy(relres_ctx* c)
 {
     if (!c) return;
     (void)hipDeviceSynchronize();
-    for (DBuf* b : {&c->d_back_tab, &c->d_bpartial, &c->d_sys, &c->d_boxes, &c->d_row_ew, &c->d_wave_ew,
-                    &c->d_wave_sys}) release(*b);
+    for (DBuf* b : {&c->d_back_tab, &c->d_bpartial, &c->d_sys, &c->d_boxes, &c->d_wave_ew})
+        release(*b);
+    for (auto& kind : c->wave_tab)
+        for (auto& t : kind) {
+            release(t.waves);
+            release(t.first);
+        }
     for (DBuf* b : {&c->d_bond_blocks, &c->d_bond_passes, &c->d_bond_terms, &c->d_term_par, &c->d_atom_slot,
                     &c->d_bond_part, &c->d_bond_sum,
                     &c->d_mass, &c->d_md_state, &c->d_md_xref,

@@ -142,11 +142,13 @@ struct ForceArgs {
     double inv_box[3];
     int nsys;
     const double* boxes;      // [nsys][6]: L_x, L_y, L_z, 1/L_x, 1/L_y, 1/L_z
-    double* row_ew;           // nsys > 1: 8 FP64 partials per row (atom rows, then site
-                              // rows), written only by waves across a system boundary
+    // nsys > 1: rows of each wave of the launch, so that no wave holds rows of
+    // two systems: {first row, rows, system, 0} per wave of a kind, and the
+    // first wave of every system (nsys + 1)
+    const int4* waves_tab[2];
+    const int* sys_wave[2];
+    int n_waves[2];
     double* wave_ew;          // nsys > 1: 8 FP64 sums per wave (atom waves, then site waves)
-    int* wave_sys;            // ... and the wave's system; -1: across a boundary (rows in
-                              // row_ew), -2: no rows of its own
     // atom list rows (all atoms, atom-grid order); record = (caller index,
     // type + 32 system, stored entries, 1 if hybrid)
     int n_arow;
@@ -257,10 +259,8 @@ constexpr size_t kScratchBytes = RELRES_NOALLOC_SCRATCH_BYTES;
 constexpr size_t kScratchEpochBytes = 256;
 hipError_t scratch_address(void** out);
 hipError_t launch_zero_outputs(double* energy, double* virial, int nsys, hipStream_t s);
-// nsys > 1: energy/virial of each system from the wave sums (and the row
-// partials of waves across a system boundary)
-hipError_t launch_reduce_sys_ew(const GridDev* grids_dev, int ngrids, const ForceArgs& a,
-                                double* energy, double* virial, hipStream_t s);
+// nsys > 1: energy/virial of each system from the wave sums
+hipError_t launch_reduce_sys_ew(const ForceArgs& a, double* energy, double* virial, hipStream_t s);
 
 // Bonded terms and scaled 1-4 pairs (relres_md.hip).  One term as a block of
 // the bonded kernel evaluates it: its atoms in the term's order (a bond uses

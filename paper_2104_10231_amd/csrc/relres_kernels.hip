@@ -1314,10 +1314,28 @@ constexpr int kBatchWide = 4;
 
 constexpr uint32_t kNoEntry = 0xffffffffu;
 
-// Periodic box of the system a row belongs to: edges and their reciprocals.
+// Periodic box of a system: edges and their reciprocals.
 struct BoxV {
     double L[3], iL[3];
 };
+
+// The box of a wave whose rows all belong to system `sys`, in scalar registers.
+__device__ __forceinline__ BoxV wave_box(const ForceArgs& a, int sys)
+{
+    BoxV b;
+    if (a.nsys == 1) {
+        for (int k = 0; k < 3; ++k) {
+            b.L[k] = a.box[k];
+            b.iL[k] = a.inv_box[k];
+        }
+    } else {
+        for (int k = 0; k < 3; ++k) {
+            b.L[k] = readfirst_d(a.boxes[6 * sys + k]);
+            b.iL[k] = readfirst_d(a.boxes[6 * sys + 3 + k]);
+        }
+    }
+    return b;
+}
 
 __device__ __forceinline__ BoxV row_box(const ForceArgs& a, int sys)
 {
@@ -1641,9 +1659,16 @@ __device__ void ew_finish(const ForceArgs& a, const double acc[8], unsigned tag)
     }
 }
 
+// The rows of a wave belong to one system (with several systems a table says
+// which), so the box stays in scalar registers; a box per lane held 12 vector
+// registers.  At least 6 waves per SIMD: the launches of large systems wait
+// for their list entries and gathers, and 80 registers against 87 (5 waves)
+// took the energy/virial launch of 256 replicas from 214.6 to 203.0 us, of the
+// 98304-atom copolymer from 22.1 to 19.3, of 80000 atoms at 14 A from 62.5 to
+// 58.9 (72 and 64 registers spill: no faster, and 30 to 70 % slower).
 template <typename S, typename TF, bool EW, bool LDS, bool PC, int B>
-__global__ __launch_bounds__(kForceBlock) void k_forces(ForceArgs a, Cutoffs<S> cut,
-                                                       Cutoffs<double> cut64)
+__global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces(
+    ForceArgs a, Cutoffs<S> cut, Cutoffs<double> cut64)
 {
     const bool rb = (int)blockIdx.x >= a.blocks_a;
     const int lb = rb ? (int)blockIdx.x - a.blocks_a : (int)blockIdx.x;
@@ -1654,8 +1679,22 @@ __global__ __launch_bounds__(kForceBlock) void k_forces(ForceArgs a, Cutoffs<S> 
     const int logical = (lb & 7) * per + (lb >> 3);
     const int lg = rb ? a.log_lanes_b : a.log_lanes_a;
     const int G = 1 << lg;
-    const int row = logical * (kForceBlock >> lg) + ((int)threadIdx.x >> lg);
     const int sub = (int)threadIdx.x & (G - 1);
+    // wave of this kind, and its rows
+    const int lw = __builtin_amdgcn_readfirstlane(logical * (kForceBlock / kWave) +
+                                                  (int)threadIdx.x / kWave);
+    int row = ((int)threadIdx.x & (kWave - 1)) >> lg, rows = kWave >> lg, sys = 0;
+    if (a.nsys == 1) {
+        rows = min(rows, (rb ? a.n_srow : a.n_arow) - (lw << (6 - lg)));
+    } else {
+        int4 w = make_int4(0, 0, 0, 0);
+        if (lw < a.n_waves[rb ? 1 : 0]) w = a.waves_tab[rb ? 1 : 0][lw];
+        rows = w.y;
+        sys = __builtin_amdgcn_readfirstlane(w.z);
+        row += w.x;
+    }
+    const bool live = ((int)threadIdx.x & (kWave - 1)) >> lg < rows;
+    if (a.nsys == 1) row += lw << (6 - lg);
 
     // the first words of the LDS tables are read before the row record, so
     // the two reads overlap (written to LDS once the record is in)
@@ -1689,7 +1728,6 @@ __global__ __launch_bounds__(kForceBlock) void k_forces(ForceArgs a, Cutoffs<S> 
     // first entries are loaded together with the record.  Slots past the row's
     // count read the row's padding (in bounds) and are dropped once the count
     // is known.
-    const bool live = rb ? row < a.n_srow : row < a.n_arow;
     const int* own_list = rb ? a.s_list + (size_t)row * a.s_cap : a.a_list + (size_t)row * a.a_cap;
     const int own_cap = rb ? a.s_cap : a.a_cap;
     uint32_t e_own[B];
@@ -1771,9 +1809,9 @@ __global__ __launch_bounds__(kForceBlock) void k_forces(ForceArgs a, Cutoffs<S> 
         double fxp[B], fyp[B], fzp[B], sxp[B], syp[B], szp[B];
         gather_batch<B>(a, e_fg, fxp, fyp, fzp);
         if (rb) gather_batch<B>(a, e_own, sxp, syp, szp);
-        // the row's box (several systems: a read) after the gathers, so the
-        // wave does not wait for it before issuing them
-        const BoxV bx = row_box(a, rec.y >> kTypeBits);
+        // the box (several systems: a read) after the gathers, so the wave does
+        // not wait for it before issuing them
+        const BoxV bx = wave_box(a, sys);
         const int ro = ti * a.ntypes;
         const RowTab<S> rt{coef + ro, coef64 + ro, PC ? pcut + ro : nullptr,
                            PC ? pcut64 + ro : nullptr};
@@ -1811,34 +1849,12 @@ __global__ __launch_bounds__(kForceBlock) void k_forces(ForceArgs a, Cutoffs<S> 
         if (a.nsys == 1) {
             ew_finish(a, acc, tag);
         } else {
-            // several systems (rows are grouped by system): a wave whose own
-            // rows all belong to one system adds its lanes and writes one
-            // record; a wave across a system boundary (rare) writes every
-            // row's partials.  A second kernel adds each system's records.
+            // several systems: a wave's rows belong to one of them, and it
+            // writes their sums; a second kernel adds each system's waves
             const int lane = (int)threadIdx.x & (kWave - 1);
-            const size_t wrec = (rb ? (size_t)a.blocks_a * (kForceBlock / kWave) : 0) +
-                                (size_t)logical * (kForceBlock / kWave) + (threadIdx.x / kWave);
-            const int sys_row = own ? (rec.y >> kTypeBits) : -1;
-            const uint64_t own_mask = __ballot(own);
-            if (own_mask == 0ull) {
-                if (lane == 0) a.wave_sys[wrec] = -2;
-            } else {
-                const int s0 = __builtin_amdgcn_readlane(sys_row, __ffsll((long long)own_mask) - 1);
-                if (__ballot(own && sys_row != s0) == 0ull) {
-                    const double ws = wave_sum8(acc);
-                    if (lane < 8) a.wave_ew[8 * wrec + wave_sum8_lane(lane)] = ws;
-                    if (lane == 0) a.wave_sys[wrec] = s0;
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) acc[k] = group_sum(acc[k], G);
-                    if (live && sub == 0) {
-                        double* out = a.row_ew + 8 * (size_t)(rb ? a.n_arow + row : row);
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) out[k] = own ? acc[k] : 0.0;
-                    }
-                    if (lane == 0) a.wave_sys[wrec] = -1;
-                }
-            }
+            const size_t wrec = (rb ? (size_t)a.blocks_a * (kForceBlock / kWave) : 0) + (size_t)lw;
+            const double ws = wave_sum8(acc);
+            if (lane < 8) a.wave_ew[8 * wrec + wave_sum8_lane(lane)] = ws;
         }
     }
 }
@@ -1852,94 +1868,41 @@ __global__ void k_zero_outputs(double* energy, double* virial, int nsys)
     }
 }
 
-// Energy and virial of every system (one block per system) from the per-row
-// partials of the force kernel: the system's atom-list rows, then its
-// site-list rows, each thread in row order, then a fixed-order block sum.
-// One block per system: the records of the waves that hold its rows (wave
-// w of a kind holds rows w * rpw .. w * rpw + rpw - 1 of that kind, rpw =
-// 64 / lanes per row), and for a wave across a system boundary the partials
-// of its rows in this system; fixed order, so results are deterministic.
+// Energy and virial of every system (one block per system): the sums of the
+// system's atom waves, then of its site waves, each thread in wave order, then
+// a fixed-order block sum, so results are deterministic.  kSysLoads waves per
+// thread per round are requested before any is added.
 constexpr int kSysLoads = 4;
 
-__global__ __launch_bounds__(256) void k_reduce_sys_ew(const GridDev* __restrict__ grids,
-                                                       int ngrids, ForceArgs a,
-                                                       double* __restrict__ energy,
+__global__ __launch_bounds__(256) void k_reduce_sys_ew(ForceArgs a, double* __restrict__ energy,
                                                        double* __restrict__ virial)
 {
     __shared__ double red[8][4];
     const int sy = (int)blockIdx.x;
     double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    // the system's waves of both kinds (atom rows, then site rows) as one
-    // range: both kinds' row ranges are read first, then kSysLoads waves per
-    // thread per round have their system tags and records requested before
-    // any is used (a record is read whatever its tag says); the waves whose
-    // rows are all this system's (tag sy) are added here
-    // (the grid array always has two entries, so both kinds' ranges are read
-    // unconditionally, as scalar loads all in flight together)
-    int w0[2] = {0, 0}, nw[2] = {0, 0}, rpw[2] = {1, 1}, r0[2] = {0, 0}, r1[2] = {0, 0};
-    {
-        RELRES_GLOBAL const GridDev* gg = gbl(grids);
-        RELRES_GLOBAL const GeomDev* ge0 = gbl(gg[0].geom);
-        RELRES_GLOBAL const GeomDev* ge1 = gbl(gg[1].geom);
-        const int base[2] = {ge0[sy].row_base, ge1[sy].row_base};
-        const int mem[2] = {ge0[sy].members, ngrids > 1 ? ge1[sy].members : 0};
-#pragma unroll
-        for (int kind = 0; kind < 2; ++kind) {
-            rpw[kind] = kWave >> (kind ? a.log_lanes_b : a.log_lanes_a);
-            r0[kind] = base[kind];
-            r1[kind] = base[kind] + mem[kind];
-            w0[kind] = r0[kind] / rpw[kind];
-            nw[kind] = mem[kind] > 0 ? (r1[kind] - 1) / rpw[kind] - w0[kind] + 1 : 0;
-        }
+    const int wa = a.sys_wave[0][sy], na = a.sys_wave[0][sy + 1] - wa;
+    int ws = 0, ns = 0;
+    if (a.n_srow > 0) {
+        ws = a.sys_wave[1][sy];
+        ns = a.sys_wave[1][sy + 1] - ws;
     }
-    const size_t woff1 = (size_t)a.blocks_a * (kForceBlock / kWave);
-    const int total = nw[0] + nw[1];
+    const size_t woff1 = (size_t)a.blocks_a * (kForceBlock / kWave) + (size_t)ws;
+    const int total = na + ns;
     for (int jb = (int)threadIdx.x; jb < total; jb += 256 * kSysLoads) {
-        int ws[kSysLoads];
         double4 q[kSysLoads][2];
 #pragma unroll
         for (int u = 0; u < kSysLoads; ++u) {
             const int j = min(jb + 256 * u, total - 1);
-            const size_t wg = j < nw[0] ? (size_t)(w0[0] + j) : woff1 + (size_t)(w0[1] + j - nw[0]);
+            const size_t wg = j < na ? (size_t)(wa + j) : woff1 + (size_t)(j - na);
             const double4* p = reinterpret_cast<const double4*>(a.wave_ew + 8 * wg);
-            ws[u] = jb + 256 * u < total ? a.wave_sys[wg] : -2;
             q[u][0] = p[0];
             q[u][1] = p[1];
         }
 #pragma unroll
         for (int u = 0; u < kSysLoads; ++u) {
-            if (ws[u] == sy) {
+            if (jb + 256 * u < total) {
                 v[0] += q[u][0].x; v[1] += q[u][0].y; v[2] += q[u][0].z; v[3] += q[u][0].w;
                 v[4] += q[u][1].x; v[5] += q[u][1].y; v[6] += q[u][1].z; v[7] += q[u][1].w;
-            }
-        }
-    }
-    // A wave across a system boundary (tag -1) left partials per row; only
-    // the first or the last wave of a kind's range can be one.  Their rows of
-    // this system, one row per thread, all four waves' loads issued together.
-    {
-        int wsb[4];
-        bool use[4];
-        double4 qb[4][2];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int kind = q >> 1, e = q & 1;
-            const bool any = nw[kind] > 0 && (e == 0 || nw[kind] > 1);
-            const int w = e == 0 ? w0[kind] : w0[kind] + nw[kind] - 1;
-            const int lo = max(w * rpw[kind], r0[kind]), hi = min((w + 1) * rpw[kind], r1[kind]);
-            const int r = lo + (int)threadIdx.x;
-            use[q] = any && r < hi;
-            wsb[q] = any ? a.wave_sys[(kind ? woff1 : 0) + (size_t)w] : -2;
-            const size_t ri = any ? (kind ? (size_t)a.n_arow : 0) + (size_t)(use[q] ? r : lo) : 0;
-            const double4* p = reinterpret_cast<const double4*>(a.row_ew + 8 * ri);
-            qb[q][0] = p[0];
-            qb[q][1] = p[1];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (use[q] && wsb[q] == -1) {
-                v[0] += qb[q][0].x; v[1] += qb[q][0].y; v[2] += qb[q][0].z; v[3] += qb[q][0].w;
-                v[4] += qb[q][1].x; v[5] += qb[q][1].y; v[6] += qb[q][1].z; v[7] += qb[q][1].w;
             }
         }
     }
@@ -2562,11 +2525,9 @@ hipError_t launch_zero_outputs(double* energy, double* virial, int nsys, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_sys_ew(const GridDev* grids_dev, int ngrids, const ForceArgs& a,
-                                double* energy, double* virial, hipStream_t s)
+hipError_t launch_reduce_sys_ew(const ForceArgs& a, double* energy, double* virial, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_reduce_sys_ew, dim3(a.nsys), dim3(256), 0, s, grids_dev, ngrids, a,
-                       energy, virial);
+    hipLaunchKernelGGL(k_reduce_sys_ew, dim3(a.nsys), dim3(256), 0, s, a, energy, virial);
     return hipGetLastError();
 }
 
