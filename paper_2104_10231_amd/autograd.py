@@ -52,7 +52,10 @@ class _RelResFunction(torch.autograd.Function):
         _install(rr, ctx.params)
         (pos,) = ctx.saved_tensors
         gpos, gtype = rr.backward_types(pos, grad_forces, grad_energy)
-        grads = tuple(gtype[k].to(ctx.devices[k]) for k in range(4))
+        # one copy for the parameters on the host, not one (and a wait) each
+        host = gtype.cpu() if any(d.type == "cpu" for d in ctx.devices) else None
+        grads = tuple(host[k].clone() if d.type == "cpu" else gtype[k].to(d)
+                      for k, d in enumerate(ctx.devices))
         return (None, gpos) + grads
 
 

@@ -178,9 +178,12 @@ def _ptr(a) -> Optional[int]:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    """The handle of a stream, by default the current one of the current
+    device, read without building a torch.cuda.Stream object: that takes
+    2.6 us, a third of a force call's time on the host."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dp(a: np.ndarray):
@@ -290,9 +293,9 @@ class RelRes:
 
     # -- hot path ------------------------------------------------------------
     def _pos(self, pos: torch.Tensor) -> torch.Tensor:
-        if pos.dtype != torch.float64 or pos.device.type != "cuda" or not pos.is_contiguous():
+        if pos.dtype != torch.float64 or not pos.is_cuda or not pos.is_contiguous():
             raise TypeError("pos must be a contiguous float64 CUDA tensor of shape (N, 3)")
-        if tuple(pos.shape) != (self.n, 3):
+        if pos.shape != (self.n, 3):
             raise ValueError(f"pos has shape {tuple(pos.shape)}, expected ({self.n}, 3)")
         return pos
 
@@ -349,7 +352,7 @@ class RelRes:
         dt = torch.float64 if self.precision == 64 else torch.float32
         if out is None:
             out = torch.empty((self.n, 3), dtype=dt, device=pos.device)
-        elif out.dtype != dt or tuple(out.shape) != (self.n, 3) or not out.is_contiguous():
+        elif out.dtype != dt or out.shape != (self.n, 3) or not out.is_contiguous():
             raise TypeError("out must be a contiguous (N, 3) tensor of the force dtype")
         eshape = (3,) if self.nsys == 1 else (self.nsys, 3)
         wshape = (6,) if self.nsys == 1 else (self.nsys, 6)
