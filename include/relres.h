@@ -141,12 +141,14 @@ typedef struct relres_stats {
                                              more than half the skin from their
                                              previous-build positions          */
     int place_launches;                   /* launches that put the members of the
-                                             last build into cell order: 1 (grids
-                                             of at most 8192 cells, not crowded:
-                                             per-cell buckets filled while binning,
-                                             then one scan-and-sort launch) or 3
-                                             (scan, scatter, cell sort); 0 before
-                                             any build of a non-empty system    */
+                                             last build into cell order: 1 (cells not
+                                             crowded: per-cell buckets filled while
+                                             binning, then one scan-and-sort launch),
+                                             2 (the same for more than 8192 cells that
+                                             hold a member on average: the counts of
+                                             cell ranges summed first) or 3 (scan,
+                                             scatter, cell sort); 0 before any build
+                                             of a non-empty system              */
 } relres_stats;
 
 /* Create a context.  Validates the cutoff ordering r_s- <= r_s+ <= r_c- <=

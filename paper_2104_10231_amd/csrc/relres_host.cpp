@@ -716,14 +716,14 @@ int setup_grid(GridHost& g, const std::vector<double>& rl_sys, const std::vector
         TRY(ensure(g.rank_of_lin, sizeof(int) * total, gen));
         TRY(ensure(g.lin_of_rank, sizeof(int) * total, gen));
         TRY(ensure(g.cell_sys, sizeof(int) * total, gen));
-        TRY(ensure(g.count, sizeof(int) * total, gen));
+        TRY(ensure(g.count, sizeof(int) * 2 * (size_t)total, gen));   // counts, chain heads
         TRY(ensure(g.start, sizeof(int) * (total + 1), gen));
         if (!nbr.empty())
             HIP_TRY(hipMemcpy(g.nbr.p, nbr.data(), sizeof(int) * nbr.size(), hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(g.rank_of_lin.p, rank_of_lin.data(), sizeof(int) * total, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(g.lin_of_rank.p, lin_of_rank.data(), sizeof(int) * total, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(g.cell_sys.p, cell_sys.data(), sizeof(int) * total, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemset(g.count.p, 0, sizeof(int) * total));
+        HIP_TRY(hipMemset(g.count.p, 0, sizeof(int) * 2 * (size_t)total));
         g.nsys = nsys;
         g.sys_n = nn;
         g.div = div;
@@ -1049,17 +1049,21 @@ int enqueue_build(relres_ctx* c, const double* pos, const double* box, hipStream
                        c->div_s ? c->div_s : 1, &c->alloc_generation));
     if (c->ga.ncell + (sites ? c->gs.ncell : 0) != dims_before) c->lanes_stale = true;
     bool one_launch = false;
+    // Buckets for many cells only where these hold a member on average: the
+    // buckets of a sparse box would take more memory than its atoms, and most
+    // of the placement's lanes would find nothing.
+    const int cells = c->ga.ncell + (sites ? c->gs.ncell : 0);
+    const bool filled = (long long)c->n + (sites ? c->n_sites : 0) >= cells;
     TRY(set_buckets(c, c->ga, sites ? &c->gs : nullptr,
-                    c->place_one_launch && c->ga.ncell + (sites ? c->gs.ncell : 0) <= kPlaceMaxCells,
-                    &one_launch));
+                    c->place_one_launch && (cells <= kPlaceMaxCells || filled), &one_launch));
     const void* wpos_before = c->d_wpos.p;
     TRY(ensure(c->d_wpos, sizeof(double4) * c->n, &c->alloc_generation));
     const bool check_moved = c->ref_valid && same_boxes && c->d_wpos.p == wpos_before;
     TRY(ensure(c->d_key_a, sizeof(int2) * c->n, &c->alloc_generation));
     TRY(ensure(c->d_key_s, sizeof(int2) * c->n, &c->alloc_generation));
     TRY(ensure(c->d_user2arow, sizeof(int) * c->n, &c->alloc_generation));
-    TRY(ensure(c->d_seg_tot, sizeof(int) * (size_t)(scan_segments(c->ga.ncell) +
-                                                   (sites ? scan_segments(c->gs.ncell) : 0) + 1),
+    TRY(ensure(c->d_seg_tot, sizeof(int) * (size_t)(place_segments(c->ga.ncell) +
+                                                   (sites ? place_segments(c->gs.ncell) : 0) + 1),
                &c->alloc_generation));
     TRY(ensure(c->d_a_rec, sizeof(int4) * std::max(1, c->n), &c->alloc_generation));
     TRY(ensure(c->d_s_rec, sizeof(int4) * std::max(1, c->n_sites), &c->alloc_generation));
@@ -1086,7 +1090,7 @@ int enqueue_build(relres_ctx* c, const double* pos, const double* box, hipStream
         if (one_launch) {
             HIP_TRY(launch_place(gd, c->ga.ncell, ncs, members, c->n, c->d_key_a.as<int2>(),
                                  c->d_key_s.as<int2>(), c->d_wpos.as<double4>(), topo,
-                                 c->d_user2arow.as<int>(), s));
+                                 c->d_user2arow.as<int>(), c->d_seg_tot.as<int>(), s));
         } else {
             HIP_TRY(launch_scan(gd, sites ? 2 : 1, c->ga.ncell, ncs, c->d_seg_tot.as<int>(), s));
             HIP_TRY(launch_scatter(c->n, gd, c->d_key_a.as<int2>(), c->d_key_s.as<int2>(), s));
@@ -1116,7 +1120,8 @@ int enqueue_build(relres_ctx* c, const double* pos, const double* box, hipStream
     relres_stats& st = c->stats;
     st.n_atoms = c->n;
     st.n_sites = c->n_sites;
-    if (c->n > 0) st.place_launches = one_launch ? 1 : 3;
+    if (c->n > 0)
+        st.place_launches = one_launch ? (cells > kPlaceMaxCells ? 2 : 1) : 3;
     for (int k = 0; k < 3; ++k) {
         st.atom_cells[k] = c->ga.n[k];
         st.site_cells[k] = sites ? c->gs.n[k] : 0;

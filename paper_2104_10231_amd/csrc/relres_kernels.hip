@@ -179,6 +179,22 @@ __device__ __forceinline__ int claim_slots(RELRES_GLOBAL int* count, int r, cons
     return got;
 }
 
+// One-launch placement: member i goes straight into its cell's bucket; one that
+// finds it full goes to the head of the cell's chain (count[ncell + cell] is its
+// last member), and the member before it is returned as its key's second word
+// (the first of a chain gets the head of an earlier build: a chain is followed
+// for as many members as the cell's count says).  Otherwise that word is the slot.
+__device__ __forceinline__ int file_member(const GridDev& g, int cell, int slot, int i)
+{
+    if (g.bucket_cap <= 0) return slot;
+    if (slot < g.bucket_cap) {
+        gbl(g.user_unsorted)[(size_t)cell * g.bucket_cap + slot] = i;
+        return slot;
+    }
+    return __hip_atomic_exchange(gbl(g.count) + g.ncell + cell, i, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ int lin_cell(const double w[3], const double inv[3], const int n[3])
 {
     return (cell_coord(w[0], inv[0], n[0]) * n[1] + cell_coord(w[1], inv[1], n[1])) * n[2] +
@@ -245,12 +261,8 @@ __global__ __launch_bounds__(256) void k_bin(int n, const double* __restrict__ p
     if (in) wpos[i] = make_double4(w[0], w[1], w[2], 0.0);
     const int slot = __shfl(got_a, qa.lead) + qa.rank, slot_s = __shfl(got_s, qs.lead) + qs.rank;
     if (in) {
-        key_a[i] = make_int2(r, slot);
-        key_s[i] = hyb ? make_int2(rs, slot_s) : make_int2(-1, -1);
-        // one-launch placement: the member goes straight into its cell's bucket
-        if (slot < ga.bucket_cap) gbl(ga.user_unsorted)[(size_t)r * ga.bucket_cap + slot] = i;
-        if (hyb && slot_s < gs.bucket_cap)
-            gbl(gs.user_unsorted)[(size_t)rs * gs.bucket_cap + slot_s] = i;
+        key_a[i] = make_int2(r, file_member(ga, r, slot, i));
+        key_s[i] = hyb ? make_int2(rs, file_member(gs, rs, slot_s, i)) : make_int2(-1, -1);
     }
 }
 
@@ -527,20 +539,54 @@ __global__ void k_cellsort(const GridDev* __restrict__ grids, int ncell_a, int n
 }
 
 
-// Scan, scatter and cell sort in one launch, for grids of few cells whose
-// members k_bin has filed into per-cell buckets of bucket_cap slots.  A block
+// Scan, scatter and cell sort in one launch, for grids whose members k_bin has filed into per-cell buckets of bucket_cap slots.  A block
 // takes kCells consecutive cells of one grid (the atom grid's blocks first):
 // it adds up the counts of every cell before its own (each block repeats
-// this, so it suits a few thousand cells), writes its cells' starts, then
+// this, so it suits a few thousand cells; larger grids have k_place_totals
+// run first), writes its cells' starts, then
 // ranks each cell's members by caller index as k_cellsort does and writes
-// the sorted arrays.  A cell with more members than its bucket holds finds
-// them, already in caller order, by a wave-wide pass over the key array.
+// the sorted arrays.  A cell with more members than its bucket holds finds the
+// others in its chain, or, when they are many, all of them, already in caller
+// order, by a wave-wide pass over the key array.
 // The counts stay as they are: the list kernel clears them.
 constexpr int kPlaceThreads = 256;
 
+// Grids of many cells: the members of every kPlaceSeg consecutive cells, one
+// block each (blocks 0 .. nseg_a - 1 the atom grid's, the rest the site
+// grid's), so that a block of k_place adds up segments and the counts of part
+// of its own segment instead of every count before its cells.
+__global__ __launch_bounds__(kPlaceThreads) void k_place_totals(const GridDev* __restrict__ grids,
+                                                                int nseg_a, int* __restrict__ seg_tot)
+{
+    __shared__ int wtot[kPlaceThreads / kWave];
+    const int b = (int)blockIdx.x;
+    const GridDev& g = grids[b >= nseg_a ? 1 : 0];
+    const int seg = (b >= nseg_a ? b - nseg_a : b) * kPlaceSeg, nc = g.ncell;
+    RELRES_GLOBAL const int* gcount = gbl(g.count);
+    int s = 0;
+#pragma unroll
+    for (int u = 0; u < kPlaceSeg / kPlaceThreads; ++u) {
+        const int c = seg + u * kPlaceThreads + (int)threadIdx.x;
+        const int v = gcount[min(c, nc - 1)];
+        s += c < nc ? v : 0;
+    }
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & (kWave - 1)) == 0) wtot[threadIdx.x / kWave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+#pragma unroll
+        for (int k = 0; k < kPlaceThreads / kWave; ++k) t += wtot[k];
+        seg_tot[b] = t;
+    }
+}
+
 template <int kSortGroup>
 __global__ __launch_bounds__(kPlaceThreads) void k_place(const GridDev* __restrict__ grids,
-                                                         int blocks_a, int n,
+                                                         int blocks_a,
+                                                         const int* __restrict__ seg_tot,
+                                                         int nseg_a, int n,
                                                          const int2* __restrict__ key_a,
                                                          const int2* __restrict__ key_s,
                                                          const double4* __restrict__ wpos,
@@ -578,11 +624,18 @@ __global__ __launch_bounds__(kPlaceThreads) void k_place(const GridDev* __restri
     // above; grids of more than 4096 cells before the block loop further)
     // (global 16-byte reads of clamped index, the ones past the end dropped,
     // so no branch splits them)
+    // (with segment totals the counts start at the block's own segment, and
+    // the earlier segments' totals are added)
     int s = 0;
-    const int n4 = c0 >> 2;
+    const int seg = seg_tot ? c0 / kPlaceSeg : 0;
+    if (seg > 0) {
+        const int* __restrict__ tot = seg_tot + (site ? nseg_a : 0);
+        for (int k = (int)threadIdx.x; k < seg; k += kPlaceThreads) s += tot[k];
+    }
+    const int n4 = (c0 - seg * kPlaceSeg) >> 2;
     if (n4 > 0) {
         typedef int int4v __attribute__((ext_vector_type(4)));
-        RELRES_GLOBAL const int4v* c4 = (RELRES_GLOBAL const int4v*)gcount;
+        RELRES_GLOBAL const int4v* c4 = (RELRES_GLOBAL const int4v*)(gcount + seg * kPlaceSeg);
         auto round = [&](int base) {
             int4v q4[4];
 #pragma unroll
@@ -654,8 +707,31 @@ __global__ __launch_bounds__(kPlaceThreads) void k_place(const GridDev* __restri
             if (lane < lenk) place_member(g, site, ck, bk + rk, v, wpos, topo, user2arow);
             continue;
         }
-        // the cell outgrew its bucket: its members in caller order from the keys
         const int2* __restrict__ key = site ? key_s : key_a;
+        const int over = lenk - cap;
+        if (over <= kWave && (long long)over * kWave <= n) {
+            // the cell outgrew its bucket: the members beyond it from its
+            // chain, one dependent read each, where that is fewer than the
+            // rounds of the pass below
+            const int v = lane < cap ? bucket[(size_t)ck * cap + lane] : 0x7fffffff;
+            int w = 0x7fffffff;
+            int j = __builtin_amdgcn_readfirstlane(gcount[nc + ck]);
+            for (int t = 0; t < over && (unsigned)j < (unsigned)n; ++t) {
+                if (lane == t) w = j;
+                if (t + 1 < over) j = __builtin_amdgcn_readfirstlane(key[j].y);
+            }
+            int rv = 0, rw = 0;
+            for (int t = 0; t < lenk; ++t) {
+                const int u_t = t < cap ? readlane_i(v, t) : readlane_i(w, t - cap);
+                rv += u_t < v;
+                rw += u_t < w;
+            }
+            if (lane < cap) place_member(g, site, ck, bk + rv, v, wpos, topo, user2arow);
+            if (lane < over && w != 0x7fffffff)
+                place_member(g, site, ck, bk + rw, w, wpos, topo, user2arow);
+            continue;
+        }
+        // far more members than the bucket holds: in caller order from the keys
         int run = 0;
         for (int i0 = 0; i0 < n; i0 += kWave) {
             const int i = i0 + lane;
@@ -2053,21 +2129,32 @@ hipError_t launch_cellsort(GridDev* grids_dev, int ncell_a, int ncell_total, lon
     return hipGetLastError();
 }
 
+int place_segments(int ncell) { return (ncell + kPlaceSeg - 1) / kPlaceSeg; }
+
 hipError_t launch_place(GridDev* grids_dev, int ncell_a, int ncell_s, long long members, int n,
                         const int2* key_a, const int2* key_s, const double4* wpos, TopoDev topo,
-                        int* user2arow, hipStream_t s)
+                        int* user2arow, int* seg_tot, hipStream_t s)
 {
     // a few members per cell (mean below 8): 4 cells per wave, as k_cellsort
     const bool small = members < 8LL * (ncell_a + ncell_s);
     const int cells = (kPlaceThreads / kWave) * (small ? 4 : 1);
     const int blocks_a = (ncell_a + cells - 1) / cells, blocks_s = (ncell_s + cells - 1) / cells;
     if (blocks_a + blocks_s == 0) return hipSuccess;
+    const int nseg_a = place_segments(ncell_a);
+    if (ncell_a + ncell_s > kPlaceMaxCells) {
+        hipLaunchKernelGGL(k_place_totals, dim3(nseg_a + place_segments(ncell_s)),
+                           dim3(kPlaceThreads), 0, s, grids_dev, nseg_a, seg_tot);
+    } else {
+        seg_tot = nullptr;
+    }
     if (small)
         hipLaunchKernelGGL(k_place<16>, dim3(blocks_a + blocks_s), dim3(kPlaceThreads), 0, s,
-                           grids_dev, blocks_a, n, key_a, key_s, wpos, topo, user2arow);
+                           grids_dev, blocks_a, seg_tot, nseg_a, n, key_a, key_s, wpos, topo,
+                           user2arow);
     else
         hipLaunchKernelGGL(k_place<64>, dim3(blocks_a + blocks_s), dim3(kPlaceThreads), 0, s,
-                           grids_dev, blocks_a, n, key_a, key_s, wpos, topo, user2arow);
+                           grids_dev, blocks_a, seg_tot, nseg_a, n, key_a, key_s, wpos, topo,
+                           user2arow);
     return hipGetLastError();
 }
 
