@@ -371,13 +371,14 @@ struct relres_ctx {
     DBuf d_bond_blocks, d_bond_passes, d_bond_terms, d_term_par, d_atom_slot, d_bond_part,
         d_bond_sum;
     int bond_nblocks = 0;             // blocks of the bonded kernel
+    bool bond_closed = false;          // no term crosses a bonded block
     int bond_max_atoms = 0, bond_max_slots = 0;
     // dynamics (relres_md_setup / relres_md_run)
     bool md_ready = false;
     double md_ftm2v = 0.0;
     int md_rebuild = 10;
     int md_cur = 0;                   // which of the two state buffers is current
-    DBuf d_mass, d_md_state, d_md_xref, d_md_vsave, d_md_F, d_md_E, d_md_W, d_md_part;
+    DBuf d_mass, d_md_state, d_md_xref, d_md_vsave, d_md_Fb, d_md_F, d_md_E, d_md_W, d_md_part;
     unsigned md_stale_seen = 0;       // Status::md_stale when a run last looked at it
 
     bool timing = false;
@@ -1944,19 +1945,22 @@ int force_args(relres_ctx* c, const double* pos, void* forces, double* energy, d
 
 }  // namespace
 
-int relres_forces(relres_ctx* c, const double* pos, void* forces, double* energy, double* virial,
-                  void* stream)
+namespace {
+
+// The force launch of the current lists on stream s; with kick the half kick of
+// a dynamics step too (*nparts: the kinetic partials it leaves).
+int enqueue_forces(relres_ctx* c, const double* pos, void* forces, double* energy, double* virial,
+                   const MdKick* kick, int* nparts, hipStream_t s)
 {
-    if (!c) return fail(RELRES_ERR_ARG, "ctx is NULL");
-    if (!c->built) return fail(RELRES_ERR_NO_LISTS, "no lists: call relres_build_lists first");
-    hipStream_t s = (hipStream_t)stream;
-    if (c->n == 0) {
-        if (energy || virial) HIP_TRY(launch_zero_outputs(energy, virial, c->nsys, s));
-        return RELRES_OK;
-    }
-    if (!pos || !forces) return fail(RELRES_ERR_ARG, "pos or forces is NULL");
     ForceArgs a;
     TRY(force_args(c, pos, forces, energy, virial, a));
+    if (kick) {
+        a.kick = *kick;
+        *nparts = a.blocks_a + a.blocks_b;
+        long long none = 0;                // no graph holds this buffer: a run is not captured
+        TRY(ensure(c->d_md_part, sizeof(double) * (size_t)*nparts, &none));
+        a.kick.partial = c->d_md_part.as<double>();
+    }
     {
         // energy/virial records: a fresh buffer may hold another context's
         // records, whose tags could match this context's; clear it (tag 0)
@@ -1991,6 +1995,22 @@ int relres_forces(relres_ctx* c, const double* pos, void* forces, double* energy
     if (ew && c->nsys > 1)
         HIP_TRY(launch_reduce_sys_ew(a, energy, virial, s));
     return RELRES_OK;
+}
+
+}  // namespace
+
+int relres_forces(relres_ctx* c, const double* pos, void* forces, double* energy, double* virial,
+                  void* stream)
+{
+    if (!c) return fail(RELRES_ERR_ARG, "ctx is NULL");
+    if (!c->built) return fail(RELRES_ERR_NO_LISTS, "no lists: call relres_build_lists first");
+    hipStream_t s = (hipStream_t)stream;
+    if (c->n == 0) {
+        if (energy || virial) HIP_TRY(launch_zero_outputs(energy, virial, c->nsys, s));
+        return RELRES_OK;
+    }
+    if (!pos || !forces) return fail(RELRES_ERR_ARG, "pos or forces is NULL");
+    return enqueue_forces(c, pos, forces, energy, virial, nullptr, nullptr, s);
 }
 
 int relres_forces_noalloc(relres_ctx* c, const double* pos, void* forces, double* energy,
@@ -2289,6 +2309,7 @@ int relres_set_bonded(relres_ctx* c, int nbonds, const int* bonds, const double*
     std::vector<double4> term_par;
     std::vector<unsigned short> atom_slot;
     int max_atoms = 0, max_slots = 0;
+    bool closed = true;               // no term crosses a block boundary
     const int nt = c->ntypes;
     std::vector<int> slots;
     for (int blk = 0; blk < nblk; ++blk) {
@@ -2336,6 +2357,7 @@ int relres_set_bonded(relres_ctx* c, int nbonds, const int* bonds, const double*
                         for (int u = 0; u < 4; ++u) {
                             const int atom = q[u < kAtoms[kind] ? u : 0];
                             it.atom[u] = owned(atom) ? atom - bb.atom0 : ~atom;
+                            closed = closed && owned(atom);
                             it.slot[u] = kNoSlot;
                             if (u < kAtoms[kind] && owned(atom))
                                 it.slot[u] = (unsigned short)slots[atom - bb.atom0]++;
@@ -2372,11 +2394,10 @@ int relres_set_bonded(relres_ctx* c, int nbonds, const int* bonds, const double*
     TRY(up(c->d_atom_slot, atom_slot.data(), sizeof(unsigned short) * atom_slot.size()));
     TRY(ensure(c->d_bond_part, sizeof(double) * 10 * (size_t)std::max(1, nblk), gen));
     TRY(ensure(c->d_bond_sum, sizeof(double) * 16, gen));
-    // kinetic partials of the kick (one per bonded block) and of k_md_kinetic
-    TRY(ensure(c->d_md_part, sizeof(double) * (size_t)std::max({1, nblk, md_blocks(n)}), gen));
     c->bond_nblocks = nblk;
     c->bond_max_atoms = max_atoms;
     c->bond_max_slots = max_slots;
+    c->bond_closed = closed;
     c->scale14 = scale14;
     c->has_bonded = true;
     return RELRES_OK;
@@ -2384,8 +2405,7 @@ int relres_set_bonded(relres_ctx* c, int nbonds, const int* bonds, const double*
 
 namespace {
 
-int enqueue_bonded(relres_ctx* c, const double* pos, void* forces, bool sums, const MdArgs* m,
-                   hipStream_t s)
+BondedArgs bonded_args(relres_ctx* c, const double* pos, void* forces, bool add, bool sums)
 {
     BondedArgs b{};
     b.pos = pos;
@@ -2403,12 +2423,23 @@ int enqueue_bonded(relres_ctx* c, const double* pos, void* forces, bool sums, co
     b.coef64 = c->d_coef64.as<PairCoef<double>>();
     b.pcut64 = c->d_pcut64.as<Cutoffs<double>>();
     b.forces = forces;
+    b.add = add ? 1 : 0;
     b.partial = sums ? c->d_bond_part.as<double>() : nullptr;
-    HIP_TRY(launch_bonded(b, m, c->precision, s));
-    if (sums)
-        HIP_TRY(launch_sum_partials(c->d_bond_part.as<double>(), c->bond_nblocks,
-                                    nullptr, 0, 10, c->d_bond_sum.as<double>(), s));
+    return b;
+}
+
+// The sums over the blocks of a launch with sums.
+int enqueue_bonded_sums(relres_ctx* c, hipStream_t s)
+{
+    HIP_TRY(launch_sum_partials(c->d_bond_part.as<double>(), c->bond_nblocks, nullptr, 0, 10,
+                                c->d_bond_sum.as<double>(), s));
     return RELRES_OK;
+}
+
+int enqueue_bonded(relres_ctx* c, const double* pos, void* forces, bool add, bool sums, hipStream_t s)
+{
+    HIP_TRY(launch_bonded(bonded_args(c, pos, forces, add, sums), c->precision, s));
+    return sums ? enqueue_bonded_sums(c, s) : RELRES_OK;
 }
 
 }  // namespace
@@ -2423,7 +2454,7 @@ int relres_bonded_forces(relres_ctx* c, const double* pos, void* forces, double*
     if (!pos || !forces) return fail(RELRES_ERR_ARG, "pos or forces is NULL");
     hipStream_t s = (hipStream_t)stream;
     const bool sums = energy || virial;
-    TRY(enqueue_bonded(c, pos, forces, sums, nullptr, s));
+    TRY(enqueue_bonded(c, pos, forces, true, sums, s));
     const double* sum = c->d_bond_sum.as<double>();
     if (energy) HIP_TRY(hipMemcpyAsync(energy, sum, 4 * sizeof(double), hipMemcpyDeviceToDevice, s));
     if (virial) HIP_TRY(hipMemcpyAsync(virial, sum + 4, 6 * sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -2452,7 +2483,8 @@ int relres_md_setup(relres_ctx* c, const double* masses, double dt, double kT, d
     TRY(ensure(c->d_md_F, (c->precision == 64 ? 8 : 4) * 3 * (size_t)n, gen));
     TRY(ensure(c->d_md_E, sizeof(double) * 3, gen));
     TRY(ensure(c->d_md_W, sizeof(double) * 6, gen));
-    TRY(ensure(c->d_md_part, sizeof(double) * (size_t)std::max(md_blocks(n), c->bond_nblocks), gen));
+    TRY(ensure(c->d_md_Fb, (c->precision == 64 ? 8 : 4) * 3 * (size_t)n, gen));
+    TRY(ensure(c->d_md_part, sizeof(double) * (size_t)md_blocks(n), gen));
     TRY(ensure(c->d_bond_sum, sizeof(double) * 16, gen));
     MdState st{};
     st.xi = st.eta = 0.0;
@@ -2468,8 +2500,8 @@ int relres_md_setup(relres_ctx* c, const double* masses, double dt, double kT, d
     c->md_cur = 0;
     c->md_ftm2v = ftm2v;
     c->md_rebuild = rebuild_every;
-    // the per-atom bonded kernel also gives the half kick: without bonded
-    // terms it runs with none
+    // the drift kernel works on the bonded blocks: without bonded terms these
+    // hold none
     if (!c->has_bonded)
         TRY(relres_set_bonded(c, 0, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr, 0,
                               nullptr, nullptr, nullptr, nullptr, 0, nullptr, 0.0));
@@ -2523,8 +2555,8 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
     MdState* stb = c->d_md_state.as<MdState>();             // two buffers, then the saved state
     m.st = stb + c->md_cur;
     double* vsave = c->d_md_vsave.as<double>();
-    const int nblk = md_blocks(c->n);                       // partials of k_md_kinetic
-    const int nblk_kick = c->bond_nblocks;                  // partials of the kick
+    int nparts = md_blocks(c->n);      // kinetic partials: of k_md_kinetic, then of the last kick
+    void* Fb = c->d_md_Fb.p;           // bonded forces of the step
     const double* e_nb = c->d_md_E.as<double>();
     const double* w_nb = c->d_md_W.as<double>();
     const double* eb = c->d_bond_sum.as<double>();
@@ -2575,12 +2607,44 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
         first = true;
         return RELRES_OK;
     };
-    // forces of step `step`, the half kick and the kinetic partials
+    // drift to step `step` and the bonded forces there: one launch where no term
+    // crosses a bonded block, else two (the bonded launch reads other blocks'
+    // new positions).  From the second step on, the drift also does the scalar
+    // work after the previous step (second thermostat half step, its row, first
+    // half step of this one), reading one state buffer, writing the other.
+    auto drift = [&](int step) -> int {
+        const bool out = row_of(step) != nullptr;
+        DriftArgs d{};
+        d.st_in = d.st_out = m.st;
+        if (step > 1) {
+            const int next = 1 - c->md_cur;
+            d.st_out = stb + next;
+            d.nparts = nparts;
+            d.scalar = 1;
+            d.e_nb = e_nb;
+            d.w_nb = w_nb;
+            d.eb = eb;
+            d.row = row_of(step - 1);
+            c->md_cur = next;
+            m.st = stb + next;
+        }
+        m.partial = c->d_md_part.as<double>();
+        if (!c->bond_closed) {
+            HIP_TRY(launch_md_drift(m, d, prec, s));
+            return enqueue_bonded(c, pos, Fb, false, out, s);
+        }
+        HIP_TRY(launch_md_drift_bonded(m, d, bonded_args(c, pos, Fb, false, out), prec, s));
+        return out ? enqueue_bonded_sums(c, s) : RELRES_OK;
+    };
+    // the pair forces of step `step`, with the bonded ones added, the half kick
+    // and the kinetic partials
     auto finish_step = [&](int step) -> int {
         const bool out = row_of(step) != nullptr;
-        TRY(relres_forces(c, pos, F, out ? c->d_md_E.as<double>() : nullptr,
-                          out ? c->d_md_W.as<double>() : nullptr, s));
-        return enqueue_bonded(c, pos, F, out, &m, s);
+        const MdKick kick{vel, m.mass, Fb, m.st, nullptr, m.ftm2v};
+        TRY(enqueue_forces(c, pos, F, out ? c->d_md_E.as<double>() : nullptr,
+                           out ? c->d_md_W.as<double>() : nullptr, &kick, &nparts, s));
+        m.partial = c->d_md_part.as<double>();
+        return RELRES_OK;
     };
     // steps step0 + 1 .. nsteps and the end of the run, the lists being those
     // of step0's build
@@ -2589,26 +2653,18 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
             // forces at the starting positions, the kinetic energy and the
             // first thermostat half step
             TRY(relres_forces(c, pos, F, nullptr, nullptr, s));
-            TRY(enqueue_bonded(c, pos, F, false, nullptr, s));
+            TRY(enqueue_bonded(c, pos, F, true, false, s));
+            nparts = md_blocks(c->n);
             HIP_TRY(launch_md_kinetic(m, s));
-            HIP_TRY(launch_md_scalar(m.st, m.partial, nblk, m.ftm2v, 0, nsteps > 0, nullptr, nullptr,
+            HIP_TRY(launch_md_scalar(m.st, m.partial, nparts, m.ftm2v, 0, nsteps > 0, nullptr, nullptr,
                                      nullptr, nullptr, s));
         } else {
+            // gone back to: the bonded forces of that step are long overwritten
+            TRY(enqueue_bonded(c, pos, Fb, false, row_of(step0) != nullptr, s));
             TRY(finish_step(step0));
         }
         for (int step = step0 + 1; step <= nsteps; ++step) {
-            // from the second step on, the drift also does the scalar work after
-            // the previous step (second thermostat half step, its row, first
-            // half step of this one), reading one state buffer, writing the other
-            if (step == 1) {
-                HIP_TRY(launch_md_drift(m, m.st, m.st, 0, 0, nullptr, nullptr, nullptr, nullptr, prec, s));
-            } else {
-                const int next = 1 - c->md_cur;
-                HIP_TRY(launch_md_drift(m, stb + c->md_cur, stb + next, nblk_kick, 1, e_nb, w_nb, eb,
-                                        row_of(step - 1), prec, s));
-                c->md_cur = next;
-                m.st = stb + next;
-            }
+            TRY(drift(step));
             if (step % c->md_rebuild == 0) {
                 TRY(confirm());
                 TRY(build(step));
@@ -2617,7 +2673,7 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
         }
         // the second half step of the last step
         if (nsteps > 0)
-            HIP_TRY(launch_md_scalar(m.st, m.partial, nblk_kick, m.ftm2v, 1, 0, e_nb, w_nb, eb,
+            HIP_TRY(launch_md_scalar(m.st, m.partial, nparts, m.ftm2v, 1, 0, e_nb, w_nb, eb,
                                      row_of(nsteps), s));
         HIP_TRY(launch_md_finish(m, s));
         // the last steps since the previous build must not have outrun the skin either
@@ -2747,7 +2803,7 @@ void relres_destroy(relres_ctx* c)
     for (DBuf* b : {&c->d_bond_blocks, &c->d_bond_passes, &c->d_bond_terms, &c->d_term_par, &c->d_atom_slot,
                     &c->d_bond_part, &c->d_bond_sum,
                     &c->d_mass, &c->d_md_state, &c->d_md_xref,
-                    &c->d_md_F, &c->d_md_E, &c->d_md_W, &c->d_md_part, &c->d_md_vsave})
+                    &c->d_md_F, &c->d_md_E, &c->d_md_W, &c->d_md_part, &c->d_md_vsave, &c->d_md_Fb})
         release(*b);
     for (DBuf* b : {&c->d_coef64, &c->d_coef32, &c->d_hybrid, &c->d_types, &c->d_mol, &c->d_excl_off,
                     &c->d_excl_idx, &c->d_grids, &c->d_wpos, &c->d_key_a, &c->d_key_s,

@@ -137,6 +137,27 @@ struct Status {
                                     // atom more than half the skin from the last build
 };
 
+// Thermostat and integrator state on the device.
+struct MdState {
+    double xi, eta;                   // thermostat velocity and position
+    double K;                         // kinetic energy of the true velocities
+    double s2;                        // pending velocity scale (true v = stored v * s2)
+    double s_apply;                   // scale the next drift applies to stored v
+    double s_last;
+    double dt, kT, g, Q;
+};
+// The half kick that ends a dynamics step, given by the force launch (vel null:
+// none): v += dt/2 (F + bonded) / m, the forces stored are the sum, and every
+// block writes its sum of m v^2 to partial.
+struct MdKick {
+    double* vel;              // N x 3, stored velocities
+    const double* mass;
+    const void* bonded;       // N x 3 of the force type
+    const MdState* st;
+    double* partial;          // one per block of the launch
+    double ftm2v;             // force / mass -> acceleration
+};
+
 struct ForceArgs {
     const double* pos;        // caller positions, N x 3
     double box[3];            // box of system 0 (the only one when nsys == 1)
@@ -178,6 +199,7 @@ struct ForceArgs {
     int blocks_a, blocks_b;   // multiples of 8
     int lanes_a, lanes_b;     // lanes per row (powers of two)
     int log_lanes_a, log_lanes_b;
+    MdKick kick;
 };
 
 // Launchers (relres_kernels.hip).  All return hipError_t of the launch.
@@ -314,27 +336,17 @@ struct BondedArgs {
     double scale14;
     const PairCoef<double>* coef64;
     const Cutoffs<double>* pcut64;
-    void* forces;                     // N x 3 of the force type; added to
+    void* forces;                     // N x 3 of the force type
+    int add;                          // 1: forces += the bonded forces, 0: forces = them
     double* partial;                  // per block: 4 energies, 6 virial; or null
 };
-struct MdArgs;
-// Bonded and 1-4 forces added to b.forces; with m, also the half kick of a
-// dynamics step and the kinetic partials (m->partial).
-hipError_t launch_bonded(const BondedArgs& b, const MdArgs* m, int force_prec, hipStream_t s);
+// Bonded and 1-4 forces into b.forces.
+hipError_t launch_bonded(const BondedArgs& b, int force_prec, hipStream_t s);
 int md_blocks(int n);                 // blocks of the one-thread-per-atom kernels
 // out[k] = sum of p1[blk * K + k] over its blocks, then of p2, in block order
 hipError_t launch_sum_partials(const double* p1, int n1, const double* p2, int n2, int K,
                                double* out, hipStream_t s);
 
-// Thermostat and integrator state on the device.
-struct MdState {
-    double xi, eta;                   // thermostat velocity and position
-    double K;                         // kinetic energy of the true velocities
-    double s2;                        // pending velocity scale (true v = stored v * s2)
-    double s_apply;                   // scale the next drift applies to stored v
-    double s_last;
-    double dt, kT, g, Q;
-};
 struct MdArgs {
     int n;
     double ftm2v;                     // force / mass -> acceleration
@@ -352,9 +364,18 @@ struct MdArgs {
 // between the previous step and this one from st_in (kinetic partials
 // m.partial[0..nparts), the thermodynamic row when row != 0) and block 0
 // stores the new state in st_out (a different buffer).
-hipError_t launch_md_drift(const MdArgs& m, const MdState* st_in, MdState* st_out, int nparts,
-                           int scalar, const double* e_nb, const double* w_nb, const double* eb,
-                           double* row, int force_prec, hipStream_t s);
+struct DriftArgs {
+    const MdState* st_in;
+    MdState* st_out;
+    int nparts, scalar;
+    const double *e_nb, *w_nb, *eb;   // energies and virials of the row's step
+    double* row;
+};
+hipError_t launch_md_drift(const MdArgs& m, const DriftArgs& d, int force_prec, hipStream_t s);
+// The drift and the bonded forces at the new positions in one launch, for
+// bonded blocks whose terms hold atoms of the block only.
+hipError_t launch_md_drift_bonded(const MdArgs& m, const DriftArgs& d, const BondedArgs& b,
+                                  int force_prec, hipStream_t s);
 // positions, velocities and thermostat state at a list build: m.xref = pos,
 // vsave = vel, *ssave = *m.st
 hipError_t launch_md_mark(const MdArgs& m, double* vsave, MdState* ssave, hipStream_t s);

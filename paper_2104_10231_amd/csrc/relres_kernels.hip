@@ -1783,6 +1783,15 @@ __device__ void ew_finish(const ForceArgs& a, const double acc[8], unsigned tag)
     }
 }
 
+// What the half kick of atom i, component c, needs besides the pair forces.
+template <typename TF>
+__device__ __forceinline__ void kick_read(const MdKick& k, int i, int c, double& v, TF& f, double& m)
+{
+    v = k.vel[3 * i + c];
+    f = ((const TF*)k.bonded)[3 * i + c];
+    m = k.mass[i];
+}
+
 // The rows of a wave belong to one system (with several systems a table says
 // which), so the box stays in scalar registers; a box per lane held 12 vector
 // registers.  At least 6 waves per SIMD: the launches of large systems wait
@@ -1790,7 +1799,10 @@ __device__ void ew_finish(const ForceArgs& a, const double acc[8], unsigned tag)
 // took the energy/virial launch of 256 replicas from 214.6 to 203.0 us, of the
 // 98304-atom copolymer from 22.1 to 19.3, of 80000 atoms at 14 A from 62.5 to
 // 58.9 (72 and 64 registers spill: no faster, and 30 to 70 % slower).
-template <typename S, typename TF, bool EW, bool LDS, bool PC, int B>
+// Kick: the half kick of a dynamics step follows.  What it needs is read under
+// the pair terms, in launches with energy and virial (no registers left for it)
+// after them.
+template <typename S, typename TF, bool EW, bool LDS, bool PC, int B, bool Kick>
 __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces(
     ForceArgs a, Cutoffs<S> cut, Cutoffs<double> cut64)
 {
@@ -1917,6 +1929,10 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces
     }
 
     TF fx = TF(0), fy = TF(0), fz = TF(0);
+    // dynamics: velocity, bonded force (component sub) and mass of the row's
+    // atom for the half kick, read under the pair terms
+    double kv = 0.0, km = 1.0;
+    TF kf = TF(0);
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const bool own = rb ? rec.x >= 0 : (rec.x >= 0 && rec.w == 0);   // hybrid atom rows belong to the site range
     if (own) {
@@ -1933,6 +1949,8 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces
         double fxp[B], fyp[B], fzp[B], sxp[B], syp[B], szp[B];
         gather_batch<B>(a, e_fg, fxp, fyp, fzp);
         if (rb) gather_batch<B>(a, e_own, sxp, syp, szp);
+        if constexpr (Kick && !EW)
+            if (sub < 3) kick_read<TF>(a.kick, ui, sub, kv, kf, km);
         // the box (several systems: a read) after the gathers, so the wave does
         // not wait for it before issuing them
         const BoxV bx = wave_box(a, sys);
@@ -1963,7 +1981,32 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces
     fx = group_sum(fx, G);
     fy = group_sum(fy, G);
     fz = group_sum(fz, G);
-    if (own && sub == 0) {
+    if constexpr (Kick) {
+        // one component per lane of the row (all by the first lanes of a
+        // narrower group), then the block's kinetic sum
+        __shared__ double kred[kForceBlock / kWave];
+        double ke = 0.0;
+        if (own) {
+            const double h = 0.5 * a.kick.st->dt;
+            for (int c = sub; c < 3; c += G) {
+                if (EW || c != sub) kick_read<TF>(a.kick, rec.x, c, kv, kf, km);
+                const TF ft = (c == 0 ? fx : c == 1 ? fy : fz) + kf;
+                ((TF*)a.forces)[3 * rec.x + c] = ft;
+                const double v = kv + h * (a.kick.ftm2v / km) * (double)ft;
+                a.kick.vel[3 * rec.x + c] = v;
+                ke += km * v * v;
+            }
+        }
+        ke = wave_sum(ke);                 // complete in lane 63
+        if (((int)threadIdx.x & (kWave - 1)) == kWave - 1) kred[threadIdx.x / kWave] = ke;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < kForceBlock / kWave; ++w) t += kred[w];
+            a.kick.partial[blockIdx.x] = t;
+        }
+    } else if (own && sub == 0) {
         TF* F = (TF*)a.forces;
         F[3 * rec.x] = fx;
         F[3 * rec.x + 1] = fy;
@@ -2225,15 +2268,20 @@ template <typename S, typename TF, bool EW, bool LDS, bool PC>
 void launch_force_kernel(const ForceArgs& a, const double* cut64, dim3 grid, dim3 block,
                          hipStream_t s)
 {
-    if constexpr (!EW) {
-        if (a.wide_batch) {
-            hipLaunchKernelGGL((k_forces<S, TF, EW, LDS, PC, kBatchWide>), grid, block, 0, s, a,
-                               cut_as<S>(cut64), cut_as<double>(cut64));
-            return;
-        }
+#define RELRES_FORCES(B, KICK)                                                                   \
+    hipLaunchKernelGGL((k_forces<S, TF, EW, LDS, PC, B, KICK>), grid, block, 0, s, a,            \
+                       cut_as<S>(cut64), cut_as<double>(cut64))
+    if constexpr (EW) {
+        if (a.kick.vel) RELRES_FORCES(kBatch, true);
+        else RELRES_FORCES(kBatch, false);
+    } else if (a.kick.vel) {
+        if (a.wide_batch) RELRES_FORCES(kBatchWide, true);
+        else RELRES_FORCES(kBatch, true);
+    } else {
+        if (a.wide_batch) RELRES_FORCES(kBatchWide, false);
+        else RELRES_FORCES(kBatch, false);
     }
-    hipLaunchKernelGGL((k_forces<S, TF, EW, LDS, PC, kBatch>), grid, block, 0, s, a,
-                       cut_as<S>(cut64), cut_as<double>(cut64));
+#undef RELRES_FORCES
 }
 
 hipError_t launch_forces(const ForceArgs& a, const double* cut64, bool per_pair, int pair_math,

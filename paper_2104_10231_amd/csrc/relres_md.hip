@@ -4,8 +4,9 @@
 //
 // Bonded terms: a block owns a range of consecutive atoms and evaluates every
 // term that touches them once in FP64, waves of one term kind; each atom then
-// adds its terms' forces from LDS in a fixed order, and in a dynamics step the
-// same kernel gives the half kick.  A term's energy and virial are counted by
+// adds its terms' forces from LDS in a fixed order.  In a dynamics step the
+// drift is part of the same kernel, and the force launch that follows gives the
+// half kick.  A term's energy and virial are counted by
 // the block that owns its first atom (a 1-4 pair's by halves).  No atomics, so
 // results are deterministic.  Formulas
 // (forces are -dE/dx):
@@ -219,56 +220,32 @@ __device__ __forceinline__ void pair14_force(const BondedArgs& b, int pi, const 
     add_virial(acc + 4, hd, f[0]);
 }
 
-// Bonded and 1-4 forces, one block per range of consecutive atoms
-// (BondBlock).  The block's positions are staged in LDS; thread t evaluates
-// the block's terms t, t + 256, ..., which the host has grouped so that a wave
-// holds terms of one kind, and leaves each owned atom's force in that atom's
-// slots in LDS; then one thread per atom adds its slots in order.  Every term
-// is evaluated once per block that owns an atom of it, so once for molecules
-// that do not straddle blocks, by waves that take one branch: bound by the
-// dependent reads (term, then position) and the arithmetic of one term.
-// (One lane per atom and term, the version
-// before, evaluated each term two to four times in waves of all four kinds:
-// 48000-atom hexane 29.8 us in the kernel trace, now 7.4; 6000 atoms 8.0, now
-// 4.7, the launch and three dependent memory round trips.)
-// The atom's thread adds the sum to `forces` and, in a dynamics step
-// (kick != 0), gives the half kick v += dt/2 F/m and the kinetic term of the
-// block partial.  With Sums every block writes its 10 sums to b.partial
-// (energies: bonds, angles, dihedrals, 1-4; virial).  No atomics, so results are
-// deterministic.
-template <typename TF, bool Sums>
-__global__ __launch_bounds__(kMdBlock) void k_bonded(BondedArgs b, MdArgs m, int kick)
+// What thread tid of a bonded block reads first: its first term.
+__device__ __forceinline__ void first_term(const BondedArgs& b, const BondPass& ps, BondTerm& it,
+                                           double4& par)
 {
-    extern __shared__ double lds[];
-    __shared__ double red[Sums ? 10 : 1][kMdBlock / 64];
-    double* lpos = lds;                                  // [3][max_atoms]
-    double* lf = lds + 3 * b.max_atoms;                  // [3][max_slots]
-    const BondBlock bb = b.blocks[blockIdx.x];
     const int tid = (int)threadIdx.x;
-    const int a = bb.atom0 + tid;
-    const bool live = tid < bb.natoms;                   // this thread's atom
-    double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    double fa[3] = {0.0, 0.0, 0.0};
-    // the first term and the atom's own data: none of these reads waits on another
-    BondPass ps = bb.pass;
-    BondTerm it;
     it.kind = -1;
-    double4 par = make_double4(0.0, 0.0, 0.0, 0.0);
+    par = make_double4(0.0, 0.0, 0.0, 0.0);
     if (tid < ps.nterms) {
         it = b.terms[ps.term0 + tid];
         par = b.term_par[ps.term0 + tid];
     }
-    TF* F = (TF*)b.forces;
-    TF f0[3] = {TF(0), TF(0), TF(0)};
-    double v0[3] = {0.0, 0.0, 0.0}, ma = 1.0;
-    if (live) {
-        for (int c = 0; c < 3; ++c) lpos[c * b.max_atoms + tid] = b.pos[3 * (size_t)a + c];
-        for (int c = 0; c < 3; ++c) f0[c] = F[3 * (size_t)a + c];
-        if (kick) {
-            for (int c = 0; c < 3; ++c) v0[c] = m.vel[3 * (size_t)a + c];
-            ma = m.mass[a];
-        }
-    }
+}
+
+// The bonded forces on the block's atoms at the positions in lpos (thread tid:
+// atom bb.atom0 + tid, its force in fa), it and par being the thread's first
+// term.  Thread t evaluates the block's terms t, t + 256, ..., which the host
+// has grouped so that a wave holds terms of one kind, and leaves each owned
+// atom's force in that atom's slots in LDS; then one thread per atom adds its
+// slots in order.  Without Cross every atom of every term is the block's own.
+template <bool Sums, bool Cross>
+__device__ __forceinline__ void bonded_forces(const BondedArgs& b, const BondBlock& bb, double* lpos,
+                                              double* lf, BondTerm it, double4 par, double fa[3],
+                                              double acc[10])
+{
+    const int tid = (int)threadIdx.x;
+    BondPass ps = bb.pass;
     __syncthreads();
     for (int p = 0; ps.nterms > 0; ++p) {
         for (int t = tid; t < ps.nterms; t += kMdBlock) {
@@ -283,7 +260,7 @@ __global__ __launch_bounds__(kMdBlock) void k_bonded(BondedArgs b, MdArgs m, int
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int c = 0; c < 3; ++c) x[q][c] = lpos[c * b.max_atoms + max(it.atom[q], 0)];
-            if ((it.atom[0] | it.atom[1] | it.atom[2] | it.atom[3]) < 0) {
+            if (Cross && (it.atom[0] | it.atom[1] | it.atom[2] | it.atom[3]) < 0) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     if (it.atom[q] < 0)
@@ -305,7 +282,7 @@ __global__ __launch_bounds__(kMdBlock) void k_bonded(BondedArgs b, MdArgs m, int
             }
         }
         __syncthreads();
-        if (live) {
+        if (tid < bb.natoms) {
             const int s0 = b.atom_slot[ps.slot0 + tid], s1 = b.atom_slot[ps.slot0 + tid + 1];
             for (int k = s0; k < s1; ++k)
 #pragma unroll
@@ -315,30 +292,49 @@ __global__ __launch_bounds__(kMdBlock) void k_bonded(BondedArgs b, MdArgs m, int
         ps = b.passes[bb.more0 + p];
         __syncthreads();               // the slots are used again
     }
-    double ke = 0.0;
-    if (live) {
-        TF ft[3];
+}
+
+// Bonded and 1-4 forces, one block per range of consecutive atoms
+// (BondBlock), whose positions are staged in LDS.  Every term
+// is evaluated once per block that owns an atom of it, so once for molecules
+// that do not straddle blocks, by waves that take one branch: bound by the
+// dependent reads (term, then position) and the arithmetic of one term.
+// (One lane per atom and term, the version
+// before, evaluated each term two to four times in waves of all four kinds:
+// 48000-atom hexane 29.8 us in the kernel trace, so 7.4; 6000 atoms 8.0 and
+// 4.7, the launch and three dependent memory round trips.)
+// With Sums every block writes its 10 sums to b.partial (energies: bonds,
+// angles, dihedrals, 1-4; virial).  No atomics, so results are deterministic.
+template <typename TF, bool Sums>
+__global__ __launch_bounds__(kMdBlock) void k_bonded(BondedArgs b)
+{
+    extern __shared__ double lds[];
+    __shared__ double red[Sums ? 10 : 1][kMdBlock / 64];
+    double* lpos = lds;                                  // [3][max_atoms]
+    double* lf = lds + 3 * b.max_atoms;                  // [3][max_slots]
+    const BondBlock bb = b.blocks[blockIdx.x];
+    const int tid = (int)threadIdx.x;
+    const int a = bb.atom0 + tid;
+    const bool live = tid < bb.natoms;                   // this thread's atom
+    double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    double fa[3] = {0.0, 0.0, 0.0};
+    // the first term and the atom's own data: none of these reads waits on another
+    BondTerm it;
+    double4 par;
+    first_term(b, bb.pass, it, par);
+    TF* F = (TF*)b.forces;
+    TF f0[3] = {TF(0), TF(0), TF(0)};
+    if (live)
         for (int c = 0; c < 3; ++c) {
-            ft[c] = f0[c] + (TF)fa[c];
-            F[3 * (size_t)a + c] = ft[c];
+            lpos[c * b.max_atoms + tid] = b.pos[3 * (size_t)a + c];
+            if (b.add) f0[c] = F[3 * (size_t)a + c];
         }
-        if (kick) {
-            const double dt = m.st->dt;
-            const double am = m.ftm2v / ma;
-            for (int c = 0; c < 3; ++c) {
-                const double v = v0[c] + 0.5 * dt * am * (double)ft[c];
-                m.vel[3 * (size_t)a + c] = v;
-                ke += ma * v * v;
-            }
-        }
-    }
+    bonded_forces<Sums, true>(b, bb, lpos, lf, it, par, fa, acc);
+    if (live)
+        for (int c = 0; c < 3; ++c) F[3 * (size_t)a + c] = f0[c] + (TF)fa[c];
     if constexpr (Sums) {
         const double r = block_sum<10>(acc, red);
         if (tid < 10) b.partial[(size_t)blockIdx.x * 10 + tid] = r;
-    }
-    if (kick) {
-        const double r = block_sum<1>(&ke, red);
-        if (tid == 0) m.partial[blockIdx.x] = r;
     }
 }
 
@@ -377,6 +373,27 @@ __device__ __forceinline__ double sum_blocks(const double* __restrict__ p1, int 
     add_blocks(p1, n1, K, k, lane, s);
     add_blocks(p2, n2, K, k, lane, s);
     return wave_sum(s);                // complete in lane 63
+}
+
+// Sum of the kinetic partials over a block of kMdBlock threads in a fixed
+// order (thread t adds t, t + kMdBlock, ..., the block its threads): the force
+// launch of 48000 atoms leaves about 2000 partials, one round of 8 reads in
+// flight per thread.  Thread 0 gets the sum.
+__device__ __forceinline__ double sum_kinetic(const double* __restrict__ p, int n,
+                                              double (*red)[kMdBlock / 64])
+{
+    double s = 0.0;
+    for (int base = (int)threadIdx.x; base < n; base += kMdBlock * kSumLoads) {
+        double x[kSumLoads];
+#pragma unroll
+        for (int u = 0; u < kSumLoads; ++u) {
+            const double v = p[min(base + kMdBlock * u, n - 1)];
+            x[u] = base + kMdBlock * u < n ? v : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < kSumLoads; ++u) s += x[u];
+    }
+    return block_sum<1>(&s, red);
 }
 
 // out[k] = the sums over blocks of p1[blk * K + k] and of p2 (one wave per
@@ -443,70 +460,132 @@ __device__ void scalar_step(MdState& st, double ksum, double ftm2v, int second, 
     }
 }
 
-// Drift of one step.  With `scalar`, every block first does the scalar work
-// between the previous step and this one (the same sums in the same order,
-// so every block gets the same state; block 0 stores it in st_out and writes
-// the row), which saves a launch per step; st_in is not written, so no block
-// can see a half-updated state.  Without it the state in st_in is current.
+// The atom's data of a drift: none of it depends on the scalar work, so its
+// reads overlap the sum of the partials.
 template <typename TF>
-__global__ __launch_bounds__(kMdBlock) void k_md_drift(MdArgs m, const MdState* st_in,
-                                                       MdState* st_out, int nparts, int scalar,
-                                                       const double* __restrict__ e_nb,
-                                                       const double* __restrict__ w_nb,
-                                                       const double* __restrict__ eb,
-                                                       double* __restrict__ row)
+struct DriftAtom {
+    double v[3], x[3], xref[3], mass;
+    TF f[3];
+};
+
+template <typename TF>
+__device__ __forceinline__ DriftAtom<TF> drift_read(const MdArgs& m, int i, bool in)
 {
-    __shared__ double s_sh;
-    // the atom's data first: none of it depends on the scalar work, so its
-    // reads overlap the sum of the partials
-    const int i = blockIdx.x * kMdBlock + threadIdx.x;
-    const bool in = i < m.n;
+    DriftAtom<TF> d;
     const TF* F = (const TF*)m.forces;
-    double v0[3] = {0.0, 0.0, 0.0}, x0[3] = {0.0, 0.0, 0.0}, xr[3] = {0.0, 0.0, 0.0};
-    TF f0[3] = {TF(0), TF(0), TF(0)};
-    double mass = 1.0;
+    d.mass = 1.0;
+    for (int c = 0; c < 3; ++c) {
+        d.v[c] = d.x[c] = d.xref[c] = 0.0;
+        d.f[c] = TF(0);
+    }
     if (in) {
         for (int c = 0; c < 3; ++c) {
-            v0[c] = m.vel[3 * i + c];
-            x0[c] = m.pos[3 * i + c];
-            xr[c] = m.xref[3 * i + c];
-            f0[c] = F[3 * i + c];
+            d.v[c] = m.vel[3 * i + c];
+            d.x[c] = m.pos[3 * i + c];
+            d.xref[c] = m.xref[3 * i + c];
+            d.f[c] = F[3 * i + c];
         }
-        mass = m.mass[i];
+        d.mass = m.mass[i];
     }
-    const double dt = st_in->dt;
-    double s;
-    if (scalar) {
-        if (threadIdx.x < 64) {
-            const double ks = sum_blocks(m.partial, nparts, nullptr, 0, 1, 0);
-            if (threadIdx.x == 63) {
-                MdState st = *st_in;
-                scalar_step(st, ks, m.ftm2v, 1, 1, e_nb, w_nb, eb,
-                            blockIdx.x == 0 ? row : nullptr);
-                if (blockIdx.x == 0) *st_out = st;
-                s_sh = st.s_apply;
-            }
-        }
-        __syncthreads();
-        s = s_sh;
-    } else {
-        s = st_in->s_apply;
+    return d;
+}
+
+// Scale of the stored velocities in a drift.  With d.scalar every block first
+// does the scalar work between the previous step and this one (the same sums
+// in the same order, so every block gets the same state; block 0 stores it in
+// st_out and writes the row), which saves a launch per step; st_in is not
+// written, so no block can see a half-updated state.  Without it the state in
+// st_in is current.  All threads of the block.
+__device__ __forceinline__ double drift_scale(const MdArgs& m, const DriftArgs& d, double* s_sh,
+                                              double (*red)[kMdBlock / 64])
+{
+    if (!d.scalar) return d.st_in->s_apply;
+    MdState st;
+    if (threadIdx.x == 0) st = *d.st_in;
+    const double ks = sum_kinetic(m.partial, d.nparts, red);
+    if (threadIdx.x == 0) {
+        scalar_step(st, ks, m.ftm2v, 1, 1, d.e_nb, d.w_nb, d.eb, blockIdx.x == 0 ? d.row : nullptr);
+        if (blockIdx.x == 0) *d.st_out = st;
+        *s_sh = st.s_apply;
     }
-    if (!in) return;
-    const double am = m.ftm2v / mass;
+    __syncthreads();
+    return *s_sh;
+}
+
+// The drift of atom i; its new position goes to a.x.
+template <typename TF>
+__device__ __forceinline__ void drift_atom(const MdArgs& m, int i, bool in, double dt, double s,
+                                           DriftAtom<TF>& a)
+{
+    const double am = m.ftm2v / a.mass;
     double dmax2 = 0.0;
-    for (int c = 0; c < 3; ++c) {
-        const double v = v0[c] * s + 0.5 * dt * am * (double)f0[c];
-        m.vel[3 * i + c] = v;
-        const double x = x0[c] + dt * v;
-        m.pos[3 * i + c] = x;
-        const double dx = x - xr[c];
-        dmax2 += dx * dx;
-    }
+    if (in)
+        for (int c = 0; c < 3; ++c) {
+            const double v = a.v[c] * s + 0.5 * dt * am * (double)a.f[c];
+            m.vel[3 * i + c] = v;
+            a.x[c] += dt * v;
+            m.pos[3 * i + c] = a.x[c];
+            const double dx = a.x[c] - a.xref[c];
+            dmax2 += dx * dx;
+        }
     // an atom that moved more than half the skin since the last build
     // invalidates the lists; the host checks the count with the next build's status
     const uint64_t far = __ballot(dmax2 > m.half_skin2);
     if (far != 0ull && ((int)threadIdx.x & 63) == __ffsll((long long)far) - 1) atomicAdd(m.stale, 1u);
+}
+
+// Drift of one step, one thread per atom.
+template <typename TF>
+__global__ __launch_bounds__(kMdBlock) void k_md_drift(MdArgs m, DriftArgs d)
+{
+    __shared__ double s_sh;
+    __shared__ double red[1][kMdBlock / 64];
+    const int i = blockIdx.x * kMdBlock + threadIdx.x;
+    const bool in = i < m.n;
+    DriftAtom<TF> a = drift_read<TF>(m, i, in);
+    const double dt = d.st_in->dt;
+    const double s = drift_scale(m, d, &s_sh, red);
+    drift_atom(m, i, in, dt, s, a);
+}
+
+// Drift of one step and the bonded forces at the new positions (written to
+// b.forces), one block per bonded block, for blocks whose terms hold only atoms
+// of the block.  The force launch that follows adds them and gives the half
+// kick, so a step is two launches: each launch of a 6000-atom step is bound by
+// its dependent reads (about 3 us with the gap), not by its work.  Kernel trace
+// of a step, drift + forces + bonded before, this kernel + forces now: 6000
+// atoms 3.6 + 6.7 + 5.0 to 5.9 + 7.2 us (a run 20.5 to 18.6 us a step), 48000
+// atoms 4.5 + 15.9 + 7.6 to 9.3 + 17.2 us (40.4 to 39.2).
+template <typename TF, bool Sums>
+__global__ __launch_bounds__(kMdBlock) void k_md_drift_bonded(MdArgs m, DriftArgs d, BondedArgs b)
+{
+    extern __shared__ double lds[];
+    __shared__ double s_sh;
+    __shared__ double red[Sums ? 10 : 1][kMdBlock / 64];
+    double* lpos = lds;                                  // [3][max_atoms]
+    double* lf = lds + 3 * b.max_atoms;                  // [3][max_slots]
+    const BondBlock bb = b.blocks[blockIdx.x];
+    const int tid = (int)threadIdx.x;
+    const int i = bb.atom0 + tid;
+    const bool in = tid < bb.natoms;
+    DriftAtom<TF> a = drift_read<TF>(m, i, in);
+    BondTerm it;
+    double4 par;
+    first_term(b, bb.pass, it, par);
+    const double dt = d.st_in->dt;
+    const double s = drift_scale(m, d, &s_sh, red);
+    drift_atom(m, i, in, dt, s, a);
+    if (in)
+        for (int c = 0; c < 3; ++c) lpos[c * b.max_atoms + tid] = a.x[c];
+    double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    double fa[3] = {0.0, 0.0, 0.0};
+    bonded_forces<Sums, false>(b, bb, lpos, lf, it, par, fa, acc);
+    if (in)
+        for (int c = 0; c < 3; ++c) ((TF*)b.forces)[3 * (size_t)i + c] = (TF)fa[c];
+    if constexpr (Sums) {
+        const double r = block_sum<10>(acc, red);
+        if (tid < 10) b.partial[(size_t)blockIdx.x * 10 + tid] = r;
+    }
 }
 
 // Everything a run needs to go on from a list build: the reference positions
@@ -534,17 +613,19 @@ __global__ __launch_bounds__(kMdBlock) void k_md_kinetic(MdArgs m)
     if (threadIdx.x == 0) m.partial[blockIdx.x] = r;
 }
 
-// The scalar work between two steps as a kernel of its own (one wave; at
+// The scalar work between two steps as a kernel of its own (one block; at
 // the start and the end of a run, where no drift follows): scalar_step on
 // the state in place.
-__global__ void k_md_scalar(MdState* st, const double* __restrict__ partial, int nblocks,
-                            double ftm2v, int second, int first, const double* __restrict__ e_nb,
-                            const double* __restrict__ w_nb, const double* __restrict__ eb,
-                            double* __restrict__ row)
+__global__ __launch_bounds__(kMdBlock) void k_md_scalar(MdState* st, const double* __restrict__ partial,
+                                                        int nblocks, double ftm2v, int second, int first,
+                                                        const double* __restrict__ e_nb,
+                                                        const double* __restrict__ w_nb,
+                                                        const double* __restrict__ eb,
+                                                        double* __restrict__ row)
 {
-    // one wave: the block partials in a fixed order, then lane 63 alone
-    const double s = sum_blocks(partial, nblocks, nullptr, 0, 1, 0);
-    if (threadIdx.x != 63) return;
+    __shared__ double red[1][kMdBlock / 64];
+    const double s = sum_kinetic(partial, nblocks, red);
+    if (threadIdx.x != 0) return;
     MdState cur = *st;
     scalar_step(cur, s, ftm2v, second, first, e_nb, w_nb, eb, row);
     *st = cur;
@@ -563,15 +644,20 @@ __global__ void k_md_unit_scale(MdState* st) { st->s2 = 1.0; }
 
 }  // namespace
 
-hipError_t launch_bonded(const BondedArgs& b, const MdArgs* m, int force_prec, hipStream_t s)
+namespace {
+size_t bonded_lds(const BondedArgs& b)
+{
+    return sizeof(double) * 3 * (size_t)(b.max_atoms + b.max_slots);
+}
+}  // namespace
+
+hipError_t launch_bonded(const BondedArgs& b, int force_prec, hipStream_t s)
 {
     if (b.n == 0) return hipSuccess;
     const dim3 grid(b.nblocks);
-    const MdArgs none{};
-    const int kick = m ? 1 : 0;
-    const size_t lds = sizeof(double) * 3 * (size_t)(b.max_atoms + b.max_slots);
+    const size_t lds = bonded_lds(b);
 #define RELRES_BONDED(TF, SUMS)                                                                  \
-    hipLaunchKernelGGL((k_bonded<TF, SUMS>), grid, dim3(kMdBlock), lds, s, b, m ? *m : none, kick)
+    hipLaunchKernelGGL((k_bonded<TF, SUMS>), grid, dim3(kMdBlock), lds, s, b)
     if (force_prec == 64) {
         if (b.partial) RELRES_BONDED(double, true); else RELRES_BONDED(double, false);
     } else {
@@ -590,17 +676,29 @@ hipError_t launch_sum_partials(const double* p1, int n1, const double* p2, int n
     return hipGetLastError();
 }
 
-hipError_t launch_md_drift(const MdArgs& m, const MdState* st_in, MdState* st_out, int nparts,
-                           int scalar, const double* e_nb, const double* w_nb, const double* eb,
-                           double* row, int force_prec, hipStream_t s)
+hipError_t launch_md_drift(const MdArgs& m, const DriftArgs& d, int force_prec, hipStream_t s)
 {
     const int blocks = (m.n + kMdBlock - 1) / kMdBlock;
     if (force_prec == 64)
-        hipLaunchKernelGGL(k_md_drift<double>, dim3(blocks), dim3(kMdBlock), 0, s, m, st_in,
-                           st_out, nparts, scalar, e_nb, w_nb, eb, row);
+        hipLaunchKernelGGL(k_md_drift<double>, dim3(blocks), dim3(kMdBlock), 0, s, m, d);
     else
-        hipLaunchKernelGGL(k_md_drift<float>, dim3(blocks), dim3(kMdBlock), 0, s, m, st_in,
-                           st_out, nparts, scalar, e_nb, w_nb, eb, row);
+        hipLaunchKernelGGL(k_md_drift<float>, dim3(blocks), dim3(kMdBlock), 0, s, m, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_md_drift_bonded(const MdArgs& m, const DriftArgs& d, const BondedArgs& b,
+                                  int force_prec, hipStream_t s)
+{
+    const dim3 grid(b.nblocks);
+    const size_t lds = bonded_lds(b);
+#define RELRES_STEP(TF, SUMS)                                                                    \
+    hipLaunchKernelGGL((k_md_drift_bonded<TF, SUMS>), grid, dim3(kMdBlock), lds, s, m, d, b)
+    if (force_prec == 64) {
+        if (b.partial) RELRES_STEP(double, true); else RELRES_STEP(double, false);
+    } else {
+        if (b.partial) RELRES_STEP(float, true); else RELRES_STEP(float, false);
+    }
+#undef RELRES_STEP
     return hipGetLastError();
 }
 
@@ -621,7 +719,7 @@ hipError_t launch_md_scalar(MdState* st, const double* partial, int nblocks, dou
                             int second, int first, const double* e_nb, const double* w_nb,
                             const double* eb, double* row, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_md_scalar, dim3(1), dim3(64), 0, s, st, partial, nblocks, ftm2v, second,
+    hipLaunchKernelGGL(k_md_scalar, dim3(1), dim3(kMdBlock), 0, s, st, partial, nblocks, ftm2v, second,
                        first, e_nb, w_nb, eb, row);
     return hipGetLastError();
 }
