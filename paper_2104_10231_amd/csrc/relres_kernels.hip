@@ -1595,19 +1595,27 @@ __device__ __forceinline__ void row_terms(const ForceArgs& a, const BoxV& bx,
 // read-modify-write (which serialise on one address) is needed.  The tag is
 // the device epoch + 1; the epoch advances once per launch.
 //
-// Blocks b with b % 16 == g form group g (16 groups: fewer records for each
-// group's waiting block to poll than with 8, and still one poll round for the
-// 16 group records).  The highest-numbered block of each group waits for the
-// records of the rest of its group and publishes the group sum; block nb-1
-// (the highest of all) then waits for the group records and writes energy
-// and virial.  A waiting block only ever waits for blocks with
-// lower numbers, which the hardware dispatched before it, so every wait ends;
-// it is bounded anyway (a.spin_limit polls; a negative limit gives up at
-// once), after which energy and virial are set to NaN and the status counts
-// the failure, which the host reports (relres_sync, relres_check_lists).
-// Sums are taken in a fixed order: the result does not depend on which block
-// finished when.
+// Launches of more than kEwDirect blocks: blocks b with b % 16 == g form group
+// g (16 groups: fewer records for each group's waiting block to poll than with
+// 8, and still one poll round for the 16 group records).  The highest-numbered
+// block of each group waits for the records of the rest of its group and
+// publishes the group sum; block nb-1 (the highest of all) then waits for the
+// group records and writes energy and virial.  In smaller launches block nb-1
+// waits for all the others itself, one wait in place of two: 1500 propane atoms
+// (FP64, 128 blocks) 7.5 us a launch with two, 6.9 with one; at 200 blocks the
+// two are even, and at 400 the records of one wait queue on one CU (1 us
+// slower).  A launch with energy and virial is 2.5 to 4 us longer than one with
+// forces only: about 0.8 for the block's sum and its record, the rest these
+// waits, each a store and a load through the level all XCDs share.
+//
+// A waiting block only ever waits for blocks with lower numbers, which the
+// hardware dispatched before it, so every wait ends; it is bounded anyway
+// (a.spin_limit polls; a negative limit gives up at once), after which energy
+// and virial are set to NaN and the status counts the failure, which the host
+// reports (relres_sync, relres_check_lists).  Sums are taken in a fixed order:
+// the result does not depend on which block finished when.
 constexpr int kRecWords = 16;
+constexpr int kEwDirect = 128;
 
 // Writes one record: called by the whole block, `v` valid in threads 0..7
 // (component threadIdx.x).  Lanes 0..15 of wave 0 store word threadIdx.x, so
@@ -1627,41 +1635,37 @@ __device__ __forceinline__ void put_record(unsigned long long* rec, double v, un
 
 // Waits for `count` records (record m at rec + (first + stride*m) * 16 words)
 // to carry `tag` and adds them up.  Sixteen consecutive lanes read the sixteen
-// words of one record, so every load instruction covers whole records.  On
-// return, even lanes hold their record-word pair's component (t % 16) / 2
-// summed over their records in v[]; odd lanes hold zeros.  Sets *failed if a
-// wait gave up.
+// words of one record, so every load instruction covers whole records.  Returns,
+// in the even ones of the first 16 lanes of each wave, the sum of component
+// lane / 2 over the wave's records.  Sets *failed if a wait gave up.  (Two or
+// three polls in flight, 80 to 270 ns apart, saw the records no sooner.)
 template <int kPollBatch>      // records polled per thread at once
-__device__ __forceinline__ void gather_records(const unsigned long long* rec, int first, int stride,
-                                               int count, unsigned tag, int spin_limit,
-                                               double v[8], int* failed)
+__device__ __forceinline__ double gather_records(const unsigned long long* rec, int first, int stride,
+                                                 int count, unsigned tag, int spin_limit, int* failed)
 {
     const int t = (int)threadIdx.x;
     const int word = t & (kRecWords - 1);
-    const int comp = word >> 1;
     double sum = 0.0;
     for (int base = 0; base < count; base += (kForceBlock / kRecWords) * kPollBatch) {
         // every slot loads on every poll (slots past `count` re-read the
         // first record), so all loads of a poll are in flight together; a
         // record already complete is final for this launch
-        size_t off[kPollBatch];
+        unsigned off[kPollBatch];
         bool valid[kPollBatch];
 #pragma unroll
         for (int u = 0; u < kPollBatch; ++u) {
             const int m = base + t / kRecWords + (kForceBlock / kRecWords) * u;
             valid[u] = m < count;
-            off[u] = (size_t)(first + stride * (valid[u] ? m : 0)) * kRecWords + word;
+            off[u] = (unsigned)(first + stride * (valid[u] ? m : 0)) * kRecWords + word;
         }
         unsigned long long w[kPollBatch];
         for (int it = 0;; ++it) {
 #pragma unroll
             for (int u = 0; u < kPollBatch; ++u)
                 w[u] = __hip_atomic_load(rec + off[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            bool pending = false;
+            bool pending = spin_limit < 0;          // give up at once
 #pragma unroll
-            for (int u = 0; u < kPollBatch; ++u)
-                pending |= valid[u] && (unsigned)(w[u] >> 32) != tag;
-            pending |= spin_limit < 0 && count > 0;   // give up at once
+            for (int u = 0; u < kPollBatch; ++u) pending |= valid[u] && (unsigned)(w[u] >> 32) != tag;
             if (!pending) break;
             if (it >= spin_limit) {
                 *failed = 1;
@@ -1676,78 +1680,83 @@ __device__ __forceinline__ void gather_records(const unsigned long long* rec, in
                 sum += __longlong_as_double((long long)(((w[u] & 0xffffffffull) << 32) | lo));
         }
     }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = (!(word & 1) && k == comp) ? sum : 0.0;
+    sum += __shfl_xor(sum, kRecWords);
+    return sum + __shfl_xor(sum, 2 * kRecWords);
 }
 
 // Fixed-order block reduction of v[8]: result in threads 0..7 (component
-// threadIdx.x) as the return value; `extra` (threads 0..7) is added last.
-__device__ __forceinline__ double block_reduce8(const double v[8], double extra,
-                                                double (*red)[kForceBlock / 64])
+// threadIdx.x) as the return value.
+__device__ __forceinline__ double block_reduce8(const double v[8], double (*red)[kForceBlock / 64])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const double s = wave_sum8(v);
     if (lane < 8) red[wave_sum8_lane(lane)][wave] = s;
     __syncthreads();
     double t = 0.0;
-    if (threadIdx.x < 8) {
+    if (threadIdx.x < 8)
         for (int w = 0; w < kForceBlock / 64; ++w) t += red[threadIdx.x][w];
-        t += extra;
-    }
-    __syncthreads();
     return t;
 }
 
 __device__ void ew_finish(const ForceArgs& a, const double acc[8], unsigned tag)
 {
-    __shared__ double red[8][kForceBlock / 64];
+    __shared__ double red[8][kForceBlock / 64], red2[8][kForceBlock / 64];
     __shared__ int failed;
     const int nb = (int)gridDim.x;
     const int b = (int)blockIdx.x;
-    const int g = b % kEwGroups;
-    const int ngroups = nb < kEwGroups ? nb : kEwGroups;
-    const int last_in_group = g + kEwGroups * ((nb - 1 - g) / kEwGroups);
+    const int lg = nb <= kEwDirect ? 0 : kEwLogGroups;
+    const int groups = 1 << lg;
+    const int g = b & (groups - 1);
 
     if (threadIdx.x == 0) failed = 0;
-    const double mine = block_reduce8(acc, 0.0, red);
-    // records: blocks [0, nb), groups [nb, nb + 8)
+    const double mine = block_reduce8(acc, red);
+    // records: blocks [0, nb), groups [nb, nb + kEwGroups)
     unsigned long long* grec = a.ew_rec + (size_t)nb * kRecWords;
-    if (b != last_in_group) {
+    if (b + groups < nb) {               // not the last of its group
         put_record(a.ew_rec + (size_t)b * kRecWords, mine, tag);
         return;
     }
-    // group g: members g, g+8, ..., b-8 (in that order), then this block
-    double v[8];
+    // group g: members g, g + groups, ..., b - groups (in that order), then this block
     // records per thread per poll: as few loads as cover the group in one
     // round (a poll's loads queue on this one CU's memory pipeline, so extra
     // slots that re-read a record cost time: 16 per thread took 0.5 us more
     // than 8 for 71 records)
-    const int count = b / kEwGroups;
+    const int count = b >> lg;
     constexpr int kSlots = kForceBlock / kRecWords;      // records per load instruction
+    double v;
     if (count <= 2 * kSlots)
-        gather_records<2>(a.ew_rec, g, kEwGroups, count, tag, a.spin_limit, v, &failed);
+        v = gather_records<2>(a.ew_rec, g, groups, count, tag, a.spin_limit, &failed);
     else if (count <= 4 * kSlots)
-        gather_records<4>(a.ew_rec, g, kEwGroups, count, tag, a.spin_limit, v, &failed);
+        v = gather_records<4>(a.ew_rec, g, groups, count, tag, a.spin_limit, &failed);
     else if (count <= 8 * kSlots)
-        gather_records<8>(a.ew_rec, g, kEwGroups, count, tag, a.spin_limit, v, &failed);
+        v = gather_records<8>(a.ew_rec, g, groups, count, tag, a.spin_limit, &failed);
     else
-        gather_records<16>(a.ew_rec, g, kEwGroups, count, tag, a.spin_limit, v, &failed);
-    const double gsum = block_reduce8(v, mine, red);
+        v = gather_records<16>(a.ew_rec, g, groups, count, tag, a.spin_limit, &failed);
+    const int lane = (int)threadIdx.x & (kWave - 1);
+    if (lane < kRecWords && !(lane & 1)) red2[lane >> 1][threadIdx.x / kWave] = v;
+    __syncthreads();
+    double gsum = mine;
+    if (threadIdx.x < 8) {
+        double t = 0.0;
+        for (int w = 0; w < kForceBlock / kWave; ++w) t += red2[threadIdx.x][w];
+        gsum = t + mine;
+    }
     if (b != nb - 1) {
         put_record(grec + (size_t)g * kRecWords, failed ? __builtin_nan("") : gsum, tag);
         if (threadIdx.x == 0 && failed) atomicAdd(a.ew_failed, 1u);
         return;
     }
-    // final block: the group sums in group order.  The other groups' records
+    // final block.  One group: its sum.  Else the group sums in group order: the other groups' records
     // are gathered (groups 0..ngroups-1 except g, which is this block's own);
     // to keep the order fixed, the own group's sum is slotted in at its place.
     __shared__ double gred[kEwGroups][8];
     if (threadIdx.x < 8) gred[g][threadIdx.x] = gsum;
-    {
+    if (groups > 1) {
         const int t = (int)threadIdx.x;
         const int q = t / kRecWords, word = t & (kRecWords - 1);
+        const bool other = q < groups && q != g;
         unsigned long long w = 0;
-        if (q < ngroups && q != g) {
+        if (other) {
             for (int it = 0;; ++it) {
                 w = __hip_atomic_load(grec + (size_t)q * kRecWords + word, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
@@ -1760,25 +1769,23 @@ __device__ void ew_finish(const ForceArgs& a, const double acc[8], unsigned tag)
             }
         }
         const unsigned lo = (unsigned)__shfl_down((unsigned)(w & 0xffffffffull), 1);
-        if (q < ngroups && q != g && !(word & 1))
+        if (other && !(word & 1))
             gred[q][word >> 1] = __longlong_as_double((long long)(((w & 0xffffffffull) << 32) | lo));
     }
     __syncthreads();
-    if (threadIdx.x < 8) {
-        double t = 0.0;
-        for (int q = 0; q < ngroups; ++q) t += gred[q][threadIdx.x];
-        red[threadIdx.x][0] = t;
-    }
-    __syncthreads();
+    if (threadIdx.x >= kWave) return;
     const bool bad = failed != 0;
-    if (threadIdx.x == 0 && bad) atomicAdd(a.ew_failed, 1u);
+    double val = 0.0;
     if (threadIdx.x < 8) {
-        const double val = bad ? __builtin_nan("") : red[threadIdx.x][0];
+        for (int q = 0; q < groups; ++q) val += gred[q][threadIdx.x];
+        if (bad) val = __builtin_nan("");
         if (threadIdx.x < 2 && a.energy) a.energy[1 + threadIdx.x] = val;
         if (threadIdx.x >= 2 && a.virial) a.virial[threadIdx.x - 2] = val;
     }
+    const double e_cg = __shfl_down(val, 1);
     if (threadIdx.x == 0) {
-        if (a.energy) a.energy[0] = bad ? __builtin_nan("") : red[0][0] + red[1][0];
+        if (bad) atomicAdd(a.ew_failed, 1u);
+        if (a.energy) a.energy[0] = val + e_cg;
         __hip_atomic_store(a.epoch, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
