@@ -942,7 +942,7 @@ int refresh_list_stats(relres_ctx* c, hipStream_t s)
 {
     const bool sites = c->n_sites > 0;
     if (c->n > 0) {
-        HIP_TRY(launch_list_stats(c->d_grids.as<GridDev>(), sites ? 2 : 1, c->d_status.as<Status>(), s));
+        HIP_TRY(launch_list_stats(c->d_grids.as<GridDev>(), sites ? 2 : 1, c->n, c->d_status.as<Status>(), s));
         HIP_TRY(hipMemcpyAsync(c->h_status, c->d_status.p, sizeof(Status), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
     }

@@ -254,7 +254,8 @@ hipError_t launch_lists(GridDev* grids_dev, int ncell_a, int ncell_s, int waves_
 // per_pair: the distances of each type pair come from a.pcut32 / a.pcut64
 hipError_t launch_forces(const ForceArgs& a, const double* cut64, bool per_pair, int pair_math,
                          int precision, bool ew, hipStream_t s);
-hipError_t launch_list_stats(GridDev* grids_dev, int ngrids, Status* st, hipStream_t s);
+// most_rows: rows of the larger grid
+hipError_t launch_list_stats(GridDev* grids_dev, int ngrids, int most_rows, Status* st, hipStream_t s);
 // The adjoint's table, kBackTab doubles per type pair: the FG fields of the
 // eps and the sigma derivative records, the CG fields of both, eps_FG, eps_CG,
 // and the pair's distances (Cutoffs).
