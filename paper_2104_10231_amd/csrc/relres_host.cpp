@@ -197,14 +197,11 @@ void cg_part(PairCoef<double>& k, double e, double s, int wrt, double rso, doubl
     k.cg_c6 = power_term(24.0, e, s, 6, wrt);
     k.cg_e12 = power_term(4.0, e, s, 12, wrt);
     k.cg_e6 = power_term(4.0, e, s, 6, wrt);
-    double g[5];
-    switch_on(lj3_wrt(e, s, rso, wrt), Ds, g);
-    k.sp_g0 = g[0];
-    k.sp_g3 = g[3];
-    k.sp_g4 = g[4];
-    switch_off(lj3_wrt(e, s, rci, wrt), Dc, k.cm_g);
-    k.sp_shift = poly_at(k.cm_g, Dc);
-    k.cm_shift = no_shift ? 0.0 : k.sp_shift;
+    switch_on(lj3_wrt(e, s, rso, wrt), Ds, k.sp);
+    k.sp[1] = k.sp[2] = 0.0;
+    switch_off(lj3_wrt(e, s, rci, wrt), Dc, k.cm);
+    k.sp[5] = poly_at(k.cm, Dc);
+    k.cm[5] = no_shift ? 0.0 : k.sp[5];
 }
 
 // Distances of one type pair with their squares.
@@ -495,9 +492,15 @@ int upload_tables(relres_ctx* c)
     for (size_t q = 0; q < np; ++q) {
         double* t = &back[q * kBackTab];
         for (int k = 0; k < 4; ++k) {
-            const double* rec = reinterpret_cast<const double*>(&c->coef_grad[k * np + q]);
-            if (k < 2) std::copy(rec, rec + kFgFields, t + (k == 0 ? kTabFgE : kTabFgS));
-            else std::copy(rec + kFgFields, rec + kFgFields + kCgFields, t + (k == 2 ? kTabCgE : kTabCgS));
+            const PairCoef<double>& r = c->coef_grad[k * np + q];
+            const double* rec = &r.fg_c12;
+            if (k < 2) {
+                std::copy(rec, rec + kFgFields, t + (k == 0 ? kTabFgE : kTabFgS));
+                continue;
+            }
+            const double cg[kCgFields] = {r.cg_c12, r.cg_c6, r.cg_e12, r.cg_e6, r.sp[0], r.sp[3], r.sp[4],
+                                          r.cm[0], r.cm[1], r.cm[2], r.cm[3], r.cm[4], r.cm[5], r.sp[5]};
+            std::copy(cg, cg + kCgFields, t + (k == 2 ? kTabCgE : kTabCgS));
         }
         t[kTabEps] = c->pair_eps[2 * q];
         t[kTabEps + 1] = c->pair_eps[2 * q + 1];

@@ -36,10 +36,10 @@ struct PairCoef {
     S fg_g[5];          // f_s-^FG coefficients gamma_0- .. gamma_4-
     S fg_shift;         // f_s-^FG(Dr_s)
     S cg_c12, cg_c6, cg_e12, cg_e6;
-    S sp_g0, sp_g3, sp_g4;  // f_s+^CG: gamma_0+, gamma_3+, gamma_4+ (gamma_1+ = gamma_2+ = 0)
-    S cm_g[5];          // f_c-^CG coefficients
-    S cm_shift;         // Gamma_c-' (cases 3-4 of Eq. 20)
-    S sp_shift;         // Gamma_c- (cases 1-2, inside Gamma_s+-)
+    // the two quartic zones of the CG part, alike, so that one code serves both:
+    // gamma_0 .. gamma_4 and the shift taken off
+    S sp[6];            // f_s+^CG (gamma_1+ = gamma_2+ = 0), Gamma_c- (cases 1-2, inside Gamma_s+-)
+    S cm[6];            // f_c-^CG, Gamma_c-' (cases 3-4 of Eq. 20)
 };
 
 template <typename S>
@@ -259,11 +259,11 @@ hipError_t launch_list_stats(GridDev* grids_dev, int ngrids, int most_rows, Stat
 // The adjoint's table, kBackTab doubles per type pair: the FG fields of the
 // eps and the sigma derivative records, the CG fields of both, eps_FG, eps_CG,
 // and the pair's distances (Cutoffs).
-constexpr int kFgFields = 10, kCgFields = 14;       // PairCoef's fields, FG first
+constexpr int kFgFields = 10, kCgFields = 14;       // of a record; CG without the zeros
 constexpr int kTabFgE = 0, kTabFgS = kFgFields, kTabCgE = 2 * kFgFields,
               kTabCgS = kTabCgE + kCgFields, kTabEps = kTabCgS + kCgFields,
               kTabCut = kTabEps + 2, kBackTab = kTabCut + 8;
-static_assert(sizeof(PairCoef<double>) == sizeof(double) * (kFgFields + kCgFields), "PairCoef");
+static_assert(sizeof(PairCoef<double>) == sizeof(double) * (kFgFields + kCgFields + 2), "PairCoef");
 static_assert(kBackTab % 2 == 0, "the table is copied two doubles at a time");
 // Backward (adjoint) pass: ForceArgs (positions, lists) plus
 struct BackArgs {

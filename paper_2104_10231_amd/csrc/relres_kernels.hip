@@ -1402,17 +1402,22 @@ __global__ __launch_bounds__(256) void k_list_stats(const GridDev* __restrict__ 
 // Coefficient table staged in LDS when it is small (ntypes <= kLdsTypes).
 constexpr int kLdsTypes = 8;
 
+// FP32 launches with energy and virial (Mixed) evaluate every term in FP64 and
+// read the FP64 table only.
+template <typename S, bool EW>
+constexpr bool kMixed = EW && sizeof(S) != sizeof(double);
+
 template <typename S, bool EW>
 struct CoefLds {
-    PairCoef<S> c[kLdsTypes * kLdsTypes];
-    PairCoef<double> c64[(EW && sizeof(S) != sizeof(double)) ? kLdsTypes * kLdsTypes : 1];
+    PairCoef<S> c[kMixed<S, EW> ? 1 : kLdsTypes * kLdsTypes];
+    PairCoef<double> c64[kMixed<S, EW> ? kLdsTypes * kLdsTypes : 1];
 };
 
 // Distances per type pair, staged when they are not uniform (PC).
-template <typename S, bool PC>
+template <typename S, bool EW, bool PC>
 struct CutLds {
-    Cutoffs<S> c[PC ? kLdsTypes * kLdsTypes : 1];
-    Cutoffs<double> c64[(PC && sizeof(S) != sizeof(double)) ? kLdsTypes * kLdsTypes : 1];
+    Cutoffs<S> c[PC && !kMixed<S, EW> ? kLdsTypes * kLdsTypes : 1];
+    Cutoffs<double> c64[PC && sizeof(S) != sizeof(double) ? kLdsTypes * kLdsTypes : 1];
 };
 
 // The coefficient and distance rows of one row atom's type: pair-math
@@ -1529,25 +1534,24 @@ __device__ __forceinline__ void entry_terms(const BoxV& bx, const RowTab<S>& t,
         double fpd, end;
         if constexpr (CG) cg_term<M>(t.c64[tj], cut64, r2d, fpd, end);
         else fg_term<M>(t.c64[tj], cut64, r2d, fpd, end);
+        const double gx = fpd * dx, gy = fpd * dy, gz = fpd * dz;
         if constexpr (sizeof(TF) == sizeof(double)) {
-            fx += fpd * dx;
-            fy += fpd * dy;
-            fz += fpd * dz;
+            fx = fma(fpd, dx, fx);     // no rounding of the product
+            fy = fma(fpd, dy, fy);
+            fz = fma(fpd, dz, fz);
         } else {
-            const float fp = (float)fpd;
-            fx += fp * (float)dx;
-            fy += fp * (float)dy;
-            fz += fp * (float)dz;
+            fx += (float)gx;
+            fy += (float)gy;
+            fz += (float)gz;
         }
-        if constexpr (EW) {
-            const double hf = 0.5 * fpd;
-            acc[CG ? 1 : 0] += 0.5 * end;
-            acc[2] += hf * dx * dx;
-            acc[3] += hf * dy * dy;
-            acc[4] += hf * dz * dz;
-            acc[5] += hf * dx * dy;
-            acc[6] += hf * dx * dz;
-            acc[7] += hf * dy * dz;
+        if constexpr (EW) {            // twice the sums: halved at the end
+            acc[CG ? 1 : 0] += end;
+            acc[2] += gx * dx;
+            acc[3] += gy * dy;
+            acc[4] += gz * dz;
+            acc[5] += gx * dy;
+            acc[6] += gx * dz;
+            acc[7] += gy * dz;
         }
     } else {
         float fp, en;
@@ -1823,12 +1827,13 @@ __device__ __forceinline__ void kick_read(const MdKick& k, int i, int c, double&
 // for their list entries and gathers, and 80 registers against 87 (5 waves)
 // took the energy/virial launch of 256 replicas from 214.6 to 203.0 us, of the
 // 98304-atom copolymer from 22.1 to 19.3, of 80000 atoms at 14 A from 62.5 to
-// 58.9 (72 and 64 registers spill: no faster, and 30 to 70 % slower).
+// 58.9 (72 and 64 registers spill: no faster, and 30 to 70 % slower).  Energy and
+// virial with distances per type pair read from memory need 90.
 // Kick: the half kick of a dynamics step follows.  What it needs is read under
 // the pair terms, in launches with energy and virial (no registers left for it)
 // after them.
 template <typename S, typename TF, bool EW, bool LDS, bool PC, int B, bool Kick>
-__global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces(
+__global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : EW && PC && !LDS ? 5 : 6) void k_forces(
     ForceArgs a, Cutoffs<S> cut, Cutoffs<double> cut64)
 {
     const bool rb = (int)blockIdx.x >= a.blocks_a;
@@ -1865,11 +1870,10 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces
     const int np = a.ntypes * a.ntypes;
     uint32_t stg[4] = {0u, 0u, 0u, 0u};
     if constexpr (LDS) {
-        stg[0] = stage_first(coef_g, np);
-        if constexpr (EW && sizeof(S) != sizeof(double))
-            stg[1] = stage_first((const PairCoef<double>*)a.coef64, np);
+        if constexpr (kMixed<S, EW>) stg[1] = stage_first((const PairCoef<double>*)a.coef64, np);
+        else stg[0] = stage_first(coef_g, np);
         if constexpr (PC) {
-            stg[2] = stage_first(pcut_g, np);
+            if constexpr (!kMixed<S, EW>) stg[2] = stage_first(pcut_g, np);
             if constexpr (sizeof(S) != sizeof(double)) stg[3] = stage_first(a.pcut64, np);
         }
     }
@@ -1927,17 +1931,18 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces
     const Cutoffs<double>* pcut64 = nullptr;
     if constexpr (LDS) {
         __shared__ CoefLds<S, EW> tab;
-        __shared__ CutLds<S, PC> ctab;
-        stage_table(tab.c, coef_g, np, stg[0]);
-        if constexpr (EW && sizeof(S) != sizeof(double))
+        __shared__ CutLds<S, EW, PC> ctab;
+        if constexpr (kMixed<S, EW>)
             stage_table(tab.c64, (const PairCoef<double>*)a.coef64, np, stg[1]);
+        else
+            stage_table(tab.c, coef_g, np, stg[0]);
         if constexpr (PC) {
-            stage_table(ctab.c, pcut_g, np, stg[2]);
+            if constexpr (!kMixed<S, EW>) stage_table(ctab.c, pcut_g, np, stg[2]);
             if constexpr (sizeof(S) != sizeof(double)) stage_table(ctab.c64, a.pcut64, np, stg[3]);
         }
         __syncthreads();
         coef = tab.c;
-        if constexpr (EW && sizeof(S) != sizeof(double)) coef64 = tab.c64;
+        if constexpr (kMixed<S, EW>) coef64 = tab.c64;
         else coef64 = (const PairCoef<double>*)tab.c;
         if constexpr (PC) {
             pcut = ctab.c;
@@ -2038,6 +2043,8 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : 6) void k_forces
         F[3 * rec.x + 2] = fz;
     }
     if constexpr (EW) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] *= 0.5;
         if (a.nsys == 1) {
             ew_finish(a, acc, tag);
         } else {
