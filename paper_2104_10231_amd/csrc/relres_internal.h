@@ -358,7 +358,7 @@ struct MdArgs {
     double* xref;                     // positions at the last list build
     double half_skin2;                // (skin / 2)^2
     unsigned int* stale;              // Status::md_stale
-    double* partial;                  // per block kinetic partial
+    double* partial;                  // kinetic partials (k_md_kinetic's or the force launch's)
     MdState* st;
 };
 // Drift of one step; with scalar != 0 every block first does the scalar work
@@ -391,9 +391,9 @@ hipError_t launch_md_finish(const MdArgs& m, hipStream_t s);
 // Row record field y: atom type in the low kTypeBits bits, system above.
 constexpr int kTypeBits = 5;
 constexpr int kRowsPerWave = 16;      // most home rows per wave of the list kernel
-constexpr int kEwLogGroups = 4;
-constexpr int kEwGroups = 1 << kEwLogGroups;        // energy/virial record groups (blocks b % 16; two per
+constexpr int kEwLogGroups = 4;      // energy/virial record groups (blocks b % 16; two per
                                       // XCD under the round-robin dispatch to 8 XCDs)
+constexpr int kEwGroups = 1 << kEwLogGroups;
 constexpr int kEwRecBytes = 128;     // one energy/virial record: 16 tagged 64-bit words
 constexpr int kForceBlock = 256;
 constexpr int kListBlock = 256;

@@ -1,22 +1,25 @@
 // relres_kernels.hip -- gfx950 kernels of the RelRes Lennard-Jones hot path.
 //
-// Build (every rebuild):  k_bin -> k_scan -> k_scatter -> k_cellsort -> k_lists
+// Build (every rebuild):  k_bin -> k_place -> k_lists_wave
 //   Two cell grids are built side by side: the atom grid (cells >= r_s+ + skin,
 //   all atoms) and the site grid (cells >= r_c+ + skin, hybrid atoms only).
 //   Cells are numbered in Morton order so that neighbouring cells, and the
 //   atoms they hold, sit close together in memory.  Within a cell, members are
-//   ordered by caller index, which makes every list row deterministic.
-//   k_lists stages the candidate atoms of the deduplicated 27-cell stencil in
-//   LDS, one wave tests 64 candidates of one home atom at a time and appends
-//   the survivors to that atom's row with a ballot + mbcnt prefix.
+//   ordered by caller index, which makes every list row deterministic.  k_bin
+//   files the members into buckets of their cells and k_place puts them into
+//   cell order (more than 8192 cells: k_place_totals first); crowded or sparse
+//   grids take k_scan -> k_scatter -> k_cellsort instead.
+//   A wave of k_lists_wave takes a few home rows, tests 64 candidates of their
+//   cells' stencils at a time and appends the survivors to each row with a
+//   ballot + mbcnt prefix.
 // Forces (every call): k_forces
 //   One launch covers both lists.  Rows of ordinary atoms take the FG part over
 //   their atom-list row; rows of hybrid atoms take the FG part over their
 //   atom-list row plus the CG part over their site-list row.  Each row is owned
 //   by a group of lanes that accumulate its force in registers and reduce it
 //   with cross-lane shuffles, so no force atomics are needed.  Energy and
-//   virial are accumulated in FP64 and reduced in a fixed order by the last
-//   block to finish.
+//   virial are accumulated in FP64 and reduced in a fixed order by the blocks
+//   of highest number.
 #include "relres_internal.h"
 #include "relres_pair.h"
 #include "relres_lanes.h"
