@@ -402,9 +402,10 @@ int relres_bonded_forces(relres_ctx *ctx, const double *pos, void *forces, doubl
  * around v += dt/2 a; x += dt v; forces; v += dt/2 a.
  * masses: host double[n] (caller order); dt, tau: time unit of the caller;
  * kT: energy unit; ftm2v converts force / mass to acceleration (4.184e-4 for
- * kcal/mol, A, amu and fs).  The lists are rebuilt every rebuild_every steps
- * (waiting for each build); if an atom moved more than half the skin since
- * the previous build, relres_md_run fails with RELRES_ERR_STALE_LISTS.
+ * kcal/mol, A, amu and fs).  The lists are rebuilt every rebuild_every steps;
+ * if an atom moved more than half the skin since the previous build, also in
+ * a run that ends before the next, relres_md_run fails with
+ * RELRES_ERR_STALE_LISTS.
  * Resets the thermostat to xi = eta = 0.                                   */
 int relres_md_setup(relres_ctx *ctx, const double *masses, double dt, double kT, double tau,
                     double ftm2v, int rebuild_every);

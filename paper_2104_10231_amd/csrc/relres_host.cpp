@@ -376,7 +376,6 @@ struct relres_ctx {
     int md_rebuild = 10;
     int md_cur = 0;                   // which of the two state buffers is current
     DBuf d_mass, d_md_state, d_md_xref, d_md_vsave, d_md_Fb, d_md_F, d_md_E, d_md_W, d_md_part;
-    unsigned md_stale_seen = 0;       // Status::md_stale when a run last looked at it
 
     bool timing = false;
     std::vector<hipEvent_t> ev_free;
@@ -2570,14 +2569,15 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
     };
 
     // The run goes from list build to list build without waiting for them: a
-    // build's status is examined when the next one is due (by then it is
-    // there) and once more at the end.  Before each build the positions,
+    // build's status is examined when the next one is due or the last step is
+    // enqueued (by then it is there).  Before each build the positions,
     // velocities and thermostat state are saved on the device, so when a row
     // turns out to have overflowed (its forces were short) the run goes back to
-    // that build with grown rows.  A wait at every build left the GPU idle for
-    // about 25 us each time.
+    // that build with grown rows.  Against a wait at every build, builds every
+    // ten steps take 0.7 us a step less at 6000 atoms and 1.1 us at 48000.
     int mark = 0, mark_cur = c->md_cur;    // step and state buffer of the last build
     bool first = true;                     // no displacements to check before its status
+    unsigned stale_seen = 0;               // Status::md_stale at the last build
     // saves the run's state at step `step` (its drift done) and builds there
     auto build = [&](int step) -> int {
         mark = step;
@@ -2586,17 +2586,20 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
         if (c->lanes_stale) return build_checked(c, pos, box, s);
         return enqueue_build(c, pos, box, s);
     };
-    // examines the last build and the displacements up to its status;
+    const auto stale = [] {
+        return fail(RELRES_ERR_STALE_LISTS, "an atom moved more than half the skin between list "
+                    "builds: rebuild more often or use a larger skin");
+    };
+    // examines the last build and the displacements up to it, from the status
+    // copied with it (a later one holds steps that may have to be repeated);
     // RELRES_ERR_LIST_RETRY: go back to it
     auto confirm = [&]() -> int {
         const int rc = examine_status(c);
         c->warn_pending = false;           // dynamics checks the displacements itself
         if (rc != RELRES_OK && rc != RELRES_ERR_LIST_RETRY) return rc;
         const unsigned seen = c->h_status->md_stale;
-        if (!first && seen != c->md_stale_seen)
-            return fail(RELRES_ERR_STALE_LISTS, "an atom moved more than half the skin between list "
-                        "builds: rebuild more often or use a larger skin");
-        c->md_stale_seen = seen;
+        if (!first && seen != stale_seen) return stale();
+        stale_seen = seen;
         first = false;
         return rc;
     };
@@ -2679,10 +2682,11 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
             HIP_TRY(launch_md_scalar(m.st, m.partial, nparts, m.ftm2v, 1, 0, e_nb, w_nb, eb,
                                      row_of(nsteps), s));
         HIP_TRY(launch_md_finish(m, s));
+        TRY(confirm());
         // the last steps since the previous build must not have outrun the skin either
         HIP_TRY(hipMemcpyAsync(c->h_status, c->d_status.p, sizeof(Status), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
-        return confirm();
+        return c->h_status->md_stale != stale_seen ? stale() : RELRES_OK;
     };
     auto run = [&]() -> int {
         TRY(drain_check(c));
