@@ -424,7 +424,11 @@ int relres_md_state(relres_ctx *ctx, double *xi, double *eta, int set);
  * energy K + U + Q xi^2/2 + g kT eta (conserved by the integrator), and the
  * trace of the virial.  Enqueued on `stream`; at every list build it waits for
  * the status of the build before, and at the end for the run.  When a row of a
- * build overflowed, the run goes back to that build with grown rows.        */
+ * build overflowed, the run goes back to that build with grown rows.  An error
+ * of a build (non-finite positions, stale lists before it) leaves positions,
+ * velocities and thermostat as they were at that build; rows of thermo past it
+ * are then undefined.  Stale lists after the last build leave those of the last
+ * step.                                                                     */
 int relres_md_run(relres_ctx *ctx, double *pos, double *vel, int nsteps, int thermo_every,
                   double *thermo, void *stream);
 

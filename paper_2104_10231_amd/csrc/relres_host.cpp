@@ -2574,7 +2574,10 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
     // velocities and thermostat state are saved on the device, so when a row
     // turns out to have overflowed (its forces were short) the run goes back to
     // that build with grown rows.  Against a wait at every build, builds every
-    // ten steps take 0.7 us a step less at 6000 atoms and 1.1 us at 48000.
+    // ten steps take 0.7 us a step less at 6000 atoms and 1.1 us at 48000.  An
+    // error found in a build's status returns to that build too, so that it
+    // leaves what a wait there would have left: nothing integrated past it.
+    bool marked = false, ended = false;    // a state is saved; all steps are done and examined
     int mark = 0, mark_cur = c->md_cur;    // step and state buffer of the last build
     bool first = true;                     // no displacements to check before its status
     unsigned stale_seen = 0;               // Status::md_stale at the last build
@@ -2583,6 +2586,7 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
         mark = step;
         mark_cur = c->md_cur;
         HIP_TRY(launch_md_mark(m, vsave, stb + 2, s));
+        marked = true;
         if (c->lanes_stale) return build_checked(c, pos, box, s);
         return enqueue_build(c, pos, box, s);
     };
@@ -2683,6 +2687,7 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
                                      row_of(nsteps), s));
         HIP_TRY(launch_md_finish(m, s));
         TRY(confirm());
+        ended = true;
         // the last steps since the previous build must not have outrun the skin either
         HIP_TRY(hipMemcpyAsync(c->h_status, c->d_status.p, sizeof(Status), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
@@ -2704,7 +2709,14 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
         return rc;
     };
     const int rc = run();
-    if (rc != RELRES_OK) (void)hipStreamSynchronize(s);   // nothing of the run is left behind an error
+    if (rc != RELRES_OK) {
+        if (marked && !ended) {
+            const std::string why = g_last_error;
+            (void)go_back();
+            g_last_error = why;
+        }
+        (void)hipStreamSynchronize(s);     // nothing of the run is left behind an error
+    }
     return rc;
 }
 

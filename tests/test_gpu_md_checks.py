@@ -99,3 +99,47 @@ def test_steps_after_an_overflowed_build(oscillator, steps):
         rr.close()
     assert res[0][2] == 0 and res[1][2] >= 1
     assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
+
+
+def _bits(t):
+    return t.cpu().numpy().view(np.int64)
+
+
+@pytest.mark.parametrize("steps", [3, 25])
+def test_nonfinite_positions_leave_the_run_untouched(steps):
+    """Refused by the first build's status, which is read after steps were
+    enqueued behind it: positions, velocities and thermostat are the caller's."""
+    import torch
+    from paper_2104_10231_amd.relres import RelResError
+    s = _hexane(n_mol=80, seed=5)
+    print(f"[md] non-finite position, {steps} steps", flush=True)
+    rr, p = _ctx(s)
+    rr.md_setup(s.bonded["masses"], 1.0, 300.0, 100.0, rebuild_every=10)
+    rr.md_state(1e-4, 2e-3)
+    p[17, 1] = float("nan")
+    v = torch.from_numpy(np.ascontiguousarray(s.bonded["velocities"])).cuda()
+    before = _bits(p), _bits(v)
+    with pytest.raises(RelResError) as e:
+        rr.md_run(p, v, steps)
+    assert "non-finite" in str(e.value)
+    assert np.array_equal(_bits(p), before[0]) and np.array_equal(_bits(v), before[1])
+    assert rr.md_state() == (1e-4, 2e-3)
+    rr.close()
+
+
+def test_stale_lists_leave_the_build_that_found_them():
+    """Atoms outrun the skin in the first five steps: with builds every five, a
+    run of 20 steps ends where the build at step five found it, as a run of
+    five does."""
+    import torch
+    s = _hexane(n_mol=60, seed=5).replace(skin=0.02)
+    res = []
+    for steps in (5, 20):
+        print(f"[md] stale at step 5 of {steps}", flush=True)
+        rr, p = _ctx(s)
+        v = torch.from_numpy(np.ascontiguousarray(s.bonded["velocities"])).cuda()
+        rr.md_setup(s.bonded["masses"], 1.0, 300.0, 100.0, rebuild_every=5)
+        _stale(lambda: rr.md_run(p, v, steps))
+        res.append(_bits(p))
+        rr.close()
+    assert np.array_equal(*res)
