@@ -330,7 +330,7 @@ struct relres_ctx {
     bool grids_valid = false;
     Status* h_status = nullptr;
     Status* h_query = nullptr;        // pinned landing place of relres_moved_atoms
-    int nonfinite_seen = 0;
+    unsigned nonfinite_seen = 0;
     unsigned moved_seen = 0;          // Status::moved at the last examination
     unsigned ew_failed_seen = 0;      // Status::ew_failed at the last examination
     int spin_limit = 1 << 22;         // polls before a cross-block energy/virial wait gives up

@@ -124,7 +124,7 @@ struct TopoDev {
 // seen, so max_row > capacity means a build since the last growth
 // overflowed); entries and longest are filled on demand by k_list_stats.
 struct Status {
-    int nonfinite;                  // cumulative count of non-finite positions seen
+    unsigned nonfinite;             // cumulative count of non-finite positions seen
     int max_row[2];                 // longest overflowing row per grid since creation, 0 if none
     int longest[2];                 // longest row per grid (k_list_stats)
     unsigned moved;                 // cumulative count, over builds, of atoms found more

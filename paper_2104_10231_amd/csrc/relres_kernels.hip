@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void k_bin(int n, const double* __restrict__ p
     const int base = G->cell_base, base_s = H->cell_base;
     const double half_skin2 = G->half_skin2;
     if (!(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]))) {
-        atomicOr(&st->nonfinite, 1);
+        count_wave(in, &st->nonfinite);
         x[0] = x[1] = x[2] = 0.0;
     }
     const bool hyb = topo.hybrid[ty] != 0 && in;
