@@ -528,9 +528,10 @@ __device__ __forceinline__ void drift_atom(const MdArgs& m, int i, bool in, doub
             const double dx = a.x[c] - a.xref[c];
             dmax2 += dx * dx;
         }
-    // an atom that moved more than half the skin since the last build
-    // invalidates the lists; the host checks the count with the next build's status
-    const uint64_t far = __ballot(dmax2 > m.half_skin2);
+    // an atom that moved more than half the skin since the last build (or whose
+    // position is no number: the comparison is false) invalidates the lists; the
+    // host checks the count with the next build's status
+    const uint64_t far = __ballot(!(dmax2 <= m.half_skin2));
     if (far != 0ull && ((int)threadIdx.x & 63) == __ffsll((long long)far) - 1) atomicAdd(m.stale, 1u);
 }
 

@@ -143,3 +143,18 @@ def test_stale_lists_leave_the_build_that_found_them():
         res.append(_bits(p))
         rr.close()
     assert np.array_equal(*res)
+
+
+@pytest.mark.parametrize("steps", [1, 25])
+def test_a_run_that_blows_up_is_reported(steps):
+    """A velocity that is no number: the atom's positions after the first step
+    are none either, before any build could see them (builds every 40)."""
+    import torch
+    s = _hexane(n_mol=80, seed=5)
+    print(f"[md] velocity NaN, {steps} steps", flush=True)
+    rr, p = _ctx(s)
+    rr.md_setup(s.bonded["masses"], 1.0, 300.0, 1e9, rebuild_every=40)
+    v = torch.from_numpy(np.ascontiguousarray(s.bonded["velocities"])).cuda()
+    v[s.n - 1, 2] = float("nan")
+    _stale(lambda: rr.md_run(p, v, steps))
+    rr.close()
