@@ -953,33 +953,51 @@ int refresh_list_stats(relres_ctx* c, hipStream_t s)
     st.site_entries = (c->n && sites) ? (long long)c->h_status->entries[1] : 0;
     st.atom_max_row = c->n ? c->h_status->longest[0] : 0;
     st.site_max_row = (c->n && sites) ? c->h_status->longest[1] : 0;
-    // Automatic lanes per row: about E list entries per lane.  A launch that
-    // fits the machine a few times over is latency-bound: E = 4, lanes rounded
-    // up to a power of two (short chains per lane).  A larger one is bound by
-    // issue and by reads in flight, and its per-row work (record, reductions
-    // across the row's lanes) shrinks with fewer lanes: E = 8, the nearest
-    // power of two.  Force launch with energy and virial at E = 4 up / 8
-    // nearest: 20480-atom liquid (2304 waves at E = 4) 9.0 / 9.8 us;
-    // 20480 atoms at 14 A (10240) 18.2 / 15.9; 98304-atom copolymer (12288)
-    // 21.0 / 18.8; 48000-atom hexane (14000) 23.5 / 21.1; 80000 atoms at 14 A
-    // (40000) 57.2 / 47.0; 256 replicas (231000) 264 / 198.  Forces only, the
-    // last takes 146 us with 4 / 16 lanes (E = 4, no sums over the wave)
-    // against 168 with 2 / 8; the others are alike.
+    // Automatic lanes per row: about E list entries per lane.
+    //
+    // A launch that fits the machine a few times over (8192 waves at E = 4) is
+    // latency-bound: E = 4, rounded up to a power of two (short chains per
+    // lane).  Above that:
+    //
+    // Launches with energy or virial are bound by issue, and each wave has its
+    // sums over the lanes: E = 8, the nearest power of two.  At E = 4 up / 8
+    // nearest: 20480 atoms at 14 A (10240 waves) 18.2 / 15.9; 98304-atom
+    // copolymer (12288) 21.0 / 18.8; 48000-atom hexane (14000) 23.5 / 21.1; 80000
+    // atoms at 14 A (40000) 57.2 / 47.0; 256 replicas (231000) 264 / 198.
+    //
+    // Forces only, a wave ends with three sums, and fewer lanes only lengthen
+    // the rows' chains: E = 8, rounded up (to the nearest above 16 lanes: 80000
+    // atoms at 14 A 33.5 / 35.1 us at 16 / 32).  Copolymer of 98304 atoms, sparse
+    // (10.4 and 34.7 entries): 2 / 8 lanes 11.2 us, 1 / 4 13.8; of 75000 9.4
+    // and 12.2; neopentane of 200000 19.5 and 24.9; hexane of 98304 (21.4 and
+    // 71) 4 / 16 lanes 18.4 us, 2 / 16 19.8.  Where these lanes fill the chip
+    // twice over (12288 waves at 6 per SIMD) atom rows of 10 entries take 4:
+    // neopentane of 400000 atoms 30.4 us, 33.2 with 2, propane of 200000 26.8
+    // and 29.5; copolymer of 98304 atoms, 6144 waves, the other way round: 12.1
+    // with 4 and 11.2 with 2.
     const double avg_a = c->n ? (double)st.atom_entries / c->n : 0.0;
     const double avg_s = c->n_sites ? (double)st.site_entries / c->n_sites : 0.0;
-    const long long waves4 =
-        ((long long)c->n * next_pow2_clamped(avg_a / 4.0, 1, 32) +
-         (long long)c->n_sites * next_pow2_clamped((avg_a + avg_s) / 4.0, 1, 64)) / 64;
+    const double row[2] = {avg_a, avg_a + avg_s};
+    const int most[2] = {32, 64};
+    const auto waves = [&](const int* lanes) {
+        return ((long long)c->n * lanes[0] + (long long)c->n_sites * lanes[1]) / 64;
+    };
+    int up4[2];
+    for (int k = 0; k < 2; ++k) up4[k] = next_pow2_clamped(row[k] / 4.0, 1, most[k]);
+    const long long waves4 = waves(up4);
     for (int ew = 0; ew < 2; ++ew) {
         int* lanes = c->auto_lanes[ew];
-        if (waves4 <= 8192) {
-            lanes[0] = next_pow2_clamped(avg_a / 4.0, 1, 32);
-            lanes[1] = next_pow2_clamped((avg_a + avg_s) / 4.0, 1, 64);
-        } else {
-            const double e = !ew && waves4 > 65536 ? 4.0 : 8.0;
-            lanes[0] = nearest_pow2_clamped(avg_a / e, 1, 32);
-            lanes[1] = nearest_pow2_clamped((avg_a + avg_s) / e, 1, 64);
+        for (int k = 0; k < 2; ++k) {
+            if (waves4 <= 8192) {
+                lanes[k] = up4[k];
+            } else if (ew) {
+                lanes[k] = nearest_pow2_clamped(row[k] / 8.0, 1, most[k]);
+            } else {
+                lanes[k] = next_pow2_clamped(row[k] / 8.0, 1, most[k]);
+                if (lanes[k] > 16) lanes[k] = nearest_pow2_clamped(row[k] / 8.0, 1, most[k]);
+            }
         }
+        if (!ew && waves4 > 8192 && avg_a >= 10.0 && lanes[0] < 4 && waves(lanes) > 12288) lanes[0] = 4;
     }
     c->stats_fresh = true;
     return wave_tables(c);
