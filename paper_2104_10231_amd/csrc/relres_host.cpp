@@ -960,10 +960,16 @@ int refresh_list_stats(relres_ctx* c, hipStream_t s)
     // lane).  Above that:
     //
     // Launches with energy or virial are bound by issue, and each wave has its
-    // sums over the lanes: E = 8, the nearest power of two.  At E = 4 up / 8
-    // nearest: 20480 atoms at 14 A (10240 waves) 18.2 / 15.9; 98304-atom
-    // copolymer (12288) 21.0 / 18.8; 48000-atom hexane (14000) 23.5 / 21.1; 80000
-    // atoms at 14 A (40000) 57.2 / 47.0; 256 replicas (231000) 264 / 198.
+    // sums over the lanes: E = 8, above 65536 waves 12, the nearest power of
+    // two, but not one lane for rows of 8 entries nor 4 for hybrid rows of 32,
+    // whose many rounds wait one on the other.  At these rules / E = 8 rounded
+    // up: 80000 atoms at 14 A 47.0 / 57.2 us, 48000-atom hexane 21.1 / 23.5,
+    // 256 replicas 198 / 264; with the lower bounds / without: neopentane
+    // at 200000 atoms (10.9 and 26.9 entries per atom and site row) 26.5 / 31.6,
+    // at 400000 44.2 / 56.2, copolymer at 400000 51.9 / 58.7; with E = 12 / 8:
+    // hexane at 400000 atoms 81.7 / 89.1.  A launch of one system whose blocks
+    // would outgrow the records of relres_forces_noalloc takes E = 16, rounded
+    // up, half the lanes of the bounds.
     //
     // Forces only, a wave ends with three sums, and fewer lanes only lengthen
     // the rows' chains: E = 8, rounded up (to the nearest above 16 lanes: 80000
@@ -991,12 +997,17 @@ int refresh_list_stats(relres_ctx* c, hipStream_t s)
             if (waves4 <= 8192) {
                 lanes[k] = up4[k];
             } else if (ew) {
-                lanes[k] = nearest_pow2_clamped(row[k] / 8.0, 1, most[k]);
+                lanes[k] = nearest_pow2_clamped(row[k] / (waves4 > 65536 ? 12.0 : 8.0), 1, most[k]);
+                const int least = k == 0 ? 2 : 8;
+                if (row[k] >= 4.0 * least) lanes[k] = std::max(lanes[k], least);
             } else {
                 lanes[k] = next_pow2_clamped(row[k] / 8.0, 1, most[k]);
                 if (lanes[k] > 16) lanes[k] = nearest_pow2_clamped(row[k] / 8.0, 1, most[k]);
             }
         }
+        const long long records = (long long)((kScratchBytes - kScratchEpochBytes) / kEwRecBytes);
+        if (ew && waves4 > 65536 && c->nsys == 1 && waves(lanes) / (kForceBlock / 64) + 16 + kEwGroups > records)
+            for (int k = 0; k < 2; ++k) lanes[k] = next_pow2_clamped(row[k] / 16.0, 1, most[k]);
         if (!ew && waves4 > 8192 && avg_a >= 10.0 && lanes[0] < 4 && waves(lanes) > 12288) lanes[0] = 4;
     }
     c->stats_fresh = true;
