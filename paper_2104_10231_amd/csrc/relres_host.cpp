@@ -310,14 +310,9 @@ struct relres_ctx {
     std::vector<double> boxes_dev;    // [nsys][6] as uploaded
     DBuf d_boxes, d_wave_ew;
     // rows of the force launch's waves with several systems, for every lane
-    // count in use (ForceArgs::waves_tab, sys_wave): [kind][log2 lanes].  A
-    // table is written once for a set of systems, so that a captured launch
-    // keeps the one it was captured with.
-    struct WaveTab {
-        DBuf waves, first;
-        int n = 0;
-        bool valid = false;
-    } wave_tab[2][7];
+    // count (ForceArgs::waves_tab, sys_wave): [kind][log2 lanes]
+    DBuf d_wave_tab, d_sys_wave;
+    WaveTabs wave_tabs{};
     int same_mol = 0;
     bool has_excl = false;
     int max_excl = 0;
@@ -903,38 +898,41 @@ int force_lanes(const relres_ctx* c, int kind, bool ew)
     return set ? set : c->auto_lanes[ew ? 1 : 0][kind];
 }
 
-// The wave tables of the current lane counts (several systems): a wave takes
-// 64 / lanes consecutive rows of one system.  Called wherever the systems or
-// the lane counts change, so that force calls only pass them on.
+// The wave tables of several systems: a wave takes 64 / lanes consecutive rows
+// of one system.  They are made for every lane count when the systems are set
+// (32 bytes per row in all), so that lane counts can change under capture and
+// in calls that must not allocate.
 int wave_tables(relres_ctx* c)
 {
-    if (c->nsys == 1) return RELRES_OK;
-    for (int q = 0; q < 4; ++q) {
-        const int kind = q & 1;
+    WaveTabs& t = c->wave_tabs;
+    const int stride = c->nsys + 1;
+    t.nsys = c->nsys;
+    // rows of every kind before each system, then per kind and lane count the
+    // waves before each system
+    std::vector<int> first((size_t)(2 + 2 * kLaneCounts) * stride, 0);
+    size_t entries = 0;
+    for (int kind = 0; kind < 2; ++kind) {
         const std::vector<int>& members = kind == 0 ? c->atoms_sys : c->sites_sys;
-        const int lanes = force_lanes(c, kind, q >= 2), per = 64 / lanes;
-        relres_ctx::WaveTab& t = c->wave_tab[kind][log2i(lanes)];
-        if (t.valid) continue;
-        std::vector<int4> waves;
-        std::vector<int> first;
-        int row = 0;
-        for (int sy = 0; sy < c->nsys; ++sy) {
-            first.push_back((int)waves.size());
-            for (int k = 0; k < members[sy]; k += per)
-                waves.push_back(make_int4(row + k, std::min(per, members[sy] - k), sy, 0));
-            row += members[sy];
+        int* rows = &first[(size_t)kind * stride];
+        for (int sy = 0; sy < c->nsys; ++sy) rows[sy + 1] = rows[sy] + members[sy];
+        for (int lg = 0; lg < kLaneCounts; ++lg) {
+            int* f = &first[(size_t)(2 + kind * kLaneCounts + lg) * stride];
+            const int per = 64 >> lg;
+            for (int sy = 0; sy < c->nsys; ++sy) f[sy + 1] = f[sy] + (members[sy] + per - 1) / per;
+            t.n[kind][lg] = f[c->nsys];
+            t.at[kind][lg] = entries;
+            entries += (size_t)f[c->nsys];
         }
-        first.push_back((int)waves.size());
-        TRY(ensure(t.waves, sizeof(int4) * waves.size(), &c->alloc_generation));
-        TRY(ensure(t.first, sizeof(int) * first.size(), &c->alloc_generation));
-        HIP_TRY(hipDeviceSynchronize());   // tables of earlier systems may still be in use
-        if (!waves.empty())
-            HIP_TRY(hipMemcpy(t.waves.p, waves.data(), sizeof(int4) * waves.size(), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(t.first.p, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice));
-        t.n = (int)waves.size();
-        t.valid = true;
-        ++c->alloc_generation;             // launches captured with an earlier table are stale
     }
+    TRY(ensure(c->d_wave_tab, sizeof(int4) * entries, &c->alloc_generation));
+    TRY(ensure(c->d_sys_wave, sizeof(int) * first.size(), &c->alloc_generation));
+    t.waves = c->d_wave_tab.as<int4>();
+    t.first = c->d_sys_wave.as<int>();
+    HIP_TRY(hipDeviceSynchronize());   // tables of earlier systems may still be in use
+    HIP_TRY(hipMemcpy(c->d_sys_wave.p, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice));
+    HIP_TRY(launch_wave_tables(t, nullptr));
+    HIP_TRY(hipDeviceSynchronize());   // calls on any stream read them
+    ++c->alloc_generation;             // launches captured with earlier systems are stale
     return RELRES_OK;
 }
 
@@ -1011,7 +1009,7 @@ int refresh_list_stats(relres_ctx* c, hipStream_t s)
         if (!ew && waves4 > 8192 && avg_a >= 10.0 && lanes[0] < 4 && waves(lanes) > 12288) lanes[0] = 4;
     }
     c->stats_fresh = true;
-    return wave_tables(c);
+    return RELRES_OK;
 }
 
 // List builder: groups of rows per wave.  One block per cell remains
@@ -1644,14 +1642,17 @@ int relres_set_systems(relres_ctx* c, int nsys, const int* atom_offsets)
         HIP_TRY(hipMemcpy(c->d_sys.p, sys.data(), sizeof(int) * c->n, hipMemcpyHostToDevice));
     }
     c->nsys = nsys;
-    for (auto& kind : c->wave_tab)
-        for (auto& t : kind) t.valid = false;
     c->skins.clear();                 // every system at the default skin
     c->sys_off = off;
     c->atoms_sys = atoms;
     c->sites_sys = sites;
     c->built = false;
     c->lanes_stale = true;
+    if (nsys > 1 && c->n > 0) {
+        c->topo_set = false;          // no force call without the tables
+        TRY(wave_tables(c));
+        c->topo_set = true;
+    }
     if (nsys > 1) {
         // bonded terms and dynamics are single-system
         c->has_bonded = false;
@@ -1744,7 +1745,7 @@ int relres_set_launch(relres_ctx* c, int lanes_atom, int lanes_site)
             return fail(RELRES_ERR_ARG, "lanes per row must be 0 (automatic) or a power of two <= 64");
     c->lanes_a = lanes_atom;
     c->lanes_b = lanes_site;
-    return c->topo_set ? wave_tables(c) : RELRES_OK;
+    return RELRES_OK;
 }
 
 int relres_set_list_launch(relres_ctx* c, int rows_atom, int rows_site, int cand_per_lane)
@@ -1910,8 +1911,8 @@ namespace {
 
 // Arguments of one force launch over the lists of the last build, with the
 // lane split of the context; energy/virial buffers are the caller's.
-int force_args(relres_ctx* c, const double* pos, void* forces, double* energy, double* virial,
-               ForceArgs& a)
+ForceArgs force_args(const relres_ctx* c, const double* pos, void* forces, double* energy,
+                     double* virial)
 {
     const bool sites = c->n_sites > 0;
     const bool ew = energy || virial;
@@ -1920,7 +1921,7 @@ int force_args(relres_ctx* c, const double* pos, void* forces, double* energy, d
         long long b = (rows * lanes + kForceBlock - 1) / kForceBlock;
         return (int)((b + 7) / 8 * 8);
     };
-    a = ForceArgs{};
+    ForceArgs a{};
     a.pos = pos;
     for (int k = 0; k < 3; ++k) {
         a.box[k] = c->box[k];
@@ -1961,17 +1962,17 @@ int force_args(relres_ctx* c, const double* pos, void* forces, double* energy, d
     const double avg_s = c->n_sites ? (double)c->stats.site_entries / c->n_sites : 0.0;
     a.wide_batch = c->n > 0 && avg_a >= 8.0 * la && (!sites || avg_a + avg_s >= 8.0 * lb);
     if (c->nsys > 1) {
-        TRY(wave_tables(c));               // there already, but for a changed override
+        const WaveTabs& t = c->wave_tabs;
         for (int kind = 0; kind < 2; ++kind) {
-            const relres_ctx::WaveTab& t = c->wave_tab[kind][log2i(kind == 0 ? la : lb)];
-            a.waves_tab[kind] = t.waves.as<int4>();
-            a.sys_wave[kind] = t.first.as<int>();
-            a.n_waves[kind] = t.n;
+            const int lg = kind == 0 ? a.log_lanes_a : a.log_lanes_b;
+            a.waves_tab[kind] = t.waves + t.at[kind][lg];
+            a.sys_wave[kind] = t.first + (size_t)(2 + kind * kLaneCounts + lg) * (t.nsys + 1);
+            a.n_waves[kind] = t.n[kind][lg];
         }
         a.blocks_a = blocks(a.n_waves[0], 64);
         a.blocks_b = sites ? blocks(a.n_waves[1], 64) : 0;
     }
-    return RELRES_OK;
+    return a;
 }
 
 }  // namespace
@@ -1983,8 +1984,7 @@ namespace {
 int enqueue_forces(relres_ctx* c, const double* pos, void* forces, double* energy, double* virial,
                    const MdKick* kick, int* nparts, hipStream_t s)
 {
-    ForceArgs a;
-    TRY(force_args(c, pos, forces, energy, virial, a));
+    ForceArgs a = force_args(c, pos, forces, energy, virial);
     if (kick) {
         a.kick = *kick;
         *nparts = a.blocks_a + a.blocks_b;
@@ -2062,8 +2062,7 @@ int relres_forces_noalloc(relres_ctx* c, const double* pos, void* forces, double
     if (!c->scratch)
         return fail(RELRES_ERR_HIP, "relres_forces_noalloc: no address for the static scratch "
                     "on device %d: %s", c->device, hipGetErrorString(c->scratch_err));
-    ForceArgs a;
-    TRY(force_args(c, pos, forces, energy, virial, a));
+    ForceArgs a = force_args(c, pos, forces, energy, virial);
     const size_t need = kScratchEpochBytes +
                         (size_t)kEwRecBytes * (size_t)(a.blocks_a + a.blocks_b + kEwGroups);
     if (ew && need > kScratchBytes)
@@ -2841,13 +2840,9 @@ void relres_destroy(relres_ctx* c)
 {
     if (!c) return;
     (void)hipDeviceSynchronize();
-    for (DBuf* b : {&c->d_back_tab, &c->d_bpartial, &c->d_sys, &c->d_boxes, &c->d_wave_ew})
+    for (DBuf* b : {&c->d_back_tab, &c->d_bpartial, &c->d_sys, &c->d_boxes, &c->d_wave_ew,
+                    &c->d_wave_tab, &c->d_sys_wave})
         release(*b);
-    for (auto& kind : c->wave_tab)
-        for (auto& t : kind) {
-            release(t.waves);
-            release(t.first);
-        }
     for (DBuf* b : {&c->d_bond_blocks, &c->d_bond_passes, &c->d_bond_terms, &c->d_term_par, &c->d_atom_slot,
                     &c->d_bond_part, &c->d_bond_sum,
                     &c->d_mass, &c->d_md_state, &c->d_md_xref,

@@ -288,6 +288,19 @@ hipError_t launch_clear_words(unsigned long long* p, size_t n, hipStream_t s);
 constexpr size_t kScratchBytes = RELRES_NOALLOC_SCRATCH_BYTES;
 constexpr size_t kScratchEpochBytes = 256;
 hipError_t scratch_address(void** out);
+// Wave tables of several systems for every lane count 2^lg of both kinds of
+// rows: entries at waves + at[kind][lg], n of them; first: rows before each
+// system of kind 0 and 1, then the waves before it of [kind][lg], nsys + 1 ints
+// each.
+constexpr int kLaneCounts = 7;        // 1 .. 64 lanes per row
+struct WaveTabs {
+    int4* waves;
+    const int* first;
+    int nsys;
+    int n[2][kLaneCounts];
+    size_t at[2][kLaneCounts];
+};
+hipError_t launch_wave_tables(const WaveTabs& t, hipStream_t s);
 hipError_t launch_zero_outputs(double* energy, double* virial, int nsys, hipStream_t s);
 // nsys > 1: energy/virial of each system from the wave sums
 hipError_t launch_reduce_sys_ew(const ForceArgs& a, double* energy, double* virial, hipStream_t s);

@@ -2062,6 +2062,28 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : EW && PC && !LDS
 }
 
 
+// The wave tables of several systems, one thread per entry, one grid row per
+// kind and lane count.
+__global__ __launch_bounds__(256) void k_wave_tables(WaveTabs t)
+{
+    const int kind = (int)blockIdx.y / kLaneCounts, lg = (int)blockIdx.y % kLaneCounts;
+    const int w = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (w >= t.n[kind][lg]) return;
+    const int stride = t.nsys + 1;
+    const int* rows = t.first + (size_t)kind * stride;
+    const int* first = t.first + (size_t)(2 + kind * kLaneCounts + lg) * stride;
+    // the last system whose waves start at or before w (systems without rows
+    // start where the next one does)
+    int lo = 0, hi = t.nsys - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (first[mid] <= w) lo = mid;
+        else hi = mid - 1;
+    }
+    const int row = rows[lo] + ((w - first[lo]) << (6 - lg));
+    t.waves[t.at[kind][lg] + w] = make_int4(row, min(kWave >> lg, rows[lo + 1] - row), lo, 0);
+}
+
 __global__ void k_zero_outputs(double* energy, double* virial, int nsys)
 {
     for (int t = threadIdx.x; t < 6 * nsys; t += blockDim.x) {
@@ -2740,6 +2762,15 @@ hipError_t launch_clear_words(unsigned long long* p, size_t n, hipStream_t s)
     size_t blocks = (n + 255) / 256;
     if (blocks > 1024) blocks = 1024;
     hipLaunchKernelGGL(k_clear_words, dim3((unsigned)blocks), dim3(256), 0, s, p, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_wave_tables(const WaveTabs& t, hipStream_t s)
+{
+    int most = 1;
+    for (int kind = 0; kind < 2; ++kind)
+        for (int lg = 0; lg < kLaneCounts; ++lg) most = t.n[kind][lg] > most ? t.n[kind][lg] : most;
+    hipLaunchKernelGGL(k_wave_tables, dim3((most + 255) / 256, 2 * kLaneCounts), dim3(256), 0, s, t);
     return hipGetLastError();
 }
 
