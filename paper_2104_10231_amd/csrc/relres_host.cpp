@@ -1909,6 +1909,15 @@ int relres_autotune(relres_ctx* c, const double* pos, const double* box, void* s
 
 namespace {
 
+// Blocks of a force launch for the rows of one kind at `lanes` per row: a
+// multiple of 8, the XCDs.
+int force_blocks(const relres_ctx* c, int kind, int lanes)
+{
+    const long long rows = kind == 0 ? c->n : c->n_sites;
+    const long long threads = c->nsys > 1 && rows > 0 ? 64LL * c->wave_tabs.n[kind][log2i(lanes)] : rows * lanes;
+    return (int)(((threads + kForceBlock - 1) / kForceBlock + 7) / 8 * 8);
+}
+
 // Arguments of one force launch over the lists of the last build, with the
 // lane split of the context; energy/virial buffers are the caller's.
 ForceArgs force_args(const relres_ctx* c, const double* pos, void* forces, double* energy,
@@ -1917,10 +1926,6 @@ ForceArgs force_args(const relres_ctx* c, const double* pos, void* forces, doubl
     const bool sites = c->n_sites > 0;
     const bool ew = energy || virial;
     const int la = force_lanes(c, 0, ew), lb = force_lanes(c, 1, ew);
-    auto blocks = [](long long rows, int lanes) {
-        long long b = (rows * lanes + kForceBlock - 1) / kForceBlock;
-        return (int)((b + 7) / 8 * 8);
-    };
     ForceArgs a{};
     a.pos = pos;
     for (int k = 0; k < 3; ++k) {
@@ -1947,8 +1952,8 @@ ForceArgs force_args(const relres_ctx* c, const double* pos, void* forces, doubl
     a.forces = forces;
     a.energy = energy;
     a.virial = virial;
-    a.blocks_a = blocks(c->n, la);
-    a.blocks_b = sites ? blocks(c->n_sites, lb) : 0;
+    a.blocks_a = force_blocks(c, 0, la);
+    a.blocks_b = force_blocks(c, 1, lb);
     a.lanes_a = la;
     a.lanes_b = lb;
     a.log_lanes_a = log2i(la);
@@ -1969,8 +1974,6 @@ ForceArgs force_args(const relres_ctx* c, const double* pos, void* forces, doubl
             a.sys_wave[kind] = t.first + (size_t)(2 + kind * kLaneCounts + lg) * (t.nsys + 1);
             a.n_waves[kind] = t.n[kind][lg];
         }
-        a.blocks_a = blocks(a.n_waves[0], 64);
-        a.blocks_b = sites ? blocks(a.n_waves[1], 64) : 0;
     }
     return a;
 }
@@ -1996,7 +1999,10 @@ int enqueue_forces(relres_ctx* c, const double* pos, void* forces, double* energ
         // energy/virial records: a fresh buffer may hold another context's
         // records, whose tags could match this context's; clear it (tag 0)
         const long long g0 = c->alloc_generation;
-        const size_t rec_bytes = (size_t)kEwRecBytes * (size_t)(a.blocks_a + a.blocks_b + kEwGroups);
+        // (of the split with energy and virial also in a call without, so that
+        // either kind may be captured after a call of the other)
+        const int blocks = force_blocks(c, 0, force_lanes(c, 0, true)) + force_blocks(c, 1, force_lanes(c, 1, true));
+        const size_t rec_bytes = (size_t)kEwRecBytes * (size_t)(blocks + kEwGroups);
         TRY(ensure(c->d_partials, rec_bytes, &c->alloc_generation));
         if (c->alloc_generation != g0)
             HIP_TRY(launch_clear_words(c->d_partials.as<unsigned long long>(),

@@ -70,3 +70,30 @@ def test_lane_changes_inside_a_capture():
         for lanes in LANES:
             assert torch.equal(outs[lanes], want[lanes]), (replay, lanes)
     rr.close()
+
+
+@pytest.mark.parametrize("side", [40, 84])
+@pytest.mark.parametrize("energy_first", [False, True])
+def test_either_kind_of_call_prepares_the_other(side, energy_first):
+    """Forces-only launches and launches with energy and virial split their rows
+    differently (64000 and 592704 atoms): a call of one kind leaves nothing for
+    the first of the other to allocate, so that one may be captured and the
+    other's captured launches stay valid."""
+    import torch
+    n, density = side ** 3, 0.0125
+    print(f"[lanes] {n} atoms, energy first {energy_first}", flush=True)
+    a = density ** (-1.0 / 3.0)
+    k = np.arange(n)
+    x = (np.stack([k // (side * side), (k // side) % side, k % side], 1) + 0.5) * a
+    s = w.two_atoms(5.0, box_len=side * a)
+    s = s.replace(pos=x, types=(k % 3 == 0).astype(np.int32), mol=(k // 3).astype(np.int32),
+                  excl_offsets=np.zeros(n + 1, np.int32))
+    rr = make_relres(s, 32)
+    p = torch.from_numpy(x).cuda()
+    rr.build_lists(p, s.box)
+    rr.forces(p, want_energy=energy_first, want_virial=energy_first)
+    before = rr.generation()
+    rr.forces(p, want_energy=not energy_first, want_virial=not energy_first)
+    torch.cuda.synchronize()
+    assert rr.generation() == before
+    rr.close()
