@@ -469,6 +469,10 @@ int upload_tables(relres_ctx* c)
         const double* src = reinterpret_cast<const double*>(&c->coef64[k]);
         float* dst = reinterpret_cast<float*>(&coef32[k]);
         for (size_t q = 0; q < sizeof(PairCoef<double>) / sizeof(double); ++q) dst[q] = (float)src[q];
+        // the zone's code also gives the constant inside it, at d = 0 (cg_term):
+        // in a zone too narrow for FP32 (1e-14 A) these would be 0 * inf there
+        for (int q = 3; q < 5; ++q)
+            coef32[k].sp[q] = (float)std::max(-1e37, std::min(1e37, c->coef64[k].sp[q]));
     }
     HIP_TRY(hipMemcpy(c->d_coef64.p, c->coef64.data(), sizeof(PairCoef<double>) * c->coef64.size(),
                       hipMemcpyHostToDevice));
