@@ -610,14 +610,16 @@ int list_rows_per_wave(const GridHost& g, long long launch_rows, int rows)
 // the difference is not the nearest image yet, folded with the rounded box
 // edge: below d = 8 * 2^-24 A per axis in all.  A pair at distance r then has
 // an FP32 distance within sqrt(3) d of r, and its square is rounded by less
-// than 8 * 2^-24.  Where that bound says nothing (or a box does not fit
-// FP32), every pair is left to the FP64 recipe.
+// than 8 * 2^-24.  Where that bound says nothing (a box that does not fit FP32,
+// or one cell along an axis, whose rows are up to 2 A apart: 9 * 2^-24 A),
+// every pair is left to the FP64 recipe.
 void list_filter(GeomDev& d, double rl, int reach)
 {
     double A = 0.0;
     for (int k = 0; k < 3; ++k) A = std::max(A, std::min(0.5 * d.box[k], reach * d.box[k] / d.n[k]));
     const double u = std::ldexp(1.0, -24), slack = std::sqrt(3.0) * 8.0 * u * A * 1.01;
-    if (!(slack < 0.5 * rl) || !(std::max({d.box[0], d.box[1], d.box[2], rl}) < 1e12)) {
+    if (!(slack < 0.5 * rl) || std::min({d.n[0], d.n[1], d.n[2]}) < 2 ||
+        !(std::max({d.box[0], d.box[1], d.box[2], rl}) < 1e12)) {
         d.filter_lo = -1.0f;
         d.filter_hi = INFINITY;
         return;
