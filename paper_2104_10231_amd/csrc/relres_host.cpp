@@ -370,7 +370,8 @@ struct relres_ctx {
     double md_ftm2v = 0.0;
     int md_rebuild = 10;
     int md_cur = 0;                   // which of the two state buffers is current
-    DBuf d_mass, d_md_state, d_md_xref, d_md_vsave, d_md_Fb, d_md_F, d_md_E, d_md_W, d_md_part;
+    DBuf d_mass, d_md_state, d_md_xref, d_md_vsave, d_md_Fb, d_md_F, d_md_E, d_md_W, d_md_part,
+        d_md_sums;
 
     bool timing = false;
     std::vector<hipEvent_t> ev_free;
@@ -2657,6 +2658,18 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
         first = true;
         return RELRES_OK;
     };
+    // the kinetic partials of the last kick, added up in groups where they are
+    // many: every block of a drift reads all that are left
+    auto gather = [&]() -> int {
+        const int groups = md_groups(nparts);
+        if (groups == nparts) return RELRES_OK;
+        long long none = 0;                // a run is not captured
+        TRY(ensure(c->d_md_sums, sizeof(double) * (size_t)groups, &none));
+        HIP_TRY(launch_md_gather(m.partial, nparts, c->d_md_sums.as<double>(), s));
+        m.partial = c->d_md_sums.as<double>();
+        nparts = groups;
+        return RELRES_OK;
+    };
     // drift to step `step` and the bonded forces there: one launch where no term
     // crosses a bonded block, else two (the bonded launch reads other blocks'
     // new positions).  From the second step on, the drift also does the scalar
@@ -2667,6 +2680,7 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
         DriftArgs d{};
         d.st_in = d.st_out = m.st;
         if (step > 1) {
+            TRY(gather());
             const int next = 1 - c->md_cur;
             d.st_out = stb + next;
             d.nparts = nparts;
@@ -2678,7 +2692,6 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
             c->md_cur = next;
             m.st = stb + next;
         }
-        m.partial = c->d_md_part.as<double>();
         if (!c->bond_closed) {
             HIP_TRY(launch_md_drift(m, d, prec, s));
             return enqueue_bonded(c, pos, Fb, false, out, s);
@@ -2704,6 +2717,7 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
             // first thermostat half step
             TRY(relres_forces(c, pos, F, nullptr, nullptr, s));
             TRY(enqueue_bonded(c, pos, F, true, false, s));
+            m.partial = c->d_md_part.as<double>();
             nparts = md_blocks(c->n);
             HIP_TRY(launch_md_kinetic(m, s));
             HIP_TRY(launch_md_scalar(m.st, m.partial, nparts, m.ftm2v, 0, nsteps > 0, nullptr, nullptr,
@@ -2722,9 +2736,11 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
             TRY(finish_step(step));
         }
         // the second half step of the last step
-        if (nsteps > 0)
+        if (nsteps > 0) {
+            TRY(gather());
             HIP_TRY(launch_md_scalar(m.st, m.partial, nparts, m.ftm2v, 1, 0, e_nb, w_nb, eb,
                                      row_of(nsteps), s));
+        }
         HIP_TRY(launch_md_finish(m, s));
         TRY(confirm());
         ended = true;
@@ -2858,7 +2874,7 @@ void relres_destroy(relres_ctx* c)
     for (DBuf* b : {&c->d_bond_blocks, &c->d_bond_passes, &c->d_bond_terms, &c->d_term_par, &c->d_atom_slot,
                     &c->d_bond_part, &c->d_bond_sum,
                     &c->d_mass, &c->d_md_state, &c->d_md_xref,
-                    &c->d_md_F, &c->d_md_E, &c->d_md_W, &c->d_md_part, &c->d_md_vsave, &c->d_md_Fb})
+                    &c->d_md_F, &c->d_md_E, &c->d_md_W, &c->d_md_part, &c->d_md_sums, &c->d_md_vsave, &c->d_md_Fb})
         release(*b);
     for (DBuf* b : {&c->d_coef64, &c->d_coef32, &c->d_hybrid, &c->d_types, &c->d_mol, &c->d_excl_off,
                     &c->d_excl_idx, &c->d_grids, &c->d_wpos, &c->d_key_a, &c->d_key_s,

@@ -393,6 +393,11 @@ hipError_t launch_md_drift_bonded(const MdArgs& m, const DriftArgs& d, const Bon
 // positions, velocities and thermostat state at a list build: m.xref = pos,
 // vsave = vel, *ssave = *m.st
 hipError_t launch_md_mark(const MdArgs& m, double* vsave, MdState* ssave, hipStream_t s);
+// The kinetic partials of a force launch are read by every block of the drift
+// after it, so that work grows with the square of the system: above kMdParts
+// of them a launch before adds them up in groups (md_groups: how many are left).
+int md_groups(int nparts);
+hipError_t launch_md_gather(const double* partial, int nparts, double* sums, hipStream_t s);
 hipError_t launch_md_kinetic(const MdArgs& m, hipStream_t s);
 // kinetic energy from the partials; second / first thermostat half steps;
 // with row, one row of thermodynamic output
