@@ -324,7 +324,8 @@ struct relres_ctx {
     GridDev uploaded[2] = {};         // descriptors currently on the device
     bool grids_valid = false;
     Status* h_status = nullptr;
-    Status* h_query = nullptr;        // pinned landing place of relres_moved_atoms
+    Status* h_query = nullptr;        // pinned landing place of single words: relres_moved_atoms,
+                                      // the closing count of relres_md_run
     unsigned nonfinite_seen = 0;
     unsigned moved_seen = 0;          // Status::moved at the last examination
     unsigned ew_failed_seen = 0;      // Status::ew_failed at the last examination
@@ -2742,12 +2743,14 @@ int relres_md_run(relres_ctx* c, double* pos, double* vel, int nsteps, int therm
                                      row_of(nsteps), s));
         }
         HIP_TRY(launch_md_finish(m, s));
+        // the last steps since the previous build must not have outrun the skin
+        // either: the closing count goes to a word of its own, so that the
+        // build's status is still there and one wait serves both
+        HIP_TRY(hipMemcpyAsync(&c->h_query->md_stale, m.stale, sizeof(unsigned), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
         TRY(confirm());
         ended = true;
-        // the last steps since the previous build must not have outrun the skin either
-        HIP_TRY(hipMemcpyAsync(c->h_status, c->d_status.p, sizeof(Status), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        return c->h_status->md_stale != stale_seen ? stale() : RELRES_OK;
+        return c->h_query->md_stale != stale_seen ? stale() : RELRES_OK;
     };
     auto run = [&]() -> int {
         TRY(drain_check(c));
