@@ -177,13 +177,24 @@ def _ptr(a) -> Optional[int]:
     return None if a is None else a.ctypes.data
 
 
+def _current_stream_reader(core):
+    """A function that reads the handle of the current stream of the current
+    device: from the entries of ``core`` (torch._C) that do not build a
+    torch.cuda.Stream object, which takes 2.6 us, a third of a force call's
+    time on the host; through the public call where they are missing."""
+    try:
+        raw, device = core._cuda_getCurrentRawStream, core._cuda_getDevice
+    except AttributeError:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+_current_stream = _current_stream_reader(torch._C)
+
+
 def _stream(stream) -> int:
-    """The handle of a stream, by default the current one of the current
-    device, read without building a torch.cuda.Stream object: that takes
-    2.6 us, a third of a force call's time on the host."""
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    """The handle of a stream, by default the current one."""
+    return stream.cuda_stream if stream is not None else _current_stream()
 
 
 def _dp(a: np.ndarray):
