@@ -170,6 +170,7 @@ struct ForceArgs {
     const int4* waves_tab[2];
     const int* sys_wave[2];
     int n_waves[2];
+    int packed;               // rows of several systems share a wave (forces only)
     double* wave_ew;          // nsys > 1: 8 FP64 sums per wave (atom waves, then site waves)
     // atom list rows (all atoms, atom-grid order); record = (caller index,
     // type + 32 system, stored entries, 1 if hybrid)

@@ -1835,8 +1835,10 @@ __device__ __forceinline__ void kick_read(const MdKick& k, int i, int c, double&
 // Kick: the half kick of a dynamics step follows.  What it needs is read under
 // the pair terms, in launches with energy and virial (no registers left for it)
 // after them.
-template <typename S, typename TF, bool EW, bool LDS, bool PC, int B, bool Kick>
-__global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : EW && PC && !LDS ? 5 : 6) void k_forces(
+// Packed: rows of several systems share a wave, each lane with its row's box
+// (forces-only launches of many small systems, ForceArgs::packed).
+template <typename S, typename TF, bool EW, bool LDS, bool PC, int B, bool Kick, bool Packed>
+__global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : (EW && PC && !LDS) || Packed ? 5 : 6) void k_forces(
     ForceArgs a, Cutoffs<S> cut, Cutoffs<double> cut64)
 {
     const bool rb = (int)blockIdx.x >= a.blocks_a;
@@ -1853,7 +1855,8 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : EW && PC && !LDS
     const int lw = __builtin_amdgcn_readfirstlane(logical * (kForceBlock / kWave) +
                                                   (int)threadIdx.x / kWave);
     int row = ((int)threadIdx.x & (kWave - 1)) >> lg, rows = kWave >> lg, sys = 0;
-    if (a.nsys == 1) {
+    const bool plain = Packed || a.nsys == 1;
+    if (plain) {
         rows = min(rows, (rb ? a.n_srow : a.n_arow) - (lw << (6 - lg)));
     } else {
         int4 w = make_int4(0, 0, 0, 0);
@@ -1863,7 +1866,7 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : EW && PC && !LDS
         row += w.x;
     }
     const bool live = ((int)threadIdx.x & (kWave - 1)) >> lg < rows;
-    if (a.nsys == 1) row += lw << (6 - lg);
+    if (plain) row += lw << (6 - lg);
 
     // the first words of the LDS tables are read before the row record, so
     // the two reads overlap (written to LDS once the record is in)
@@ -1986,7 +1989,7 @@ __global__ __launch_bounds__(kForceBlock, B == kBatchWide ? 1 : EW && PC && !LDS
             if (sub < 3) kick_read<TF>(a.kick, ui, sub, kv, kf, km);
         // the box (several systems: a read) after the gathers, so the wave does
         // not wait for it before issuing them
-        const BoxV bx = wave_box(a, sys);
+        const BoxV bx = Packed ? row_box(a, rec.y >> kTypeBits) : wave_box(a, sys);
         const int ro = ti * a.ntypes;
         const RowTab<S> rt{coef + ro, coef64 + ro, PC ? pcut + ro : nullptr,
                            PC ? pcut64 + ro : nullptr};
@@ -2325,18 +2328,20 @@ template <typename S, typename TF, bool EW, bool LDS, bool PC>
 void launch_force_kernel(const ForceArgs& a, const double* cut64, dim3 grid, dim3 block,
                          hipStream_t s)
 {
-#define RELRES_FORCES(B, KICK)                                                                   \
-    hipLaunchKernelGGL((k_forces<S, TF, EW, LDS, PC, B, KICK>), grid, block, 0, s, a,            \
+#define RELRES_FORCES(B, KICK, PACKED)                                                           \
+    hipLaunchKernelGGL((k_forces<S, TF, EW, LDS, PC, B, KICK, PACKED>), grid, block, 0, s, a,    \
                        cut_as<S>(cut64), cut_as<double>(cut64))
     if constexpr (EW) {
-        if (a.kick.vel) RELRES_FORCES(kBatch, true);
-        else RELRES_FORCES(kBatch, false);
+        if (a.kick.vel) RELRES_FORCES(kBatch, true, false);
+        else RELRES_FORCES(kBatch, false, false);
     } else if (a.kick.vel) {
-        if (a.wide_batch) RELRES_FORCES(kBatchWide, true);
-        else RELRES_FORCES(kBatch, true);
+        if (a.wide_batch) RELRES_FORCES(kBatchWide, true, false);
+        else RELRES_FORCES(kBatch, true, false);
+    } else if (a.packed) {
+        RELRES_FORCES(kBatch, false, true);
     } else {
-        if (a.wide_batch) RELRES_FORCES(kBatchWide, false);
-        else RELRES_FORCES(kBatch, false);
+        if (a.wide_batch) RELRES_FORCES(kBatchWide, false, false);
+        else RELRES_FORCES(kBatch, false, false);
     }
 #undef RELRES_FORCES
 }
