@@ -263,8 +263,8 @@ struct GridHost {
     std::vector<int> sys_n;           // [nsys][3] cells per axis
     std::vector<GeomDev> geom;        // per system, as last uploaded
     std::vector<int> wave_sys;        // system of every list-kernel wave, as last uploaded
-    DBuf geom_dev, wave_sys_dev, cell_sys, rank_of_lin, lin_of_rank, nbr, count, start, user_unsorted, user, pos,
-        meta, row_cell, list, nrow;
+    DBuf geom_dev, wave_sys_dev, cell_sys, rank_of_lin, lin_of_rank, nbr, count, start, user_unsorted,
+        chain_head, user, pos, meta, row_cell, list, nrow;
     GridDev dev{};
 };
 
@@ -722,14 +722,14 @@ int setup_grid(GridHost& g, const std::vector<double>& rl_sys, const std::vector
         TRY(ensure(g.rank_of_lin, sizeof(int) * total, gen));
         TRY(ensure(g.lin_of_rank, sizeof(int) * total, gen));
         TRY(ensure(g.cell_sys, sizeof(int) * total, gen));
-        TRY(ensure(g.count, sizeof(int) * 2 * (size_t)total, gen));   // counts, chain heads
+        TRY(ensure(g.count, sizeof(int) * total, gen));
         TRY(ensure(g.start, sizeof(int) * (total + 1), gen));
         if (!nbr.empty())
             HIP_TRY(hipMemcpy(g.nbr.p, nbr.data(), sizeof(int) * nbr.size(), hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(g.rank_of_lin.p, rank_of_lin.data(), sizeof(int) * total, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(g.lin_of_rank.p, lin_of_rank.data(), sizeof(int) * total, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(g.cell_sys.p, cell_sys.data(), sizeof(int) * total, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemset(g.count.p, 0, sizeof(int) * 2 * (size_t)total));
+        HIP_TRY(hipMemset(g.count.p, 0, sizeof(int) * total));
         g.nsys = nsys;
         g.sys_n = nn;
         g.div = div;
@@ -853,15 +853,18 @@ int set_buckets(relres_ctx* c, GridHost& ga, GridHost* gs, bool want, bool* used
     int cap_s = (want && gs) ? bucket_slots(*gs) : 0;
     const bool use = cap_a > 0 && (!gs || cap_s > 0);
     if (!use) cap_a = cap_s = 0;
-    if (cap_a > 0) TRY(ensure(ga.user_unsorted, sizeof(int) * (size_t)ga.ncell * cap_a, &c->alloc_generation));
-    ga.dev.bucket_cap = cap_a;
-    ga.dev.user_unsorted = ga.user_unsorted.as<int>();
-    if (gs) {
-        if (cap_s > 0)
-            TRY(ensure(gs->user_unsorted, sizeof(int) * (size_t)gs->ncell * cap_s, &c->alloc_generation));
-        gs->dev.bucket_cap = cap_s;
-        gs->dev.user_unsorted = gs->user_unsorted.as<int>();
-    }
+    const auto set = [&](GridHost& g, int cap) -> int {
+        if (cap > 0) {
+            TRY(ensure(g.user_unsorted, sizeof(int) * (size_t)g.ncell * cap, &c->alloc_generation));
+            TRY(ensure(g.chain_head, sizeof(int) * (size_t)g.ncell * kPlaceChains, &c->alloc_generation));
+        }
+        g.dev.bucket_cap = cap;
+        g.dev.user_unsorted = g.user_unsorted.as<int>();
+        g.dev.chain_head = g.chain_head.as<int>();
+        return RELRES_OK;
+    };
+    TRY(set(ga, cap_a));
+    if (gs) TRY(set(*gs, cap_s));
     *used = use;
     return RELRES_OK;
 }
@@ -2904,7 +2907,7 @@ void relres_destroy(relres_ctx* c)
         release(*b);
     for (GridHost* g : {&c->ga, &c->gs})
         for (DBuf* b : {&g->geom_dev, &g->wave_sys_dev, &g->cell_sys, &g->rank_of_lin, &g->lin_of_rank, &g->nbr,
-                        &g->count, &g->start, &g->user_unsorted, &g->user, &g->pos, &g->meta,
+                        &g->count, &g->start, &g->user_unsorted, &g->chain_head, &g->user, &g->pos, &g->meta,
                         &g->row_cell, &g->list, &g->nrow})
             release(*b);
     if (c->h_grids) (void)hipHostFree(c->h_grids);

@@ -88,8 +88,9 @@ struct GridDev {
                               // only for stencil 3
     int stencil;              // cells per axis of the list stencil: 3 (cells of at least the
                               // list radius) or 5 (cells of at least half of it)
-    int* count;               // per cell (by rank); zero between builds.  After them, per cell,
-                              // the last member that found its bucket full
+    int* count;               // per cell (by rank); zero between builds
+    int* chain_head;          // with bucket_cap > 0: per cell the last members of its
+                              // kPlaceChains chains of members that found the bucket full
     int* start;               // ncell + 1 exclusive offsets (by rank)
     int* user_unsorted;       // member caller indices, cell-grouped; with bucket_cap > 0 the
                               // per-cell buckets (ncell x bucket_cap) that k_bin fills
@@ -226,7 +227,7 @@ hipError_t launch_cellsort(GridDev* grids_dev, int ncell_a, int ncell_total, lon
 // Scan, scatter and cell sort in one launch.  k_bin has filed every member
 // into its cell's bucket (GridDev::bucket_cap > 0); each block adds up the
 // counts of the cells before its own, then ranks and places its cells' members
-// (a cell that outgrew its bucket finds the rest in its chain or in the key
+// (a cell that outgrew its bucket finds the rest in its chains or in the key
 // arrays).  Up to kPlaceMaxCells cells of both grids together every block reads
 // all the counts before its cells; above, a launch before it adds up segments
 // of kPlaceSeg cells into seg_tot (place_segments of each grid).  Against two
@@ -235,6 +236,7 @@ hipError_t launch_cellsort(GridDev* grids_dev, int ncell_a, int ncell_total, lon
 // 100000 atoms in all 65.7 (73.9).
 constexpr int kPlaceMaxCells = 8192;
 constexpr int kPlaceSeg = 1024;
+constexpr int kPlaceChains = 16;      // chains of members beyond a cell's bucket
 int place_segments(int ncell);
 hipError_t launch_place(GridDev* grids_dev, int ncell_a, int ncell_s, long long members, int n,
                         const int2* key_a, const int2* key_s, const double4* wpos, TopoDev topo,

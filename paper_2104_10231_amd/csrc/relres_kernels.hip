@@ -183,10 +183,10 @@ __device__ __forceinline__ int claim_slots(RELRES_GLOBAL int* count, int r, cons
 }
 
 // One-launch placement: member i goes straight into its cell's bucket; one that
-// finds it full goes to the head of the cell's chain (count[ncell + cell] is its
-// last member), and the member before it is returned as its key's second word
-// (the first of a chain gets the head of an earlier build: a chain is followed
-// for as many members as the cell's count says).  Otherwise that word is the slot.
+// finds it full goes to the head of one of the cell's chains, in turn by its
+// slot, and the member before it is returned as its key's second word (the first
+// of a chain gets the head of an earlier build: a chain is followed for as many
+// members as the cell's count says).  Otherwise that word is the slot.
 __device__ __forceinline__ int file_member(const GridDev& g, int cell, int slot, int i)
 {
     if (g.bucket_cap <= 0) return slot;
@@ -194,8 +194,8 @@ __device__ __forceinline__ int file_member(const GridDev& g, int cell, int slot,
         gbl(g.user_unsorted)[(size_t)cell * g.bucket_cap + slot] = i;
         return slot;
     }
-    return __hip_atomic_exchange(gbl(g.count) + g.ncell + cell, i, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+    const size_t chain = (size_t)cell * kPlaceChains + (slot - g.bucket_cap) % kPlaceChains;
+    return __hip_atomic_exchange(gbl(g.chain_head) + chain, i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ int lin_cell(const double w[3], const double inv[3], const int n[3])
@@ -549,10 +549,19 @@ __global__ void k_cellsort(const GridDev* __restrict__ grids, int ncell_a, int n
 // run first), writes its cells' starts, then
 // ranks each cell's members by caller index as k_cellsort does and writes
 // the sorted arrays.  A cell with more members than its bucket holds finds the
-// others in its chain, or, when they are many, all of them, already in caller
-// order, by a wave-wide pass over the key array.
+// others in its chains, or, above kPlaceWide members, all of them, already in
+// caller order, by a wave-wide pass over the key array.
 // The counts stay as they are: the list kernel clears them.
 constexpr int kPlaceThreads = 256;
+constexpr int kPlaceWide = 1024;      // most members of a cell that a wave ranks in LDS
+
+// Orders a wave's LDS writes before its lanes' later reads of each other's.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // Grids of many cells: the members of every kPlaceSeg consecutive cells, one
 // block each (blocks 0 .. nseg_a - 1 the atom grid's, the rest the site
@@ -600,6 +609,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_place(const GridDev* __restri
     constexpr int kCells = kWaves * kCellsPerWave;     // at most 64: one wave scans them
     __shared__ int wtot[kWaves];
     __shared__ int cnt_sh[kCells], first_sh[kCells];
+    __shared__ int wide[kWaves][kPlaceWide];
     const bool site = (int)blockIdx.x >= blocks_a;
     const GridDev& g = grids[site ? 1 : 0];
     const int c0 = ((int)blockIdx.x - (site ? blocks_a : 0)) * kCells;
@@ -711,27 +721,33 @@ __global__ __launch_bounds__(kPlaceThreads) void k_place(const GridDev* __restri
             continue;
         }
         const int2* __restrict__ key = site ? key_s : key_a;
-        const int over = lenk - cap;
-        if (over <= kWave && (long long)over * kWave <= n) {
-            // the cell outgrew its bucket: the members beyond it from its
-            // chain, one dependent read each, where that is fewer than the
-            // rounds of the pass below
-            const int v = lane < cap ? bucket[(size_t)ck * cap + lane] : 0x7fffffff;
-            int w = 0x7fffffff;
-            int j = __builtin_amdgcn_readfirstlane(gcount[nc + ck]);
-            for (int t = 0; t < over && (unsigned)j < (unsigned)n; ++t) {
-                if (lane == t) w = j;
-                if (t + 1 < over) j = __builtin_amdgcn_readfirstlane(key[j].y);
+        if (lenk <= kPlaceWide) {
+            // the cell outgrew its bucket: the members beyond it from its chains,
+            // one lane each (dependent reads, 1 / kPlaceChains of them), then all
+            // ranked from LDS.  A slab of 405000 atoms in a box ten times as long,
+            // every site cell beyond its bucket: build 889 us; 6600 with a pass over
+            // the keys for each cell of more than 64 members beyond, and 1172 with
+            // the scan, scatter and sort launches
+            int* all = wide[wave];
+            const int over = lenk - cap;
+            if (lane < cap) all[lane] = bucket[(size_t)ck * cap + lane];
+            if (lane < kPlaceChains) {
+                int j = gbl(g.chain_head)[(size_t)ck * kPlaceChains + lane];
+                for (int t = lane; t < over; t += kPlaceChains) {
+                    const bool in = (unsigned)j < (unsigned)n;
+                    all[cap + t] = in ? j : 0x7fffffff;
+                    j = in ? key[j].y : -1;
+                }
             }
-            int rv = 0, rw = 0;
-            for (int t = 0; t < lenk; ++t) {
-                const int u_t = t < cap ? readlane_i(v, t) : readlane_i(w, t - cap);
-                rv += u_t < v;
-                rw += u_t < w;
+            wave_lds_fence();
+            for (int t = lane; t < lenk; t += kWave) {
+                const int v = all[t];
+                int rk = 0;
+#pragma unroll 8
+                for (int u = 0; u < lenk; ++u) rk += all[u] < v;
+                if (v != 0x7fffffff) place_member(g, site, ck, bk + rk, v, wpos, topo, user2arow);
             }
-            if (lane < cap) place_member(g, site, ck, bk + rv, v, wpos, topo, user2arow);
-            if (lane < over && w != 0x7fffffff)
-                place_member(g, site, ck, bk + rw, w, wpos, topo, user2arow);
+            wave_lds_fence();                   // used again for the wave's next cell
             continue;
         }
         // far more members than the bucket holds: in caller order from the keys
