@@ -745,22 +745,28 @@ int setup_grid(GridHost& g, const std::vector<double>& rl_sys, const std::vector
     double densest = 0.0;
     for (int sy = 0; sy < nsys; ++sy) {
         GeomDev& d = geom[sy];
-        std::memset(&d, 0, sizeof d);
         const double* box = boxes + 3 * sy;
-        for (int k = 0; k < 3; ++k) {
-            d.n[k] = nn[3 * sy + k];
-            d.inv_cell[k] = d.n[k] / box[k];
-            d.box[k] = box[k];
-            d.inv_box[k] = 1.0 / box[k];
-            d.half[k] = 0.5 * box[k];
+        const double rl2 = rl_sys[sy] * rl_sys[sy];
+        const GeomDev* was = same && g.geom.size() == geom.size() ? &g.geom[sy] : nullptr;
+        if (was && was->rl2 == rl2 && std::equal(box, box + 3, was->box)) {
+            d = *was;                  // box, cells and radius of the last build
+        } else {
+            std::memset(&d, 0, sizeof d);
+            for (int k = 0; k < 3; ++k) {
+                d.n[k] = nn[3 * sy + k];
+                d.inv_cell[k] = d.n[k] / box[k];
+                d.box[k] = box[k];
+                d.inv_box[k] = 1.0 / box[k];
+                d.half[k] = 0.5 * box[k];
+            }
+            d.rl2 = rl2;
+            list_filter(d, rl_sys[sy], div + 1);
         }
         d.cell_base = cell_base[sy];
         d.row_base = rows;
         d.members = members_sys[sy];
         d.wave_base = waves;
-        d.rl2 = rl_sys[sy] * rl_sys[sy];
         d.half_skin2 = 0.25 * skin_sys[sy] * skin_sys[sy];
-        list_filter(d, rl_sys[sy], div + 1);
         rows += members_sys[sy];
         waves += (members_sys[sy] + g.rpw - 1) / g.rpw;
         // expected neighbours within the system's list radius
