@@ -2035,8 +2035,9 @@ int enqueue_forces(relres_ctx* c, const double* pos, void* forces, double* energ
         const long long g0 = c->alloc_generation;
         // (of the split with energy and virial also in a call without, so that
         // either kind may be captured after a call of the other)
-        const int blocks = force_blocks(c, 0, force_lanes(c, 0, true), false) +
-                           force_blocks(c, 1, force_lanes(c, 1, true), false);
+        const int blocks = energy || virial ? a.blocks_a + a.blocks_b
+                                            : force_blocks(c, 0, force_lanes(c, 0, true), false) +
+                                                  force_blocks(c, 1, force_lanes(c, 1, true), false);
         const size_t rec_bytes = (size_t)kEwRecBytes * (size_t)(blocks + kEwGroups);
         TRY(ensure(c->d_partials, rec_bytes, &c->alloc_generation));
         if (c->alloc_generation != g0)

@@ -177,24 +177,23 @@ def _ptr(a) -> Optional[int]:
     return None if a is None else a.ctypes.data
 
 
-def _current_stream_reader(core):
-    """A function that reads the handle of the current stream of the current
-    device: from the entries of ``core`` (torch._C) that do not build a
+def _stream_readers(core):
+    """(raw, device): raw(device()) is the handle of the current stream of the
+    current device.  From the entries of ``core`` (torch._C) that do not build a
     torch.cuda.Stream object, which takes 2.6 us, a third of a force call's
-    time on the host; through the public call where they are missing."""
+    time on the host; through the public call where one is missing."""
     try:
-        raw, device = core._cuda_getCurrentRawStream, core._cuda_getDevice
+        return core._cuda_getCurrentRawStream, core._cuda_getDevice
     except AttributeError:
-        return lambda: torch.cuda.current_stream().cuda_stream
-    return lambda: raw(device())
+        return (lambda device: torch.cuda.current_stream().cuda_stream), (lambda: None)
 
 
-_current_stream = _current_stream_reader(torch._C)
+_raw_stream, _device = _stream_readers(torch._C)
 
 
 def _stream(stream) -> int:
     """The handle of a stream, by default the current one."""
-    return stream.cuda_stream if stream is not None else _current_stream()
+    return _raw_stream(_device()) if stream is None else stream.cuda_stream
 
 
 def _dp(a: np.ndarray):

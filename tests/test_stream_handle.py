@@ -9,10 +9,11 @@ def test_private_entries_are_optional(monkeypatch):
     serves, and a given stream's own handle always does."""
     stream = types.SimpleNamespace(cuda_stream=4711)
     monkeypatch.setattr(relres.torch.cuda, "current_stream", lambda: stream)
-    for core in (types.SimpleNamespace(), types.SimpleNamespace(_cuda_getDevice=lambda: 3)):
-        monkeypatch.setattr(relres, "_current_stream", relres._current_stream_reader(core))
-        assert relres._stream(None) == 4711
-    core = types.SimpleNamespace(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda d: 100 + d)
-    monkeypatch.setattr(relres, "_current_stream", relres._current_stream_reader(core))
-    assert relres._stream(None) == 103
-    assert relres._stream(types.SimpleNamespace(cuda_stream=9)) == 9
+    for core, want in ((types.SimpleNamespace(), 4711),
+                       (types.SimpleNamespace(_cuda_getDevice=lambda: 3), 4711),
+                       (types.SimpleNamespace(_cuda_getDevice=lambda: 3,
+                                              _cuda_getCurrentRawStream=lambda d: 100 + d), 103)):
+        for name, value in zip(("_raw_stream", "_device"), relres._stream_readers(core)):
+            monkeypatch.setattr(relres, name, value)
+        assert relres._stream(None) == want
+        assert relres._stream(types.SimpleNamespace(cuda_stream=9)) == 9
