@@ -7,6 +7,7 @@ import pytest
 import workloads as w
 from _util import make_relres
 from test_gpu_md import _ctx, _hexane
+from test_gpu_md_regrow import _collapse
 
 pytestmark = pytest.mark.gpu
 
@@ -158,3 +159,32 @@ def test_a_run_that_blows_up_is_reported(steps):
     v[s.n - 1, 2] = float("nan")
     _stale(lambda: rr.md_run(p, v, steps))
     rr.close()
+
+
+def test_overflow_in_the_first_build_goes_back_to_it():
+    """Lists of a dilute frame, then a run from a dense one, whose first build
+    overflows, against a run whose rows were sized for the dense frame: the same
+    result bit for bit, with and without a return to the build."""
+    import torch
+    s, _ = _collapse()
+    dense = (s.pos - 32.0) * 0.55 + 32.0
+    v0 = np.random.default_rng(4).normal(scale=1e-3, size=dense.shape)
+    res, regrows = [], []
+    for grown in (True, False):
+        print(f"[md] first build, grown {grown}", flush=True)
+        rr = make_relres(s, 64)
+        rr.set_launch(4, 4)
+        rr.build_lists(torch.from_numpy(s.pos).cuda(), s.box)
+        p, v = torch.from_numpy(dense).cuda(), torch.from_numpy(v0).cuda()
+        if grown:
+            rr.build_lists(p, s.box)
+        rr.md_setup(np.full(s.n, 5000.0), 1.0, 300.0, 1e9, rebuild_every=3)
+        before = rr.stats()["regrows"]
+        th = rr.md_run(p, v, 8, 2)
+        torch.cuda.synchronize()
+        regrows.append(rr.stats()["regrows"] - before)
+        res.append([t.cpu().numpy() for t in (p, v, th)])
+        rr.close()
+    assert regrows[0] == 0 and regrows[1] >= 1
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
