@@ -296,7 +296,7 @@ int relres_forces(relres_ctx *ctx, const double *pos, void *forces, double *ener
  * than the array holds (256 bytes, then 128 for every block of 256 threads
  * and for each of 16 record groups: up to 16366 blocks, e.g. a million rows
  * at 4 lanes per row) or, with energy or virial requested, for several
- * systems (their per-row partials need context buffers; forces only is
+ * systems (their sums per wave need context buffers; forces only is
  * fine).  Every call on one GPU shares that GPU's array: calls that overlap
  * on one GPU (several streams, threads or contexts at once) race and must be
  * serialised by the caller.  No timing events are recorded.  Asynchronous on

@@ -977,14 +977,14 @@ int refresh_list_stats(relres_ctx* c, hipStream_t s)
     // Launches with energy or virial are bound by issue, and each wave has its
     // sums over the lanes: E = 8, above 65536 waves 12, the nearest power of
     // two, but not one lane for rows of 8 entries nor 4 for hybrid rows of 32,
-    // whose many rounds wait one on the other.  At these rules / E = 8 rounded
-    // up: 80000 atoms at 14 A 47.0 / 57.2 us, 48000-atom hexane 21.1 / 23.5,
-    // 256 replicas 198 / 264; with the lower bounds / without: neopentane
-    // at 200000 atoms (10.9 and 26.9 entries per atom and site row) 26.5 / 31.6,
-    // at 400000 44.2 / 56.2, copolymer at 400000 51.9 / 58.7; with E = 12 / 8:
-    // hexane at 400000 atoms 81.7 / 89.1.  A launch of one system whose blocks
-    // would outgrow the records of relres_forces_noalloc takes E = 16, rounded
-    // up, half the lanes of the bounds.
+    // whose many rounds wait one on the other.  At these rules, at E = 8 rounded
+    // up and at E = 4 rounded up: 80000 atoms at 14 A 51.2, 60.0 and 60.0 us, hexane
+    // of 98304 atoms 28.0, 28.8 and 36.9, of 400000 81.7, 93.3 and 130, 256 replicas
+    // 201, 209 and 266.  With the lower bounds / without: neopentane of 200000
+    // atoms (10.9 and 26.9 entries per atom and site row) 26.5 / 31.6, of 400000
+    // 44.2 / 56.2, copolymer of 400000 51.9 / 58.7.  A launch of one system whose
+    // blocks would outgrow the records of relres_forces_noalloc takes E = 16,
+    // rounded up, half the lanes of the bounds.
     //
     // Forces only, a wave ends with three sums, and fewer lanes only lengthen
     // the rows' chains: E = 8, rounded up (to the nearest above 16 lanes: 80000

@@ -374,7 +374,8 @@ struct MdArgs {
     double* xref;                     // positions at the last list build
     double half_skin2;                // (skin / 2)^2
     unsigned int* stale;              // Status::md_stale
-    double* partial;                  // kinetic partials (k_md_kinetic's or the force launch's)
+    double* partial;                  // kinetic partials (k_md_kinetic's, the force launch's or
+                                      // their sums in groups)
     MdState* st;
 };
 // Drift of one step; with scalar != 0 every block first does the scalar work
