@@ -264,7 +264,7 @@ struct GridHost {
     std::vector<GeomDev> geom;        // per system, as last uploaded
     std::vector<int> wave_sys;        // system of every list-kernel wave, as last uploaded
     DBuf geom_dev, wave_sys_dev, cell_sys, rank_of_lin, lin_of_rank, nbr, count, start, user_unsorted,
-        chain_head, user, pos, meta, row_cell, list, nrow;
+        user, pos, meta, row_cell, list, nrow;
     GridDev dev{};
 };
 
@@ -860,13 +860,13 @@ int set_buckets(relres_ctx* c, GridHost& ga, GridHost* gs, bool want, bool* used
     const bool use = cap_a > 0 && (!gs || cap_s > 0);
     if (!use) cap_a = cap_s = 0;
     const auto set = [&](GridHost& g, int cap) -> int {
-        if (cap > 0) {
-            TRY(ensure(g.user_unsorted, sizeof(int) * (size_t)g.ncell * cap, &c->alloc_generation));
-            TRY(ensure(g.chain_head, sizeof(int) * (size_t)g.ncell * kPlaceChains, &c->alloc_generation));
-        }
+        const size_t slots = (size_t)g.ncell * cap;    // then the chains' heads
+        if (cap > 0)
+            TRY(ensure(g.user_unsorted, sizeof(int) * (slots + (size_t)g.ncell * kPlaceChains),
+                       &c->alloc_generation));
         g.dev.bucket_cap = cap;
         g.dev.user_unsorted = g.user_unsorted.as<int>();
-        g.dev.chain_head = g.chain_head.as<int>();
+        g.dev.chain_head = cap > 0 ? g.user_unsorted.as<int>() + slots : nullptr;
         return RELRES_OK;
     };
     TRY(set(ga, cap_a));
@@ -2914,7 +2914,7 @@ void relres_destroy(relres_ctx* c)
         release(*b);
     for (GridHost* g : {&c->ga, &c->gs})
         for (DBuf* b : {&g->geom_dev, &g->wave_sys_dev, &g->cell_sys, &g->rank_of_lin, &g->lin_of_rank, &g->nbr,
-                        &g->count, &g->start, &g->user_unsorted, &g->chain_head, &g->user, &g->pos, &g->meta,
+                        &g->count, &g->start, &g->user_unsorted, &g->user, &g->pos, &g->meta,
                         &g->row_cell, &g->list, &g->nrow})
             release(*b);
     if (c->h_grids) (void)hipHostFree(c->h_grids);
